@@ -2,9 +2,17 @@
 // of one implicit step (used by the adjoint of a converged step).
 //
 // A is row-major with leading dimension lda; only its lower triangle is read
-// and the factor L (A = L L^T) overwrites it.  Blocked right-looking
-// algorithm on 64x64 tiles: factor the diagonal tile in LDS, solve the panel
-// below it against L_kk^T, update the trailing lower tiles with L_ik L_jk^T.
+// and the factor L (A = L L^T) overwrites it.  Two-level blocked
+// right-looking algorithm without scratch memory:
+//   * inner steps of NB = 64 columns: the rows below the factored diagonal
+//     tile are solved against it (k_chol_panel), then the tiles of the rest
+//     of the outer block are updated with these 64 columns;
+//   * outer blocks of OB = 256 columns: the trailing matrix is read and
+//     written once per 256 columns, not once per 64 (at 64 that traffic
+//     alone, 19 GB at n = 7644, costs 4 ms at the rate of a copy).
+// Both updates run on the FP64 matrix cores (k_chol_update), and the
+// workgroup that updates the next diagonal tile factors it at once, so an
+// inner step is two launches.
 #include <algorithm>
 #include <cmath>
 
@@ -12,181 +20,375 @@
 
 namespace eipc {
 
-constexpr int NB = 64;
-constexpr int NBP = NB + 1;  // LDS row padding
+constexpr int NB = 64;        // inner block (columns per panel)
+constexpr int NBP = NB + 1;   // LDS row padding
+constexpr int OB = 256;       // outer block
 
-__device__ __forceinline__ double ld_a(const double *A, int64_t lda, int64_t n, int64_t r, int64_t c) {
-  return (r < n && c < n) ? A[r * lda + c] : (r == c ? 1.0 : 0.0);
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Factors the 64x64 tile s (lower triangle; LDS) in place, by a workgroup of
+// four wavefronts.  Wavefront w holds columns 16 w .. 16 w + 15, lane = row:
+// in step p wavefront p factors its 16 columns for all rows, passing column
+// entries between lanes by readlane, and the later wavefronts apply them.
+// Bound by the serial chain of 64 pivots (about 10 us a tile; the earlier
+// version, one thread taking the pivots and three barriers per column, took
+// 82 us).  k0 + 64 may pass n: the caller pads with the unit matrix.
+__device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k0, int64_t *info) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double a[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) a[j] = s[lane][16 * w + j];
+  for (int p = 0; p < 4; ++p) {
+    if (w == p) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int c = 16 * p + j;
+        double d = lane_value(a[j], c);
+        if (!(d > 0.0) || !isfinite(d)) {
+          if (lane == 0 && k0 + c < n) atomicCAS((unsigned long long *)info, 0ull, (unsigned long long)(k0 + c + 1));
+          d = 1.0;  // keep going with finite values; info reports the failure
+        }
+        const double rs = sqrt(d), ri = 1.0 / rs;
+        a[j] = lane == c ? rs : a[j] * ri;
+#pragma unroll
+        for (int l = j + 1; l < 16; ++l) a[l] -= a[j] * lane_value(a[j], 16 * p + l);
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s[lane][16 * p + j] = a[j];
+    }
+    __syncthreads();
+    if (w > p) {
+      double x[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = s[lane][16 * p + j];
+#pragma unroll
+      for (int l = 0; l < 16; ++l)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[l] -= x[j] * s[16 * w + l][16 * p + j];
+    }
+  }
+}
+
+// the diagonal tile at k0, loaded into s (unit matrix past n)
+__device__ __forceinline__ void load_diag(double (*s)[NBP], const double *A, int64_t n, int64_t lda, int64_t k0) {
+  for (int e = threadIdx.x; e < NB * NB; e += blockDim.x) {
+    const int r = e / NB, c = e % NB;
+    s[r][c] = (k0 + r < n && c <= r) ? A[(k0 + r) * lda + k0 + c] : (r == c ? 1.0 : 0.0);
+  }
+}
+__device__ __forceinline__ void store_diag(const double (*s)[NBP], double *A, int64_t n, int64_t lda, int64_t k0) {
+  for (int e = threadIdx.x; e < NB * NB; e += blockDim.x) {
+    const int r = e / NB, c = e % NB;
+    if (c <= r && k0 + r < n) A[(k0 + r) * lda + k0 + c] = s[r][c];
+  }
 }
 
 __global__ __launch_bounds__(256) void k_chol_diag(double *A, int64_t n, int64_t lda, int64_t k0, int64_t *info) {
   __shared__ double s[NB][NBP];
-  const int t = threadIdx.x;
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e % NB;
-    s[r][c] = ld_a(A, lda, n, k0 + r, k0 + c);
-  }
+  load_diag(s, A, n, lda, k0);
   __syncthreads();
-  for (int j = 0; j < NB; ++j) {
-    if (t == 0) {
-      const double d = s[j][j];
-      if (!(d > 0.0) || !isfinite(d)) {
-        if (k0 + j < n) atomicCAS((unsigned long long *)info, 0ull, (unsigned long long)(k0 + j + 1));
-        s[j][j] = 1.0;  // keep going with finite values; info reports the failure
-      } else {
-        s[j][j] = sqrt(d);
-      }
-    }
-    __syncthreads();
-    const double djj = s[j][j];
-    for (int i = j + 1 + t; i < NB; i += 256) s[i][j] /= djj;
-    __syncthreads();
-    const int m = NB - j - 1;
-    for (int e = t; e < m * m; e += 256) {
-      const int i = j + 1 + e / m, l = j + 1 + e % m;
-      if (l <= i) s[i][l] -= s[i][j] * s[l][j];
-    }
-    __syncthreads();
-  }
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e % NB;
-    if (c <= r && k0 + r < n && k0 + c < n) A[(k0 + r) * lda + k0 + c] = s[r][c];
-  }
+  chol_tile(s, n, k0, info);
+  __syncthreads();
+  store_diag(s, A, n, lda, k0);
 }
 
-// row blocks below the diagonal: X L_kk^T = A_ik  (one thread per row)
-__global__ __launch_bounds__(NB) void k_chol_panel(double *A, int64_t n, int64_t lda, int64_t k0) {
-  __shared__ double L[NB][NBP];
+// Rows below the diagonal tile: X L_kk^T = A_ik, 64 rows per workgroup.  All
+// four wavefronts load and store; the first solves, one row per lane held in
+// registers, the columns of L read from LDS as broadcasts (2,016 independent
+// FMA per lane).
+__global__ __launch_bounds__(256) void k_chol_panel(double *A, int64_t n, int64_t lda, int64_t k0) {
+  __shared__ __align__(16) double LT[NB][NB + 2];  // LT[j][l] = L[l][j] for l > j, 1 / L[j][j] for l == j
   __shared__ double X[NB][NBP];
   const int t = threadIdx.x;
   const int64_t r0 = k0 + NB * (1 + (int64_t)blockIdx.x);
-  for (int e = t; e < NB * NB; e += NB) {
-    const int r = e / NB, c = e % NB;
-    L[r][c] = ld_a(A, lda, n, k0 + r, k0 + c);
-    X[r][c] = (r0 + r < n && k0 + c < n) ? A[(r0 + r) * lda + k0 + c] : 0.0;
-  }
-  __syncthreads();
-  for (int j = 0; j < NB; ++j) {
-    double acc = X[t][j];
-    for (int l = 0; l < j; ++l) acc -= X[t][l] * L[j][l];
-    X[t][j] = acc / L[j][j];
-  }
-  __syncthreads();
-  for (int e = t; e < NB * NB; e += NB) {
-    const int r = e / NB, c = e % NB;
-    if (r0 + r < n && k0 + c < n) A[(r0 + r) * lda + k0 + c] = X[r][c];
-  }
-}
-
-// trailing update of lower tiles (i, j), k < j <= i:  A_ij -= L_ik L_jk^T
-__global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64_t lda, int64_t k0, int nt_rem) {
-  __shared__ double Li[NB][NBP];
-  __shared__ double Lj[NB][NBP];
-  // linear block index -> (i, j) with j <= i over the remaining tiles
-  const int64_t b = blockIdx.x;
-  int i = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-  while ((int64_t)(i + 1) * (i + 2) / 2 <= b) ++i;
-  while ((int64_t)i * (i + 1) / 2 > b) --i;
-  const int j = (int)(b - (int64_t)i * (i + 1) / 2);
-  if (i >= nt_rem) return;
-  const int64_t ri = k0 + NB * (1 + (int64_t)i), rj = k0 + NB * (1 + (int64_t)j);
-  const int t = threadIdx.x;
   for (int e = t; e < NB * NB; e += 256) {
     const int r = e / NB, c = e % NB;
-    Li[r][c] = (ri + r < n && k0 + c < n) ? A[(ri + r) * lda + k0 + c] : 0.0;
-    Lj[r][c] = (rj + r < n && k0 + c < n) ? A[(rj + r) * lda + k0 + c] : 0.0;
+    X[r][c] = r0 + r < n ? A[(r0 + r) * lda + k0 + c] : 0.0;
   }
-  __syncthreads();
-  const int tr = t / 16, tc = t % 16;  // 4x4 outputs per thread
-  double acc[4][4] = {};
-  for (int l = 0; l < NB; ++l) {
-    double a[4], bb[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = Li[4 * tr + u][l];
-      bb[u] = Lj[4 * tc + u][l];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * bb[v];
+  for (int e = t; e < NB * NB; e += 256) {
+    const int r = e / NB, c = e % NB;
+    const double v = A[(k0 + r) * lda + k0 + c];
+    LT[c][r] = r == c ? 1.0 / v : v;
   }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t r = ri + 4 * tr + u, cc = rj + 4 * tc + v;
-      if (r < n && cc < n && cc <= r) A[r * lda + cc] -= acc[u][v];
-    }
-}
-
-// forward substitution L y = b for one block row of 64 unknowns, one
-// workgroup per right-hand side: partial sums over the solved prefix, then
-// the 64x64 triangular solve.
-__global__ __launch_bounds__(256) void k_trsv_lower(const double *L, int64_t n, int64_t lda, double *B, int64_t nrhs,
-                                                   int64_t r0) {
-  __shared__ double part[256];
-  __shared__ double y[NB];
-  const int t = threadIdx.x;
-  const int64_t rhs = blockIdx.x;
-  const int rows = (int)std::min<int64_t>(NB, n - r0);
-  // part[t]: thread t sums over columns c = t, t + 256, ... < r0 for row (t / 4)?  Use 4 threads per row.
-  const int row = t / 4, lane4 = t % 4;
-  double acc = 0.0;
-  if (row < rows) {
-    const double *Lr = L + (r0 + row) * lda;
-    for (int64_t c = lane4; c < r0; c += 4) acc += Lr[c] * B[c * nrhs + rhs];
-  }
-  part[t] = acc;
   __syncthreads();
   if (t < NB) {
-    y[t] = (t < rows) ? B[(r0 + t) * nrhs + rhs] - (part[4 * t] + part[4 * t + 1] + part[4 * t + 2] + part[4 * t + 3])
-                      : 0.0;
-  }
-  __syncthreads();
-  if (t == 0) {
-    for (int i = 0; i < rows; ++i) {
-      double s = y[i];
-      const double *Lr = L + (r0 + i) * lda + r0;
-      for (int c = 0; c < i; ++c) s -= Lr[c] * y[c];
-      y[i] = s / Lr[i];
+    double x[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) x[j] = X[t][j];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      x[j] *= LT[j][j];
+#pragma unroll
+      for (int l = j + 1; l < NB; ++l) x[l] -= x[j] * LT[j][l];
     }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) X[t][j] = x[j];
   }
   __syncthreads();
-  if (t < rows) B[(r0 + t) * nrhs + rhs] = y[t];
+  for (int e = t; e < NB * NB; e += 256) {
+    const int r = e / NB, c = e % NB;
+    if (r0 + r < n) A[(r0 + r) * lda + k0 + c] = X[r][c];
+  }
 }
 
-// backward substitution L^T x = y for one block row (rows r0..r0+63),
-// using the already solved x below it.
-__global__ __launch_bounds__(256) void k_trsv_upper(const double *L, int64_t n, int64_t lda, double *B, int64_t nrhs,
-                                                   int64_t r0) {
-  __shared__ double part[256];
-  __shared__ double y[NB];
-  const int t = threadIdx.x;
-  const int64_t rhs = blockIdx.x;
-  const int rows = (int)std::min<int64_t>(NB, n - r0);
-  const int row = t / 4, lane4 = t % 4;
-  double acc = 0.0;
-  if (row < rows) {
-    // (L^T x)_row = sum_{c > row} L[c][row] x_c over c >= r0 + NB
-    for (int64_t c = r0 + NB + lane4; c < n; c += 4) acc += L[c * lda + r0 + row] * B[c * nrhs + rhs];
+// Update A_ij -= P_i P_j^T of the lower tiles with columns in [r0, c_end),
+// P the K finished columns from kc (K a multiple of 16, kc + K <= r0).  Tile
+// TM x TM, four wavefronts each a quarter of it as (TM / 32)^2 products of
+// v_mfma_f64_16x16x4; the operands go through LDS 16 columns at a time, the
+// next 16 loaded into registers meanwhile.  TM = 128 halves the operand
+// traffic of 64 and serves the trailing matrix; TM = 64 serves the outer
+// block's few columns and short remainders, where 128 leaves most of the 256
+// CUs without a tile.  The first workgroup's tile holds the next diagonal
+// tile, which it factors at once.  tri: the grid is the packed lower
+// triangle of tiles, else (row tile, column tile).
+template <int TM>
+__global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64_t lda, int64_t kc, int K, int64_t r0,
+                                                     int64_t c_end, int tri, int64_t *info) {
+  constexpr int KB = 16, KP = KB + 2;        // stride of 36 banks: 16 rows x 2 columns without conflict
+  constexpr int NLD = TM * KB / 256;         // loads per thread and operand
+  constexpr int MT = TM / 32;                // 16x16 products per wavefront and axis
+  __shared__ union {
+    struct {
+      double a[TM][KP], b[TM][KP];
+    } op;
+    double s[NB][NBP];
+  } sh;
+  int64_t i, j;
+  if (tri) {
+    const int64_t b = blockIdx.x;
+    i = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+    while ((i + 1) * (i + 2) / 2 <= b) ++i;
+    while (i * (i + 1) / 2 > b) --i;
+    j = b - i * (i + 1) / 2;
+  } else {
+    i = blockIdx.x;
+    j = blockIdx.y;
+    if (j > i) return;
   }
-  part[t] = acc;
-  __syncthreads();
-  if (t < NB) {
-    y[t] = (t < rows) ? B[(r0 + t) * nrhs + rhs] - (part[4 * t] + part[4 * t + 1] + part[4 * t + 2] + part[4 * t + 3])
-                      : 0.0;
-  }
-  __syncthreads();
-  if (t == 0) {
-    for (int i = rows - 1; i >= 0; --i) {
-      double s = y[i];
-      for (int c = i + 1; c < rows; ++c) s -= L[(r0 + c) * lda + r0 + i] * y[c];
-      y[i] = s / L[(r0 + i) * lda + r0 + i];
+  const int64_t ri = r0 + TM * i, rj = r0 + TM * j;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int wr = (w >> 1) * (TM / 2), wc = (w & 1) * (TM / 2);
+  const int lr = lane & 15, lk = lane >> 4;
+  v4d acc[MT][MT];
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int v = 0; v < MT; ++v) acc[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
+  double pa[NLD], pb[NLD];
+  auto load = [&](int64_t k) {
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+      const int e = u * 256 + t, r = e / KB, c = e % KB;
+      pa[u] = ri + r < n ? A[(ri + r) * lda + k + c] : 0.0;
+      pb[u] = rj + r < n ? A[(rj + r) * lda + k + c] : 0.0;
+    }
+  };
+  load(kc);
+  for (int k = 0; k < K; k += KB) {
+    __syncthreads();  // the previous chunk is consumed
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+      const int e = u * 256 + t, r = e / KB, c = e % KB;
+      sh.op.a[r][c] = pa[u];
+      sh.op.b[r][c] = pb[u];
+    }
+    __syncthreads();
+    if (k + KB < K) load(kc + k + KB);
+#pragma unroll
+    for (int kk = 0; kk < KB; kk += 4) {
+      double fa[MT], fb[MT];
+#pragma unroll
+      for (int u = 0; u < MT; ++u) {
+        fa[u] = sh.op.a[wr + 16 * u + lr][kk + lk];
+        fb[u] = sh.op.b[wc + 16 * u + lr][kk + lk];
+      }
+#pragma unroll
+      for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int v = 0; v < MT; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[v], acc[u][v], 0, 0, 0);
     }
   }
+  const bool first = i == 0 && j == 0;
+  if (first) {
+    __syncthreads();  // operands consumed: their space takes the diagonal tile
+    for (int e = t; e < NB * NB; e += 256) {
+      const int r = e / NB, c = e % NB;
+      sh.s[r][c] = r == c ? 1.0 : 0.0;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int v = 0; v < MT; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int tr = wr + 16 * u + 4 * e + lk, tc = wc + 16 * v + lr;
+        const int64_t r = ri + tr, c = rj + tc;
+        if (r < n && c <= r && c < c_end) {
+          const double x = A[r * lda + c] - acc[u][v][e];
+          if (first && tr < NB && tc < NB)
+            sh.s[tr][tc] = x;
+          else
+            A[r * lda + c] = x;
+        }
+      }
+  if (first) {
+    __syncthreads();
+    chol_tile(sh.s, n, r0, info);
+    __syncthreads();
+    store_diag(sh.s, A, n, lda, r0);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Triangular solves, in place and without scratch: one launch per block of
+// TB unknowns.  Launch k subtracts the solved block k from every remaining
+// block (one workgroup each), and the workgroup of the next block then
+// solves it, so a launch needs only what earlier launches finished.  Bound
+// by the chain of n / TB launches.  The TB x TB diagonal block waits in LDS
+// meanwhile; one wavefront solves it with two rows per lane, the solved
+// unknown passed by readlane.
+// ---------------------------------------------------------------------------
+constexpr int TB = 128;
+constexpr int TBH = TB / 2;
+
+struct TrsvTile {
+  double d00[TBH][TBH + 1], d10[TBH][TBH + 1], d11[TBH][TBH + 1];
+  double part[4][TB];
+};
+
+__device__ __forceinline__ void load_tri(TrsvTile &s, const double *L, int64_t n, int64_t lda, int64_t r0) {
+  for (int e = threadIdx.x; e < TBH * TBH; e += 256) {
+    const int r = e / TBH, c = e % TBH;
+    const int64_t a = r0 + r, b = r0 + TBH + r;
+    s.d00[r][c] = (a < n && c <= r) ? L[a * lda + r0 + c] : (r == c ? 1.0 : 0.0);
+    s.d10[r][c] = b < n ? L[b * lda + r0 + c] : 0.0;
+    s.d11[r][c] = (b < n && c <= r) ? L[b * lda + r0 + TBH + c] : (r == c ? 1.0 : 0.0);
+  }
+}
+
+// forward: block kb is solved (kb < 0: none yet); workgroup x updates block
+// kb + 1 + x, and the first one solves its block
+__global__ __launch_bounds__(256) void k_trsv_lower(const double *__restrict__ L, int64_t n, int64_t lda, double *B,
+                                                    int64_t nrhs, int64_t kb) {
+  __shared__ TrsvTile s;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t rhs = blockIdx.y;
+  const int64_t r0 = TB * (kb + 1 + (int64_t)blockIdx.x);
+  const bool solve = blockIdx.x == 0;
+  if (solve) load_tri(s, L, n, lda, r0);
+  if (kb >= 0) {
+    const int64_t c0 = TB * kb;  // a full block: kb is not the last
+    const double y0 = B[(c0 + lane) * nrhs + rhs], y1 = B[(c0 + TBH + lane) * nrhs + rhs];
+    // wavefront w: 32 rows, lane = column
+    double v[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+      const int64_t r = r0 + 32 * w + u;
+      const double *p = L + (r < n ? r : n - 1) * lda + c0;
+      v[u] = p[lane] * y0 + p[TBH + lane] * y1;
+    }
+    // sums over the lanes: each halving leaves half the rows to each half
+#pragma unroll
+    for (int h = 32; h > 1; h >>= 1)
+#pragma unroll
+      for (int u = 0; u < h / 2; ++u) {
+        const bool up = (lane & (h / 2)) != 0;
+        const double keep = up ? v[u + h / 2] : v[u], give = up ? v[u] : v[u + h / 2];
+        v[u] = keep + __shfl_xor(give, h / 2, 64);
+      }
+    const double sum = v[0] + __shfl_xor(v[0], 32, 64);  // row = the lane's low five bits
+    if (lane < 32) s.part[0][32 * w + lane] = sum;
+  }
   __syncthreads();
-  if (t < rows) B[(r0 + t) * nrhs + rhs] = y[t];
+  if (!solve) {
+    const int64_t r = r0 + t;
+    if (t < TB && r < n) B[r * nrhs + rhs] -= s.part[0][t];
+    return;
+  }
+  if (w != 0) return;
+  const int64_t ra = r0 + lane, rb = r0 + TBH + lane;
+  double ta = ra < n ? B[ra * nrhs + rhs] : 0.0, tb = rb < n ? B[rb * nrhs + rhs] : 0.0;
+  if (kb >= 0) {
+    ta -= s.part[0][lane];
+    tb -= s.part[0][TBH + lane];
+  }
+  const double ia = 1.0 / s.d00[lane][lane], ib = 1.0 / s.d11[lane][lane];
+#pragma unroll 8
+  for (int j = 0; j < TBH; ++j) {
+    const double y = lane_value(ta * ia, j);
+    ta = lane == j ? ta : ta - s.d00[lane][j] * y;  // zero above the diagonal
+    tb -= s.d10[lane][j] * y;
+  }
+#pragma unroll 8
+  for (int j = 0; j < TBH; ++j) {
+    const double y = lane_value(tb * ib, j);
+    tb = lane == j ? tb : tb - s.d11[lane][j] * y;
+  }
+  if (ra < n) B[ra * nrhs + rhs] = ta * ia;
+  if (rb < n) B[rb * nrhs + rhs] = tb * ib;
+}
+
+// backward, L^T x = y: block kb is solved (kb = number of blocks: none yet);
+// workgroup x updates block kb - 1 - x, and the first one solves its block
+__global__ __launch_bounds__(256) void k_trsv_upper(const double *__restrict__ L, int64_t n, int64_t lda, double *B,
+                                                    int64_t nrhs, int64_t kb) {
+  __shared__ TrsvTile s;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t rhs = blockIdx.y;
+  const int64_t r0 = TB * (kb - 1 - (int64_t)blockIdx.x);
+  const int64_t k0 = TB * kb;
+  const bool solve = blockIdx.x == 0;
+  const bool any = k0 < n;
+  if (solve) load_tri(s, L, n, lda, r0);
+  if (any) {
+    // wavefront w: 32 rows of the solved block, lane = two columns of ours
+    double a0 = 0.0, a1 = 0.0;
+#pragma unroll 16
+    for (int u = 0; u < 32; ++u) {
+      const int64_t r = k0 + 32 * w + u;
+      const bool in = r < n;
+      const double x = in ? B[r * nrhs + rhs] : 0.0;
+      const double *p = L + (in ? r : n - 1) * lda + r0;
+      a0 += p[lane] * x;
+      a1 += p[TBH + lane] * x;
+    }
+    s.part[w][lane] = a0;
+    s.part[w][TBH + lane] = a1;
+  }
+  __syncthreads();
+  auto part = [&](int k) { return any ? (s.part[0][k] + s.part[1][k]) + (s.part[2][k] + s.part[3][k]) : 0.0; };
+  if (!solve) {
+    if (t < TB) B[(r0 + t) * nrhs + rhs] -= part(t);  // not the last block: full
+    return;
+  }
+  if (w != 0) return;
+  const int64_t ra = r0 + lane, rb = r0 + TBH + lane;
+  double ta = ra < n ? B[ra * nrhs + rhs] - part(lane) : 0.0;
+  double tb = rb < n ? B[rb * nrhs + rhs] - part(TBH + lane) : 0.0;
+  const double ia = 1.0 / s.d00[lane][lane], ib = 1.0 / s.d11[lane][lane];
+#pragma unroll 8
+  for (int j = TBH - 1; j >= 0; --j) {
+    const double x = lane_value(tb * ib, j);
+    tb = lane == j ? tb : tb - s.d11[j][lane] * x;  // zero above the diagonal
+    ta -= s.d10[j][lane] * x;
+  }
+#pragma unroll 8
+  for (int j = TBH - 1; j >= 0; --j) {
+    const double x = lane_value(ta * ia, j);
+    ta = lane == j ? ta : ta - s.d00[j][lane] * x;
+  }
+  if (ra < n) B[ra * nrhs + rhs] = ta * ia;
+  if (rb < n) B[rb * nrhs + rhs] = tb * ib;
 }
 
 }  // namespace eipc
@@ -202,19 +404,29 @@ eipc_status eipc_cholesky(eipc_ctx *c, double *A, int64_t n, int64_t lda, int64_
   hipStream_t s = (hipStream_t)stream;
   int64_t *d_info = c->counters + 12;
   EIPC_TRY(launch_zero(c, d_info, 8, s));
-  const int64_t nt = (n + NB - 1) / NB;
-  for (int64_t k = 0; k < nt; ++k) {
-    const int64_t k0 = k * NB;
-    k_chol_diag<<<1, 256, 0, s>>>(A, n, lda, k0, d_info);
+  if (n > 0) {
+    k_chol_diag<<<1, 256, 0, s>>>(A, n, lda, 0, d_info);
     EIPC_HIP(c, hipGetLastError());
-    const int64_t rem = nt - k - 1;
-    if (rem > 0) {
-      k_chol_panel<<<(unsigned)rem, NB, 0, s>>>(A, n, lda, k0);
-      EIPC_HIP(c, hipGetLastError());
-      const int64_t nblk = rem * (rem + 1) / 2;
-      k_chol_update<<<(unsigned)nblk, 256, 0, s>>>(A, n, lda, k0, (int)rem);
-      EIPC_HIP(c, hipGetLastError());
+  }
+  for (int64_t k0 = 0; k0 + NB < n; k0 += NB) {
+    const int64_t r0 = k0 + NB, o0 = k0 / OB * OB, oend = std::min<int64_t>(o0 + OB, n);
+    const int64_t rem = (n - r0 + NB - 1) / NB;
+    k_chol_panel<<<(unsigned)rem, 256, 0, s>>>(A, n, lda, k0);
+    EIPC_HIP(c, hipGetLastError());
+    if (r0 < oend) {
+      // inside the outer block: its remaining columns, with these 64
+      const unsigned nc = (unsigned)((oend - r0 + NB - 1) / NB);
+      k_chol_update<64><<<dim3((unsigned)rem, nc), 256, 0, s>>>(A, n, lda, k0, NB, r0, oend, 0, d_info);
+    } else {
+      // the outer block is finished: the whole trailing matrix; 64-tiles
+      // while 128-tiles would be fewer than two per CU
+      const int64_t nt = (n - r0 + 127) / 128, nblk = nt * (nt + 1) / 2;
+      if (nblk >= 2 * (int64_t)c->num_cu)
+        k_chol_update<128><<<(unsigned)nblk, 256, 0, s>>>(A, n, lda, o0, OB, r0, n, 1, d_info);
+      else
+        k_chol_update<64><<<(unsigned)(rem * (rem + 1) / 2), 256, 0, s>>>(A, n, lda, o0, OB, r0, n, 1, d_info);
     }
+    EIPC_HIP(c, hipGetLastError());
   }
   EIPC_HIP(c, hipMemcpyAsync(info, d_info, 8, hipMemcpyDeviceToHost, s));
   EIPC_HIP(c, hipStreamSynchronize(s));
@@ -227,14 +439,18 @@ eipc_status eipc_cholesky_solve(eipc_ctx *c, const double *L, int64_t n, int64_t
     return c ? set_err(c, EIPC_ERR_ARG, "bad solve arguments") : EIPC_ERR_ARG;
   EIPC_HIP(c, hipSetDevice(c->device));
   hipStream_t s = (hipStream_t)stream;
-  const int64_t nt = (n + NB - 1) / NB;
-  for (int64_t k = 0; k < nt; ++k) {
-    k_trsv_lower<<<(unsigned)nrhs, 256, 0, s>>>(L, n, lda, B, nrhs, k * NB);
-    EIPC_HIP(c, hipGetLastError());
-  }
-  for (int64_t k = nt - 1; k >= 0; --k) {
-    k_trsv_upper<<<(unsigned)nrhs, 256, 0, s>>>(L, n, lda, B, nrhs, k * NB);
-    EIPC_HIP(c, hipGetLastError());
+  const int64_t nt = (n + TB - 1) / TB;
+  // right-hand sides go to the grid's second axis, in runs it can hold
+  for (int64_t j0 = 0; j0 < nrhs; j0 += 65535) {
+    const unsigned nj = (unsigned)std::min<int64_t>(nrhs - j0, 65535);
+    for (int64_t k = -1; k < nt - 1; ++k) {
+      k_trsv_lower<<<dim3(k < 0 ? 1u : (unsigned)(nt - 1 - k), nj), 256, 0, s>>>(L, n, lda, B + j0, nrhs, k);
+      EIPC_HIP(c, hipGetLastError());
+    }
+    for (int64_t k = nt; k > 0; --k) {
+      k_trsv_upper<<<dim3(k == nt ? 1u : (unsigned)k, nj), 256, 0, s>>>(L, n, lda, B + j0, nrhs, k);
+      EIPC_HIP(c, hipGetLastError());
+    }
   }
   return EIPC_OK;
 }

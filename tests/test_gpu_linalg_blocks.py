@@ -1,0 +1,58 @@
+"""Dense Cholesky and triangular solves at the edges of their blocks: the
+64-column inner and 256-column outer blocks, the 128-row tiles of the large
+trailing updates (from 32 such tiles on), the 128-row blocks of the solves."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_16385_amd as E
+from paper_2409_16385_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return E.Context(0)
+
+
+@pytest.mark.parametrize("n,pad,nrhs", [(1, 0, 1), (2, 3, 2), (63, 0, 1), (64, 1, 1), (65, 0, 3), (127, 0, 1),
+                                        (128, 0, 1), (129, 5, 2), (192, 0, 1), (255, 0, 1), (256, 0, 1), (257, 1, 5),
+                                        (320, 0, 1), (513, 0, 1), (1000, 7, 1), (4352, 0, 1), (4481, 0, 2)])
+def test_factor_and_solve(ctx, n, pad, nrhs):
+    """Backward errors of the factor and of the solve: |A - L L^T| and
+    |A X - B| of order n eps |A| (|X|), with the constant 8 for the two
+    roundings of each of the blocked sums and the reciprocal pivots.  The
+    strict upper triangle and the padding stay as they were."""
+    rng = np.random.default_rng(n)
+    G = torch.as_tensor(rng.normal(size=(n, n)), device="cuda")
+    A = G @ G.T / n + torch.eye(n, dtype=torch.float64, device="cuda")
+    A = 0.5 * (A + A.T)
+    buf = torch.full((n, n + pad), 7.0, dtype=torch.float64, device="cuda")
+    buf[:, :n] = A + torch.triu(torch.ones_like(A), 1)  # the upper triangle is not read
+    keep = buf.clone()
+    info = C.c_int64(-1)
+    L = B._load()
+    ctx.check(L.eipc_cholesky(ctx.handle, buf.data_ptr(), n, n + pad, C.byref(info), ctx.stream()))
+    assert info.value == 0
+    up = torch.triu(torch.ones((n, n + pad), dtype=torch.bool, device="cuda"), 1)
+    assert torch.equal(buf[up], keep[up])
+    F = torch.tril(buf[:, :n])
+    tol = 8 * max(n, 8) * 2.2e-16
+    assert float(torch.linalg.matrix_norm(F @ F.T - A)) <= tol * float(torch.linalg.matrix_norm(A))
+    rhs = torch.as_tensor(rng.normal(size=(n, nrhs)), device="cuda")
+    x = rhs.clone()
+    ctx.check(L.eipc_cholesky_solve(ctx.handle, buf.data_ptr(), n, n + pad, x.data_ptr(), nrhs, ctx.stream()))
+    r = float(torch.linalg.matrix_norm(A @ x - rhs))
+    assert r <= 3 * tol * float(torch.linalg.matrix_norm(A)) * float(torch.linalg.matrix_norm(x))
+
+
+@pytest.mark.parametrize("n,bad", [(64, 63), (300, 0), (300, 64), (300, 200), (700, 256), (700, 699)])
+def test_first_bad_minor(ctx, n, bad):
+    A = torch.eye(n, dtype=torch.float64, device="cuda")
+    A[bad, bad] = -1.0
+    if bad + 70 < n:
+        A[bad + 70, bad + 70] = float("nan")
+    assert E.cholesky(ctx, A) == bad + 1
