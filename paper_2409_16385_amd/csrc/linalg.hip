@@ -37,9 +37,8 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // four wavefronts.  Wavefront w holds columns 16 w .. 16 w + 15, lane = row:
 // in step p wavefront p factors its 16 columns for all rows, passing column
 // entries between lanes by readlane, and the later wavefronts apply them.
-// Bound by the serial chain of 64 pivots (about 10 us a tile; the earlier
-// version, one thread taking the pivots and three barriers per column, took
-// 82 us).  k0 + 64 may pass n: the caller pads with the unit matrix.
+// Bound by the serial chain of 64 pivots.  k0 + 64 may pass n: the caller
+// pads with the unit matrix.
 __device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k0, int64_t *info) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   double a[16];
@@ -47,19 +46,27 @@ __device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k
   for (int j = 0; j < 16; ++j) a[j] = s[lane][16 * w + j];
   for (int p = 0; p < 4; ++p) {
     if (w == p) {
+      int bad = NB;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         const int c = 16 * p + j;
         double d = lane_value(a[j], c);
-        if (!(d > 0.0) || !isfinite(d)) {
-          if (lane == 0 && k0 + c < n) atomicCAS((unsigned long long *)info, 0ull, (unsigned long long)(k0 + c + 1));
-          d = 1.0;  // keep going with finite values; info reports the failure
-        }
-        const double rs = sqrt(d), ri = 1.0 / rs;
-        a[j] = lane == c ? rs : a[j] * ri;
+        // no branch on the pivots' chain: a bad one is replaced by 1 (the
+        // factor stays finite) and reported after the panel
+        const bool ok = d > 0.0 && d < INFINITY;
+        bad = ok || bad < NB ? bad : c;
+        d = ok ? d : 1.0;
+        // 1 / sqrt(d): the hardware estimate (2^-24 or better) and one
+        // third-order step
+        double ri = __builtin_amdgcn_rsq(d);
+        const double e = fma(-(d * ri), ri, 1.0);
+        ri = fma(ri * e, fma(e, 0.375, 0.5), ri);
+        a[j] = (lane == c ? d : a[j]) * ri;
 #pragma unroll
         for (int l = j + 1; l < 16; ++l) a[l] -= a[j] * lane_value(a[j], 16 * p + l);
       }
+      if (bad < NB && lane == 0 && k0 + bad < n)
+        atomicCAS((unsigned long long *)info, 0ull, (unsigned long long)(k0 + bad + 1));
 #pragma unroll
       for (int j = 0; j < 16; ++j) s[lane][16 * p + j] = a[j];
     }
@@ -78,9 +85,19 @@ __device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k
 
 // the diagonal tile at k0, loaded into s (unit matrix past n)
 __device__ __forceinline__ void load_diag(double (*s)[NBP], const double *A, int64_t n, int64_t lda, int64_t k0) {
-  for (int e = threadIdx.x; e < NB * NB; e += blockDim.x) {
-    const int r = e / NB, c = e % NB;
-    s[r][c] = (k0 + r < n && c <= r) ? A[(k0 + r) * lda + k0 + c] : (r == c ? 1.0 : 0.0);
+  // all loads first (a loop of load and store waits for each in turn: 1 us a
+  // round), addresses clamped into the lower triangle's rows
+  double v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = u * 256 + (int)threadIdx.x, r = e / NB, c = e % NB;
+    const int64_t rr = k0 + r < n ? k0 + r : n - 1;
+    v[u] = A[rr * lda + k0 + (k0 + c <= rr ? c : 0)];
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = u * 256 + (int)threadIdx.x, r = e / NB, c = e % NB;
+    s[r][c] = (k0 + r < n && c <= r) ? v[u] : (r == c ? 1.0 : 0.0);
   }
 }
 __device__ __forceinline__ void store_diag(const double (*s)[NBP], double *A, int64_t n, int64_t lda, int64_t k0) {
@@ -99,42 +116,66 @@ __global__ __launch_bounds__(256) void k_chol_diag(double *A, int64_t n, int64_t
   store_diag(s, A, n, lda, k0);
 }
 
-// Rows below the diagonal tile: X L_kk^T = A_ik, 64 rows per workgroup.  All
-// four wavefronts load and store; the first solves, one row per lane held in
-// registers, the columns of L read from LDS as broadcasts (2,016 independent
-// FMA per lane).
+// Rows below the diagonal tile: X L_kk^T = A_ik, 64 rows per workgroup, 16
+// per wavefront, as the transposed system L_kk Y = A_ik^T in blocks of 16:
+// Y_p = inv(L_pp) (C_p - sum_{q < p} L_pq Y_q) on the matrix cores.  The
+// product's result layout (row 4 e + lane / 16, column lane % 16) is the
+// layout its right operand takes, so Y stays in registers.  The four 16x16
+// inverses are formed in LDS, one column per lane of the first wavefront.
+// (One row per lane and 2,016 FMA with L broadcast from LDS took 17 us more.)
 __global__ __launch_bounds__(256) void k_chol_panel(double *A, int64_t n, int64_t lda, int64_t k0) {
-  __shared__ __align__(16) double LT[NB][NB + 2];  // LT[j][l] = L[l][j] for l > j, 1 / L[j][j] for l == j
-  __shared__ double X[NB][NBP];
-  const int t = threadIdx.x;
-  const int64_t r0 = k0 + NB * (1 + (int64_t)blockIdx.x);
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e % NB;
-    X[r][c] = r0 + r < n ? A[(r0 + r) * lda + k0 + c] : 0.0;
-  }
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e % NB;
-    const double v = A[(k0 + r) * lda + k0 + c];
-    LT[c][r] = r == c ? 1.0 / v : v;
-  }
+  __shared__ double Ls[NB][NBP + 1];
+  __shared__ double Iv[NB][17];  // row 16 p + i, column j: inv(L_pp)[i][j]
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t r = k0 + NB * (1 + (int64_t)blockIdx.x) + 16 * w + lr;
+  double *row = A + (r < n ? r : n - 1) * lda + k0;  // rows past n: clamped, not stored
+  double vl[16];
+  v4d c[4];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) vl[u] = A[(k0 + u * 4 + w) * lda + k0 + lane];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c[p][e] = row[16 * p + 4 * e + lk];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) Ls[u * 4 + w][lane] = vl[u];
   __syncthreads();
-  if (t < NB) {
-    double x[NB];
+  if (w == 0) {
+    const double rd = 1.0 / Ls[lane][lane];
+    double z[16];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) x[j] = X[t][j];
+    for (int i = 0; i < 16; ++i) z[i] = i == lr ? 1.0 : 0.0;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      x[j] *= LT[j][j];
+    for (int i = 0; i < 16; ++i) {
+      z[i] *= __shfl(rd, 16 * lk + i, 64);
 #pragma unroll
-      for (int l = j + 1; l < NB; ++l) x[l] -= x[j] * LT[j][l];
+      for (int l = i + 1; l < 16; ++l) z[l] -= Ls[16 * lk + l][16 * lk + i] * z[i];
     }
 #pragma unroll
-    for (int j = 0; j < NB; ++j) X[t][j] = x[j];
+    for (int i = 0; i < 16; ++i) Iv[16 * lk + i][lr] = z[i];
   }
   __syncthreads();
-  for (int e = t; e < NB * NB; e += 256) {
-    const int r = e / NB, c = e % NB;
-    if (r0 + r < n) A[(r0 + r) * lda + k0 + c] = X[r][c];
+  v4d y[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    v4d sum = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < p; ++q)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        sum = __builtin_amdgcn_mfma_f64_16x16x4f64(Ls[16 * p + lr][16 * q + 4 * kk + lk], y[q][kk], sum, 0, 0, 0);
+    const v4d d = c[p] - sum;
+    y[p] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      y[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(Iv[16 * p + lr][4 * kk + lk], d[kk], y[p], 0, 0, 0);
+  }
+  if (r < n) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) row[16 * p + 4 * e + lk] = y[p][e];
   }
 }
 
@@ -149,7 +190,7 @@ __global__ __launch_bounds__(256) void k_chol_panel(double *A, int64_t n, int64_
 // tile, which it factors at once.  tri: the grid is the packed lower
 // triangle of tiles, else (row tile, column tile).
 template <int TM>
-__global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64_t lda, int64_t kc, int K, int64_t r0,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chol_update(double *A, int64_t n, int64_t lda, int64_t kc, int K, int64_t r0,
                                                      int64_t c_end, int tri, int64_t *info) {
   constexpr int KB = 16, KP = KB + 2;        // stride of 36 banks: 16 rows x 2 columns without conflict
   constexpr int NLD = TM * KB / 256;         // loads per thread and operand
@@ -186,8 +227,9 @@ __global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
       const int e = u * 256 + t, r = e / KB, c = e % KB;
-      pa[u] = ri + r < n ? A[(ri + r) * lda + k + c] : 0.0;
-      pb[u] = rj + r < n ? A[(rj + r) * lda + k + c] : 0.0;
+      // rows past n clamped: their products are not stored
+      pa[u] = A[(ri + r < n ? ri + r : n - 1) * lda + k + c];
+      pb[u] = A[(rj + r < n ? rj + r : n - 1) * lda + k + c];
     }
   };
   load(kc);
@@ -200,7 +242,7 @@ __global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64
       sh.op.b[r][c] = pb[u];
     }
     __syncthreads();
-    if (k + KB < K) load(kc + k + KB);
+    load(kc + (k + KB < K ? k + KB : k));  // unconditional: a branch here moves the sums between register files
 #pragma unroll
     for (int kk = 0; kk < KB; kk += 4) {
       double fa[MT], fb[MT];
@@ -225,8 +267,20 @@ __global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64
     }
     __syncthreads();
   }
+  // a row of products at a time: its loads together (clamped into the row),
+  // then its stores
 #pragma unroll
-  for (int u = 0; u < MT; ++u)
+  for (int u = 0; u < MT; ++u) {
+    double x[MT][4];
+#pragma unroll
+    for (int v = 0; v < MT; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int64_t r = ri + wr + 16 * u + 4 * e + lk;
+        r = r < n ? r : n - 1;
+        const int64_t c = rj + wc + 16 * v + lr;
+        x[v][e] = A[r * lda + (c <= r ? c : r)];
+      }
 #pragma unroll
     for (int v = 0; v < MT; ++v)
 #pragma unroll
@@ -234,13 +288,14 @@ __global__ __launch_bounds__(256) void k_chol_update(double *A, int64_t n, int64
         const int tr = wr + 16 * u + 4 * e + lk, tc = wc + 16 * v + lr;
         const int64_t r = ri + tr, c = rj + tc;
         if (r < n && c <= r && c < c_end) {
-          const double x = A[r * lda + c] - acc[u][v][e];
+          const double y = x[v][e] - acc[u][v][e];
           if (first && tr < NB && tc < NB)
-            sh.s[tr][tc] = x;
+            sh.s[tr][tc] = y;
           else
-            A[r * lda + c] = x;
+            A[r * lda + c] = y;
         }
       }
+  }
   if (first) {
     __syncthreads();
     chol_tile(sh.s, n, r0, info);
@@ -267,12 +322,24 @@ struct TrsvTile {
 };
 
 __device__ __forceinline__ void load_tri(TrsvTile &s, const double *L, int64_t n, int64_t lda, int64_t r0) {
-  for (int e = threadIdx.x; e < TBH * TBH; e += 256) {
-    const int r = e / TBH, c = e % TBH;
-    const int64_t a = r0 + r, b = r0 + TBH + r;
-    s.d00[r][c] = (a < n && c <= r) ? L[a * lda + r0 + c] : (r == c ? 1.0 : 0.0);
-    s.d10[r][c] = b < n ? L[b * lda + r0 + c] : 0.0;
-    s.d11[r][c] = (b < n && c <= r) ? L[b * lda + r0 + TBH + c] : (r == c ? 1.0 : 0.0);
+  // all loads in flight together; rows past n and columns past the diagonal
+  // are clamped and replaced
+  double v[3][16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
+    const int64_t a = r0 + r < n ? r0 + r : n - 1, b = r0 + TBH + r < n ? r0 + TBH + r : n - 1;
+    v[0][u] = L[a * lda + (r0 + c <= a ? r0 + c : a)];
+    v[1][u] = L[b * lda + (r0 + c <= b ? r0 + c : b)];
+    v[2][u] = L[b * lda + (r0 + TBH + c <= b ? r0 + TBH + c : b)];
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
+    const bool a = r0 + r < n, b = r0 + TBH + r < n;
+    s.d00[r][c] = a && c <= r ? v[0][u] : (r == c ? 1.0 : 0.0);
+    s.d10[r][c] = b ? v[1][u] : 0.0;
+    s.d11[r][c] = b && c <= r ? v[2][u] : (r == c ? 1.0 : 0.0);
   }
 }
 
@@ -353,7 +420,7 @@ __global__ __launch_bounds__(256) void k_trsv_upper(const double *__restrict__ L
   if (any) {
     // wavefront w: 32 rows of the solved block, lane = two columns of ours
     double a0 = 0.0, a1 = 0.0;
-#pragma unroll 16
+#pragma unroll
     for (int u = 0; u < 32; ++u) {
       const int64_t r = k0 + 32 * w + u;
       const bool in = r < n;
