@@ -95,7 +95,7 @@ def concat(scenes) -> HostBatch:
 DEFAULT_FLAGS = B.ENERGY | B.GRAD | B.HESS | B.PROJECT
 # workgroups per CU of the pair-terms, expansion, narrow and CCD kernels: the
 # library context's defaults
-DEFAULT_WG_PER_CU = (1, 2, 4, 4)
+DEFAULT_WG_PER_CU = (2, 2, 4, 4)
 
 
 class Batch:

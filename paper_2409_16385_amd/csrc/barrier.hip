@@ -829,8 +829,10 @@ static eipc_status sort_active(eipc_ctx *c, const eipc_scene *sc, int kind, cons
 constexpr int TERMS_T = 256;      // four wavefronts, one per SIMD (the 9x9 projection's registers)
 constexpr int TERMS_TILE = 2048;  // pairs per class-sorted tile
 
-template <int KIND, bool REDUCED>
-__global__ __launch_bounds__(TERMS_T) void k_pair_terms(
+// GEN: pairs may be mollified (general 9x9 path) or take the reduced-block
+// projection; without it the registers fit two wavefronts per SIMD.
+template <int KIND, bool REDUCED, bool GEN>
+__global__ __launch_bounds__(TERMS_T) __attribute__((amdgpu_waves_per_eu(GEN ? 1 : 2))) void k_pair_terms(
     const int32_t *__restrict__ pairs, const int32_t *__restrict__ act, const int32_t *__restrict__ typ,
     const int4 *__restrict__ vid4, const int64_t *__restrict__ d_count, int64_t cap,
     const int32_t *__restrict__ faces, const int32_t *__restrict__ edges, const double *__restrict__ xs,
@@ -846,7 +848,7 @@ __global__ __launch_bounds__(TERMS_T) void k_pair_terms(
   const bool reduced = REDUCED && want_h;
   const bool project = (flags & EIPC_PROJECT) && !reduced;
   const bool sq = flags & EIPC_SQDIST;
-  const bool moll = (KIND == 1) && (flags & EIPC_MOLLIFY) && x_rest;
+  const bool moll = GEN && (KIND == 1) && (flags & EIPC_MOLLIFY) && x_rest;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   constexpr int NW = TERMS_T / 64;
@@ -942,9 +944,14 @@ __global__ __launch_bounds__(TERMS_T) void k_pair_terms(
             r[q] = V3{x_rest[3 * (int64_t)vid[q]], x_rest[3 * (int64_t)vid[q] + 1], x_rest[3 * (int64_t)vid[q] + 2]};
           eps = mollifier_eps(r);
         }
-        if (expand) {
+        if (expand && !GEN) {
+          // straight into the record (held in registers as a whole it takes
+          // 108 of them beside the projection's)
+          double *r = (double *)__builtin_assume_aligned(rec + i * TERM_REC, 16);
+          e_pair = pair_qterms<KIND, GEN>(cls, ty, x, eps, dhat, kappa, want_g, want_h, project, sq, r, r + 9);
+        } else if (expand) {
           double tv[54];
-          e_pair = pair_qterms<KIND>(cls, ty, x, eps, dhat, kappa, want_g, want_h, project, sq, tv, tv + 9);
+          e_pair = pair_qterms<KIND, GEN>(cls, ty, x, eps, dhat, kappa, want_g, want_h, project, sq, tv, tv + 9);
           if (reduced) {
             // dot products of the four vertices' rows of W
             int cc[4][4];
@@ -1022,21 +1029,24 @@ eipc_status launch_barrier(eipc_ctx *c, const eipc_scene *sc, int kind, const do
   const int nsc = n_scene_of(sc);
   {
     ProfScope ps(c, kind == 0 ? K_BARRIER_PT : K_BARRIER_EE, s);
-#define EIPC_TERMS_LAUNCH(K, R)                                                                                    \
-  k_pair_terms<K, R><<<blocks, TERMS_T, 0, s>>>(pairs, act, typ, vid4, d_count, cap, sc->faces, sc->edges, xs,        \
+#define EIPC_TERMS_LAUNCH(K, R, G)                                                                                 \
+  k_pair_terms<K, R, G><<<blocks, TERMS_T, 0, s>>>(pairs, act, typ, vid4, d_count, cap, sc->faces, sc->edges, xs,        \
                                                 sc->x_rest, sc->n_vert, dhat, kappa, flags, want_g, want_h, energy, \
                                                 rec, vsc, nsc, c->status, sc->W_rowptr, sc->W_col, sc->W_val)
     const bool reduced = want_h && (flags & EIPC_PROJECT_REDUCED);
+    const bool moll = (flags & EIPC_MOLLIFY) && sc->x_rest;
     if (kind == 0) {
       if (reduced)
-        EIPC_TERMS_LAUNCH(0, true);
+        EIPC_TERMS_LAUNCH(0, true, true);
       else
-        EIPC_TERMS_LAUNCH(0, false);
+        EIPC_TERMS_LAUNCH(0, false, false);
     } else {
       if (reduced)
-        EIPC_TERMS_LAUNCH(1, true);
+        EIPC_TERMS_LAUNCH(1, true, true);
+      else if (moll)
+        EIPC_TERMS_LAUNCH(1, false, true);
       else
-        EIPC_TERMS_LAUNCH(1, false);
+        EIPC_TERMS_LAUNCH(1, false, false);
     }
 #undef EIPC_TERMS_LAUNCH
     EIPC_HIP(c, hipGetLastError());
@@ -1234,8 +1244,8 @@ eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out
 // pair's vertices, scattered through W^T (and unreduced into out_off).
 // H_x = Q X Q^T:  zeta = Q^T z, eta = X zeta, y = Q eta.
 // ---------------------------------------------------------------------------
-template <int KIND>
-__global__ __launch_bounds__(BR_THREADS) void k_hvp(
+template <int KIND, bool GEN>
+__global__ __launch_bounds__(BR_THREADS) __attribute__((amdgpu_waves_per_eu(GEN ? 1 : 2))) void k_hvp(
     const int32_t *__restrict__ pairs, const int32_t *__restrict__ act, const int32_t *__restrict__ typ,
     const int64_t *__restrict__ d_count, const int32_t *__restrict__ faces, const int32_t *__restrict__ edges,
     const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, const double *__restrict__ val,
@@ -1247,7 +1257,7 @@ __global__ __launch_bounds__(BR_THREADS) void k_hvp(
   LdsTables T{s_gkey, s_gval};
   HessOut none{0, nullptr, nullptr, nullptr, 0};
   Acc A{T, none, n_node, out, status};
-  const bool moll = (KIND == 1) && (flags & EIPC_MOLLIFY) && x_rest;
+  const bool moll = GEN && (KIND == 1) && (flags & EIPC_MOLLIFY) && x_rest;
   for (int t = threadIdx.x; t < LGT; t += BR_THREADS) s_gkey[t] = 0xffffffffu;
   for (int t = threadIdx.x; t < LGT * 3; t += BR_THREADS) s_gval[t] = 0.0;
   __syncthreads();
@@ -1280,7 +1290,7 @@ __global__ __launch_bounds__(BR_THREADS) void k_hvp(
       }
       // the Hessian of the barrier stage's per-class path
       double gam[9], M[45];
-      pair_qterms<KIND>(pair_class<KIND>(ty, x, eps), ty, x, eps, dhat, kappa, false, true,
+      pair_qterms<KIND, GEN>(pair_class<KIND>(ty, x, eps), ty, x, eps, dhat, kappa, false, true,
                         (flags & EIPC_PROJECT) != 0, (flags & EIPC_SQDIST) != 0, gam, M);
       // zeta = Q^T z, eta = X zeta
       double zeta[9];
@@ -1373,11 +1383,15 @@ eipc_status launch_hvp(eipc_ctx *c, const eipc_scene *sc, int kind, const double
   int blocks = (int)std::min<int64_t>(grid_for(max_count, BR_THREADS), 4 * (int64_t)c->num_cu);
   ProfScope ps(c, kind == 0 ? K_HVP_PT : K_HVP_EE, s);
   if (kind == 0)
-    k_hvp<0><<<blocks, BR_THREADS, 0, s>>>(pairs, act, typ, d_count, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
+    k_hvp<0, false><<<blocks, BR_THREADS, 0, s>>>(pairs, act, typ, d_count, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
+                                            sc->W_val, xs, xvs, sc->x_rest, sc->n_vert, sc->n_node, dhat, kappa,
+                                            flags, out, out_off, c->status);
+  else if ((flags & EIPC_MOLLIFY) && sc->x_rest)
+    k_hvp<1, true><<<blocks, BR_THREADS, 0, s>>>(pairs, act, typ, d_count, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
                                             sc->W_val, xs, xvs, sc->x_rest, sc->n_vert, sc->n_node, dhat, kappa,
                                             flags, out, out_off, c->status);
   else
-    k_hvp<1><<<blocks, BR_THREADS, 0, s>>>(pairs, act, typ, d_count, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
+    k_hvp<1, false><<<blocks, BR_THREADS, 0, s>>>(pairs, act, typ, d_count, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
                                             sc->W_val, xs, xvs, sc->x_rest, sc->n_vert, sc->n_node, dhat, kappa,
                                             flags, out, out_off, c->status);
   EIPC_HIP(c, hipGetLastError());
@@ -1417,7 +1431,7 @@ __global__ __launch_bounds__(64) void k_pair_eval(int64_t n, const int32_t *__re
   double ev = 0.0;
   if (active) {
     const int cls = pair_class<KIND>(ty, x, eps);
-    ev = pair_qterms<KIND>(cls, ty, x, eps, dhat, kappa, true, true, (flags & EIPC_PROJECT) != 0,
+    ev = pair_qterms<KIND, true>(cls, ty, x, eps, dhat, kappa, true, true, (flags & EIPC_PROJECT) != 0,
                            (flags & EIPC_SQDIST) != 0, gam, M);
   }
   if (e) e[i] = ev;

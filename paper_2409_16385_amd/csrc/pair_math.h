@@ -777,9 +777,9 @@ __device__ __forceinline__ double mollifier_eps(const V3 *r) {
 //   X = (F^T x I3) P (F x I3),  P = (L^T x I3) H_l (L x I3),
 //   proj(X) = (F^T x I3) proj(P) (F x I3).
 // A point-point pair's H_l = a y y^T + b I is projected in closed form
-// (eigenvalues a s + b along y, b across), a point-line pair's 6x6 P by
-// Jacobi, and an interior pair's 9x9 X by Jacobi.  Mollified edge-edge
-// pairs (whose mollifier involves all four slots) take the general path.
+// (eigenvalues a s + b along y, b across); point-line and interior pairs
+// through the structure of the distance (below).  Mollified edge-edge pairs
+// (whose mollifier involves all four slots) take the general 9x9 path.
 // ---------------------------------------------------------------------------
 enum { CLS_PP = 0, CLS_PL = 1, CLS_TRI = 2, CLS_GEN = 3 };
 
@@ -896,19 +896,83 @@ __device__ __forceinline__ double terms_pp(int type, const V3 *x, double dhat, d
     }
     const double yv[3] = {y.x, y.y, y.z};
 #pragma unroll
-    for (int al = 0; al < 3; ++al)
+    for (int i = 0; i < 9; ++i)
 #pragma unroll
-      for (int be = al; be < 3; ++be)
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            if (al == be && c < r) continue;
-            const double hl = c1 * yv[r] * yv[c] + (r == c ? c0 : 0.0);
-            X[pidx(3 * al + r, 3 * be + c)] = (E[al] * E[be]) * hl;
-          }
+      for (int k = i; k < 9; ++k) {
+        const int al = i / 3, r = i % 3, be = k / 3, c = k % 3;
+        const double hl = c1 * yv[r] * yv[c] + (r == c ? c0 : 0.0);
+        X[pidx(i, k)] = (E[al] * E[be]) * hl;
+      }
   }
   return kappa * br.b;
+}
+
+// Point-line and interior pairs through the structure of the distance.
+// With the closest points' weights beta over the local vectors (G x =
+// sum_j beta_j y_j = d n; beta_0 = 1, beta_k = -a_k), the free directions
+// y_1.. (m of them, perpendicular to n) and their dual vectors e^k
+// (e^k . y_l = [k = l]), the derivatives of the energy are, with
+// c1 = e'(d) / d and c2 = e''(d),
+//   gradient  c1 d (beta (x) n)
+//   Hessian   c2 (beta (x) n)(beta (x) n)^T
+//             - c1 [ s sum_kl (e^k.e^l) (u_k (x) n)(u_l (x) n)^T
+//                    + d sum_k ((u_k (x) n)(beta (x) e^k)^T + its transpose) ]
+//             + c1 (beta (x) m)(beta (x) m)^T   (point-line: m = the third axis),
+// u_k the unit vector of local vector k.  In the Q basis beta and u_k become
+// the 3-vectors bq and E[k], and the Hessian acts on span{ a (x) n } (three
+// dimensions, orthonormal in the Q coordinates) and the one or two
+// dimensions bq (x) t_j (t_j an orthonormal basis of the free directions):
+// its projection is that of a 4x4 (point-line) or 5x5 (interior) matrix
+// [[A, B], [B^T, 0]], where the general form takes 6x6 and 9x9; the m term
+// has an eigenvalue c1 |bq|^2 < 0 and projects to zero.  A Jacobi sweep of
+// the 5x5 has 10 rotations of 5 + 5 entries, of the 9x9 36 of 9 + 9.
+// The cross products are formed as in the squared distance (contraction
+// off): close to d = 0 only the same rounding keeps n consistent with s.
+
+// X from P (packed, N = 3 + NT: the projected or plain matrix), n, t and
+// bh = bq / |bq|; cm (m m^T) is added to the part along bh (x) bh.  Entries
+// are formed in packed order, so that X can be a record in memory.
+template <int NT>
+__device__ __forceinline__ void struct_to_x(const double *P, V3 n, const V3 *t, const double *bh, double cm, V3 m,
+                                            double *X) {
+  constexpr int N = 3 + NT;
+  double tau[3][3], T[6];
+  const double nv[3] = {n.x, n.y, n.z}, mv[3] = {m.x, m.y, m.z};
+  double tv[NT][3];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    tv[j][0] = t[j].x;
+    tv[j][1] = t[j].y;
+    tv[j][2] = t[j].z;
+  }
+#pragma unroll
+  for (int al = 0; al < 3; ++al)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      double acc = 0.0;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc += P[pidxn<N>(al, 3 + j)] * tv[j][c];
+      tau[al][c] = acc;
+    }
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = r; c < 3; ++c) {
+      double acc = NT == 1 ? (cm * mv[r]) * mv[c] : 0.0;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int l = 0; l < NT; ++l) acc += (P[pidxn<N>(3 + j, 3 + l)] * tv[j][r]) * tv[l][c];
+      T[pidxn<3>(r, c)] = acc;
+    }
+#pragma unroll
+  for (int i = 0; i < 9; ++i)
+#pragma unroll
+    for (int k = i; k < 9; ++k) {
+      const int al = i / 3, r = i % 3, be = k / 3, c = k % 3;
+      X[pidx(i, k)] = (P[pidxn<N>(al, be)] * nv[r]) * nv[c] + bh[be] * (nv[r] * tau[al][c]) +
+                      bh[al] * (tau[be][r] * nv[c]) + (bh[al] * bh[be]) * T[pidxn<3>(r, c)];
+    }
 }
 
 template <int KIND>
@@ -916,85 +980,50 @@ __device__ __forceinline__ double terms_pl(int type, const V3 *x, double dhat, d
                                            bool want_h, bool project, bool sq, double *gam, double *X) {
   const uint32_t code = (uint32_t)(slot_codes<KIND>() >> (8 * type)) & 0xffu;
   const int p0 = code & 3, m0 = (code >> 2) & 3, p1 = (code >> 4) & 3, m1 = (code >> 6) & 3;
-  V3 y[3];
-  y[0] = xsub(pick4(x, p0), pick4(x, m0));
-  y[1] = xsub(pick4(x, p1), pick4(x, m1));
-  y[2] = V3{0.0, 0.0, 0.0};
-  double s;
-  {
-#pragma clang fp contract(off)
-    const V3 cr = xcross(y[0], y[1]);
-    s = xdot(cr, cr) / xdot(y[1], y[1]);
-  }
+  const V3 y0 = xsub(pick4(x, p0), pick4(x, m0)), y1 = xsub(pick4(x, p1), pick4(x, m1));
+  const V3 cr = xcross(y0, y1);
+  const double D = xdot(y1, y1), cc = xdot(cr, cr);
+  const double s = cc / D;
   const Barrier br = barrier_s(s, dhat, sq);
   if (!want_g && !want_h) return kappa * br.b;
-  Local L;
-  local_derivs<FN_PL>(y, L);
-  double E[2][3];
-  e_row(p0, m0, E[0]);
-  e_row(p1, m1, E[1]);
+  const double d = sqrt(s), iD = 1.0 / D, il = sqrt(iD), icr = 1.0 / sqrt(cc);
+  const double c1 = kappa * (2.0 * br.bs1), c2 = kappa * (4.0 * s * br.bs2 + 2.0 * br.bs1);
+  // y0 = d n + a y1 and cr = d (n x y1): n = y1 x cr / (|y1| |cr|)
+  const double f = il * icr;
+  const V3 yc = xcross(y1, cr);
+  const V3 n{yc.x * f, yc.y * f, yc.z * f};
+  const double a = dot(y0, y1) * iD;
+  double E0[3], E1[3], bq[3];
+  e_row(p0, m0, E0);
+  e_row(p1, m1, E1);
+#pragma unroll
+  for (int al = 0; al < 3; ++al) bq[al] = E0[al] - a * E1[al];
   if (want_g) {
-    double gl[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) gl[i] = kappa * (br.bs1 * L.g[i]);
-#pragma unroll
-    for (int al = 0; al < 3; ++al)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) gam[3 * al + c] = E[0][al] * gl[c] + E[1][al] * gl[3 + c];
-  }
-  if (want_h) {
-    double H6[21];
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int j = i; j < 6; ++j) H6[pidxn<6>(i, j)] = kappa * (br.bs2 * L.g[i] * L.g[j] + br.bs1 * L.H[i * 9 + j]);
-    double W[2][3];
+    const double g = c1 * d;
 #pragma unroll
     for (int al = 0; al < 3; ++al) {
-      W[0][al] = E[0][al];
-      W[1][al] = E[1][al];
+      gam[3 * al] = (g * bq[al]) * n.x;
+      gam[3 * al + 1] = (g * bq[al]) * n.y;
+      gam[3 * al + 2] = (g * bq[al]) * n.z;
     }
-    if (project) {
-      // Gram [[2,1],[1,2]] = L L^T, L = [[l00, 0], [l10, l11]]
-      constexpr double l00 = 1.4142135623730951, l10 = 0.7071067811865476, l11 = 1.2247448713915890;
-      double P[21];
+  }
+  if (want_h) {
+    const double b2 = bq[0] * bq[0] + bq[1] * bq[1] + bq[2] * bq[2], bn = sqrt(b2), ib = 1.0 / bn;
+    const V3 t[1] = {V3{y1.x * il, y1.y * il, y1.z * il}};
+    const double bh[3] = {bq[0] * ib, bq[1] * ib, bq[2] * ib};
+    double P[10];
+    const double ca = -c1 * s * iD, cb = -c1 * d * bn * il;
 #pragma unroll
-      for (int r = 0; r < 3; ++r)
+    for (int al = 0; al < 3; ++al) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const double h00 = H6[pidxn<6>(r, c)], h11 = H6[pidxn<6>(3 + r, 3 + c)];
-          const double h01 = H6[pidxn<6>(r, 3 + c)], h10 = H6[pidxn<6>(3 + r, c)];
-          if (c >= r) {
-            P[pidxn<6>(r, c)] = l00 * l00 * h00 + l00 * l10 * (h01 + h10) + l10 * l10 * h11;
-            P[pidxn<6>(3 + r, 3 + c)] = l11 * l11 * h11;
-          }
-          P[pidxn<6>(r, 3 + c)] = l00 * l11 * h01 + l10 * l11 * h11;
-        }
-      project_psd<6>(P);
-#pragma unroll
-      for (int i = 0; i < 21; ++i) H6[i] = P[i];
-#pragma unroll
-      for (int al = 0; al < 3; ++al) {
-        W[0][al] = E[0][al] * (1.0 / l00);
-        W[1][al] = (E[1][al] - l10 * W[0][al]) * (1.0 / l11);
-      }
+      for (int be = al; be < 3; ++be) P[pidxn<4>(al, be)] = c2 * bq[al] * bq[be] + ca * E1[al] * E1[be];
+      P[pidxn<4>(al, 3)] = cb * E1[al];
     }
-#pragma unroll
-    for (int al = 0; al < 3; ++al)
-#pragma unroll
-      for (int be = al; be < 3; ++be)
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            if (al == be && c < r) continue;
-            double acc = 0.0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int k = 0; k < 2; ++k) acc += (W[j][al] * W[k][be]) * H6[pidxn<6>(3 * j + r, 3 * k + c)];
-            X[pidx(3 * al + r, 3 * be + c)] = acc;
-          }
+    P[pidxn<4>(3, 3)] = 0.0;
+    if (project) project_psd<4>(P);
+    // the third axis from n and t: the rounding of cr, which close to d = 0
+    // leaves it off the plane across y1, would enter the m term at first order
+    struct_to_x<1>(P, n, t, bh, project ? 0.0 : c1 * b2, cross(n, t[0]), X);
   }
   return kappa * br.b;
 }
@@ -1002,20 +1031,67 @@ __device__ __forceinline__ double terms_pl(int type, const V3 *x, double dhat, d
 template <int KIND>
 __device__ __forceinline__ double terms_tri(const V3 *x, double dhat, double kappa, bool want_g, bool want_h,
                                             bool project, bool sq, double *gam, double *X) {
-  constexpr int TT = KIND == 0 ? (int)PT_T : (int)EE_AB;
-  const double s = type_value_t<KIND, TT>(x);
-  if (!want_g && !want_h) return kappa * barrier_s(s, dhat, sq).b;
-  double gs[9], Hs[45], gE[9], HE[45];
-  s_derivs_typed<KIND, TT>(x, gs, Hs);
-  V3 Y[3];
-  y_basis<KIND>(x, Y);
-  const double e = energy_derivs_gs<KIND>(gs, Hs, Y, s, dhat, kappa, 0.0, gE, HE, want_h, sq);
-  if (want_g) grad_to_q<KIND>(gE, gam);
-  if (want_h) {
-    to_q_basis<KIND>(HE, X);
-    if (project) project_psd<9>(X);
+  constexpr TypeDef def = type_def<KIND, KIND == 0 ? (int)PT_T : (int)EE_AB>();
+  const double s = type_value_t<KIND, KIND == 0 ? (int)PT_T : (int)EE_AB>(x);
+  const Barrier br = barrier_s(s, dhat, sq);
+  if (!want_g && !want_h) return kappa * br.b;
+  const V3 y0 = xsub(x[def.plus[0]], x[def.minus[0]]), y1 = xsub(x[def.plus[1]], x[def.minus[1]]),
+           y2 = xsub(x[def.plus[2]], x[def.minus[2]]);
+  const V3 m = xcross(y1, y2);
+  const double D = xdot(m, m), N = xdot(y0, m);
+  const double d = sqrt(s), iD = 1.0 / D, im = copysign(sqrt(iD), N);
+  const double c1 = kappa * (2.0 * br.bs1), c2 = kappa * (4.0 * s * br.bs2 + 2.0 * br.bs1);
+  const V3 n{m.x * im, m.y * im, m.z * im};
+  // dual vectors of y1, y2 and the closest point's coordinates
+  const V3 q1 = xcross(y2, m), q2 = xcross(m, y1);
+  const V3 e1{q1.x * iD, q1.y * iD, q1.z * iD}, e2{q2.x * iD, q2.y * iD, q2.z * iD};
+  const double a1 = dot(y0, e1), a2 = dot(y0, e2);
+  double E1[3], E2[3], bq[3];
+#pragma unroll
+  for (int al = 0; al < 3; ++al) {
+    const double E0 = 0.5 * (kS[def.plus[0]][al] - kS[def.minus[0]][al]);
+    E1[al] = 0.5 * (kS[def.plus[1]][al] - kS[def.minus[1]][al]);
+    E2[al] = 0.5 * (kS[def.plus[2]][al] - kS[def.minus[2]][al]);
+    bq[al] = E0 - a1 * E1[al] - a2 * E2[al];
   }
-  return e;
+  if (want_g) {
+    const double g = c1 * d;
+#pragma unroll
+    for (int al = 0; al < 3; ++al) {
+      gam[3 * al] = (g * bq[al]) * n.x;
+      gam[3 * al + 1] = (g * bq[al]) * n.y;
+      gam[3 * al + 2] = (g * bq[al]) * n.z;
+    }
+  }
+  if (want_h) {
+    const double bn = sqrt(bq[0] * bq[0] + bq[1] * bq[1] + bq[2] * bq[2]), ib = 1.0 / bn;
+    const double bh[3] = {bq[0] * ib, bq[1] * ib, bq[2] * ib};
+    const double il = 1.0 / sqrt(dot(y1, y1));
+    V3 t[2];
+    t[0] = V3{y1.x * il, y1.y * il, y1.z * il};
+    t[1] = cross(n, t[0]);
+    const double g11 = dot(e1, e1), g12 = dot(e1, e2), g22 = dot(e2, e2);
+    const double ca = -c1 * s, cb = -c1 * d * bn;
+    // e2 is perpendicular to y1, so to t[0]
+    const double b10 = cb * dot(e1, t[0]), b11 = cb * dot(e1, t[1]), b21 = cb * dot(e2, t[1]);
+    double P[15];
+#pragma unroll
+    for (int al = 0; al < 3; ++al) {
+#pragma unroll
+      for (int be = al; be < 3; ++be)
+        P[pidxn<5>(al, be)] = c2 * bq[al] * bq[be] +
+                              ca * (g11 * (E1[al] * E1[be]) + g12 * (E1[al] * E2[be] + E2[al] * E1[be]) +
+                                    g22 * (E2[al] * E2[be]));
+      P[pidxn<5>(al, 3)] = b10 * E1[al];
+      P[pidxn<5>(al, 4)] = b11 * E1[al] + b21 * E2[al];
+    }
+    P[pidxn<5>(3, 3)] = 0.0;
+    P[pidxn<5>(3, 4)] = 0.0;
+    P[pidxn<5>(4, 4)] = 0.0;
+    if (project) project_psd<5>(P);
+    struct_to_x<2>(P, n, t, bh, 0.0, n, X);
+  }
+  return kappa * br.b;
 }
 
 // any type, with the mollifier when eps_x > 0
@@ -1060,13 +1136,15 @@ __device__ __forceinline__ double pair_energy(int type, const V3 *x, double eps_
 
 // Energy, Q-basis gradient gamma[9] and Hessian X (packed, 45) of one pair
 // of class cls.  Lanes of a wavefront that share the class share the path.
-template <int KIND>
+// GEN false: no pair is mollified, and the general path (its 9x9 projection
+// takes twice the registers of the others) is left out.
+template <int KIND, bool GEN>
 __device__ __forceinline__ double pair_qterms(int cls, int type, const V3 *x, double eps_x, double dhat,
                                               double kappa, bool want_g, bool want_h, bool project, bool sq,
                                               double *gam, double *X) {
   if (cls == CLS_PP) return terms_pp<KIND>(type, x, dhat, kappa, want_g, want_h, project, sq, gam, X);
   if (cls == CLS_PL) return terms_pl<KIND>(type, x, dhat, kappa, want_g, want_h, project, sq, gam, X);
-  if (cls == CLS_TRI) return terms_tri<KIND>(x, dhat, kappa, want_g, want_h, project, sq, gam, X);
+  if (!GEN || cls == CLS_TRI) return terms_tri<KIND>(x, dhat, kappa, want_g, want_h, project, sq, gam, X);
   return terms_gen<KIND>(type, x, eps_x, dhat, kappa, want_g, want_h, project, sq, gam, X);
 }
 
