@@ -130,22 +130,6 @@ static void free_retired(eipc_ctx *c) {
   c->retired.clear();
 }
 
-__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-__global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
-static eipc_status fill_i32(eipc_ctx *c, int32_t *p, int64_t n, int32_t v, hipStream_t s) {
-  if (n == 0) return EIPC_OK;
-  k_fill_i32<<<(int)std::min<int64_t>(grid_for(n, 256), 4096), 256, 0, s>>>(p, n, v);
-  EIPC_HIP(c, hipGetLastError());
-  return EIPC_OK;
-}
-
 static eipc_status check_scene(eipc_ctx *c, const eipc_scene *sc) {
   if (!c) return EIPC_ERR_ARG;
   if (!sc) return set_err(c, EIPC_ERR_ARG, "scene is NULL");
@@ -161,13 +145,6 @@ static eipc_status check_scene(eipc_ctx *c, const eipc_scene *sc) {
   return EIPC_OK;
 }
 
-static eipc_status fill_u64(eipc_ctx *c, uint64_t *p, int64_t n, uint64_t v, hipStream_t s) {
-  if (n == 0) return EIPC_OK;
-  k_fill_u64<<<(int)std::min<int64_t>(grid_for(n, 256), 4096), 256, 0, s>>>(p, n, v);
-  EIPC_HIP(c, hipGetLastError());
-  return EIPC_OK;
-}
-
 // the EE mollifier needs the rest positions it is defined by
 static eipc_status check_mollify(eipc_ctx *c, const eipc_scene *sc, uint32_t flags) {
   if ((flags & EIPC_MOLLIFY) && !sc->x_rest && sc->n_edge > 0)
@@ -180,12 +157,24 @@ static eipc_status check_dhat(eipc_ctx *c, double dhat) {
   return EIPC_OK;
 }
 
-// device status -> API status; clears the word
-static eipc_status read_status(eipc_ctx *c, hipStream_t s, bool clear = true) {
-  uint32_t st = 0;
-  EIPC_HIP(c, hipMemcpyAsync(&st, c->status, 4, hipMemcpyDeviceToHost, s));
-  EIPC_HIP(c, hipStreamSynchronize(s));
-  if (clear && st) EIPC_HIP(c, hipMemsetAsync(c->status, 0, 4, s));
+// One launch writes the wanted device words to pinned host memory, read
+// after a synchronization: a copy each costs a launch and, into pageable
+// memory, a wait of its own.
+__global__ void k_collect(Collect col, int64_t *host) {
+  const int i = threadIdx.x;
+  if (i < col.n) host[i] = col.bytes[i] == 4 ? (int64_t)*(const uint32_t *)col.p[i] : *(const int64_t *)col.p[i];
+}
+
+eipc_status launch_collect(eipc_ctx *c, const Collect &col, hipStream_t s) {
+  if (col.n == 0) return EIPC_OK;
+  k_collect<<<1, 64, 0, s>>>(col, c->host_res);
+  EIPC_HIP(c, hipGetLastError());
+  return EIPC_OK;
+}
+
+// device status word -> API status; clears the word
+static eipc_status decode_status(eipc_ctx *c, uint32_t st, hipStream_t s) {
+  if (st) EIPC_HIP(c, hipMemsetAsync(c->status, 0, 4, s));
   if (st & ST_BAD_W) return set_err(c, EIPC_ERR_ARG, "a row of W has more than 4 weights");
   if (st & ST_BAD_SCENE) return set_err(c, EIPC_ERR_ARG, "a vertex scene id is out of range");
   if (st & ST_PLAN_OVERFLOW) return set_err(c, EIPC_ERR_CAPACITY, "a capacity of the step plan was exceeded");
@@ -199,18 +188,26 @@ static eipc_status read_status(eipc_ctx *c, hipStream_t s, bool clear = true) {
   return EIPC_OK;
 }
 
+static eipc_status read_status(eipc_ctx *c, hipStream_t s) {
+  Collect col;
+  col.add(c->status, 4);
+  EIPC_TRY(launch_collect(c, col, s));
+  EIPC_HIP(c, hipStreamSynchronize(s));
+  return decode_status(c, (uint32_t)c->host_res[0], s);
+}
+
 static int64_t pow2_at_least(int64_t v) {
   uint64_t p = 1;
   while ((int64_t)p < v) p <<= 1;
   return (int64_t)std::min<uint64_t>(p, 1ull << 34);
 }
 
-// global block hash of the reduced Hessian, cleared (int64 keys, -1 empty)
-static eipc_status hess_table(eipc_ctx *c, int64_t cap, HessOut &h, hipStream_t s) {
+// global block hash of the reduced Hessian, to be cleared (int64 keys, -1 empty)
+static eipc_status hess_table(eipc_ctx *c, int64_t cap, HessOut &h, FillList &fl) {
   EIPC_TRY(ensure_t(c, B_HKEY, (size_t)cap, &h.hkey));
   EIPC_TRY(ensure_t(c, B_HVAL, (size_t)cap * 9, &h.hval));
-  EIPC_TRY(fill_u64(c, (uint64_t *)h.hkey, cap, ~0ull, s));
-  EIPC_TRY(launch_zero(c, h.hval, sizeof(double) * 9 * cap, s));
+  fl.add(h.hkey, sizeof(int64_t) * cap, ~0ull);
+  fl.add(h.hval, sizeof(double) * 9 * cap, 0);
   h.kind = 2;
   h.hmask = (uint64_t)(cap - 1);
   return EIPC_OK;
@@ -223,10 +220,63 @@ static eipc_status narrow_both(eipc_ctx *c, const eipc_scene *sc, const double *
   EIPC_TRY(ensure_t(c, B_TYP_PT, (size_t)std::max<int64_t>(n_pt, 1), typ_pt));
   EIPC_TRY(ensure_t(c, B_ACT_EE, (size_t)std::max<int64_t>(n_ee, 1), act_ee));
   EIPC_TRY(ensure_t(c, B_TYP_EE, (size_t)std::max<int64_t>(n_ee, 1), typ_ee));
-  EIPC_TRY(launch_zero(c, c->counters + 2, 2 * sizeof(int64_t), s));
   EIPC_TRY(launch_narrow(c, sc, 0, xs, pt, n_pt, dhat, *act_pt, *typ_pt, c->counters + 2, s));
   EIPC_TRY(launch_narrow(c, sc, 1, xs, ee, n_ee, dhat, *act_ee, *typ_ee, c->counters + 3, s));
   return EIPC_OK;
+}
+
+// The BSR view of a filled block table for a per-call reduction: compacted
+// at the capacity of the last one (grown and compacted again when too
+// small), so that the only synchronization is the one that reads the
+// results: host_res = {status, blocks, words of col...}.  Arena mode sizes
+// the buffers by the count first.  *full: the block table itself was too
+// small (nothing compacted is valid).  The rows' counters are cleared by the
+// caller (bsr_clear).
+static eipc_status bsr_read(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out, const Collect &col, bool *full,
+                            hipStream_t s) {
+  *full = false;
+  for (int attempt = 0; attempt < 4; ++attempt) {
+    int64_t cap = -1;
+    if (!c->arena) {
+      cap = std::max<int64_t>(c->nnzb_guess, 16 * (int64_t)n_node + 1024);
+      cap = std::min<int64_t>(cap, std::max<int64_t>((int64_t)n_node * n_node, 1));
+    } else {
+      Collect k;
+      k.add(c->status, 4);
+      EIPC_TRY(launch_collect(c, k, s));
+      EIPC_HIP(c, hipStreamSynchronize(s));
+      if ((uint32_t)c->host_res[0] & ST_HASH_OVERFLOW) {
+        *full = true;
+        return EIPC_OK;
+      }
+    }
+    if (attempt > 0) {
+      FillList fl;
+      EIPC_TRY(bsr_clear(c, n_node, fl));
+      EIPC_TRY(launch_fill(c, fl, s));
+    }
+    // word 1 of the status takes the capacity flag: it is no error here
+    EIPC_TRY(bsr_compact(c, n_node, h, out, s, cap, c->status + 1));
+    int64_t *rowptr;
+    EIPC_TRY(ensure_t(c, B_ROWPTR, (size_t)n_node + 1, &rowptr));
+    Collect k;
+    k.add(c->status, 4);
+    k.add(rowptr + n_node, 8);
+    for (int i = 0; i < col.n; ++i) k.add(col.p[i], col.bytes[i]);
+    EIPC_TRY(launch_collect(c, k, s));
+    EIPC_HIP(c, hipStreamSynchronize(s));
+    if ((uint32_t)c->host_res[0] & ST_HASH_OVERFLOW) {
+      *full = true;
+      return EIPC_OK;
+    }
+    const int64_t nnzb = c->host_res[1];
+    if (cap < 0 || nnzb <= cap) {
+      out->nnzb = nnzb;
+      return EIPC_OK;
+    }
+    c->nnzb_guess = nnzb + nnzb / 4 + 1024;
+  }
+  return set_err(c, EIPC_ERR_CAPACITY, "BSR compaction did not converge");
 }
 
 }  // namespace eipc
@@ -260,6 +310,7 @@ eipc_status eipc_create(eipc_ctx **out, int32_t device, size_t reserve_bytes) {
   if (hipSetDevice(device) != hipSuccess || hipMalloc(&c->status, 256) != hipSuccess ||
       hipMalloc(&c->stats, 32 * sizeof(double)) != hipSuccess ||
       hipMalloc(&c->counters, 16 * sizeof(int64_t)) != hipSuccess ||
+      hipHostMalloc((void **)&c->host_res, 64 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
       hipMemset(c->status, 0, 256) != hipSuccess || hipMemset(c->counters, 0, 16 * sizeof(int64_t)) != hipSuccess) {
     eipc_destroy(c);
     return EIPC_ERR_HIP;
@@ -306,6 +357,7 @@ void eipc_destroy(eipc_ctx *c) {
   free_retired(c);
   if (c->status) hipFree(c->status);
   if (c->stats) hipFree(c->stats);
+  if (c->host_res) hipHostFree(c->host_res);
   if (c->counters) hipFree(c->counters);
   if (c->fork_ev) hipEventDestroy(c->fork_ev);
   if (c->join_ev) hipEventDestroy(c->join_ev);
@@ -382,13 +434,20 @@ eipc_status eipc_build_candidates(eipc_ctx *c, const eipc_scene *sc, const doubl
   double *xs;
   EIPC_TRY(ensure_t(c, B_X, (size_t)PSTRIDE * sc->n_vert + 1, &xs));
   EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  eipc_status s1 = broad_phase(c, sc, 0, xs, nullptr, dhat, pt, cap_pt, n_pt, 1, s);
-  if ((s1 != EIPC_OK && s1 != EIPC_ERR_CAPACITY) || c->scratch_short) return s1;
-  eipc_status s2 = broad_phase(c, sc, 1, xs, nullptr, dhat, ee, cap_ee, n_ee, 1, s);
-  if ((s2 != EIPC_OK && s2 != EIPC_ERR_CAPACITY) || c->scratch_short) return s2;
-  eipc_status st = read_status(c, s);
+  BPReq req[2] = {{1, pt, cap_pt, -1, 0}, {1, ee, cap_ee, -1, 0}};
+  const eipc_status bs = broad_phase(c, sc, xs, nullptr, dhat, req, s,
+                                     [&](const int32_t *const *, const int64_t *, const int64_t *const *, Collect &col) {
+                                       col.add(c->status, 4);
+                                       return EIPC_OK;
+                                     });
+  *n_pt = req[0].n;
+  *n_ee = req[1].n;
+  if ((bs != EIPC_OK && bs != EIPC_ERR_CAPACITY) || c->scratch_short) return bs;
+  // (the status was read with the counts, except where nothing followed them)
+  const eipc_status st = bs == EIPC_OK || !c->arena ? decode_status(c, (uint32_t)c->host_res[c->collect_base], s)
+                                                    : read_status(c, s);
   if (st != EIPC_OK && st != EIPC_WARN_CCD_CAPPED) return st;
-  if (s1 == EIPC_ERR_CAPACITY || s2 == EIPC_ERR_CAPACITY)
+  if (bs == EIPC_ERR_CAPACITY)
     return set_err(c, EIPC_ERR_CAPACITY, "candidates need %lld PT / %lld EE slots", (long long)*n_pt,
                    (long long)*n_ee);
   return EIPC_OK;
@@ -413,25 +472,39 @@ eipc_status eipc_barrier_reduce(eipc_ctx *c, const eipc_scene *sc, const double 
   EIPC_HIP(c, hipSetDevice(c->device));
   double *xs;
   EIPC_TRY(ensure_t(c, B_X, (size_t)PSTRIDE * sc->n_vert + 1, &xs));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
   int32_t *act_pt, *typ_pt, *act_ee, *typ_ee;
-  EIPC_TRY(narrow_both(c, sc, xs, pt, n_pt, ee, n_ee, dhat, &act_pt, &typ_pt, &act_ee, &typ_ee, s));
   const int64_t n3 = 3 * (int64_t)sc->n_node;
+  double *g = (flags & EIPC_GRAD) ? grad_q : nullptr;
+  const uint32_t f = flags & (want_h ? ~0u : ~(uint32_t)EIPC_HESS);
+  Collect col;  // the active counts, where they are wanted
+  if (n_active) {
+    col.add(c->counters + 2, 8);
+    col.add(c->counters + 3, 8);
+  }
+  bool read = false;  // host_res = {status, blocks, counts}
   for (int attempt = 0;; ++attempt) {
-    if (energy) EIPC_TRY(launch_zero(c, energy, sizeof(double) * n_scene_of(sc), s));
-    if (grad_q && (flags & EIPC_GRAD)) EIPC_TRY(launch_zero(c, grad_q, sizeof(double) * n3, s));
+    FillList fl;
+    if (attempt == 0) fl.add(c->counters + 2, 2 * sizeof(int64_t), 0);
+    fl.add(energy, sizeof(double) * n_scene_of(sc), 0);
+    fl.add(g, sizeof(double) * n3, 0);
     HessOut h{0, nullptr, nullptr, nullptr, 0};
     if (want_h && hess_dense) {
-      EIPC_TRY(launch_zero(c, hess_dense, sizeof(double) * n3 * n3, s));
+      fl.add(hess_dense, sizeof(double) * n3 * n3, 0);
       h.kind = 1;
       h.dense = hess_dense;
     } else if (want_h) {
       int64_t cap = std::max<int64_t>(c->hash_cap, pow2_at_least(16 * (int64_t)sc->n_node));
       c->hash_cap = cap;
-      EIPC_TRY(hess_table(c, cap, h, s));
+      EIPC_TRY(hess_table(c, cap, h, fl));
+      EIPC_TRY(bsr_clear(c, sc->n_node, fl));
     }
-    const uint32_t f = flags & (want_h ? ~0u : ~(uint32_t)EIPC_HESS);
-    double *g = (flags & EIPC_GRAD) ? grad_q : nullptr;
+    if (g || want_h)
+      for (int kind = 0; kind < 2; ++kind) EIPC_TRY(sort_clear(c, sc, kind, fl));
+    EIPC_TRY(launch_fill(c, fl, s));
+    if (attempt == 0) {
+      EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
+      EIPC_TRY(narrow_both(c, sc, xs, pt, n_pt, ee, n_ee, dhat, &act_pt, &typ_pt, &act_ee, &typ_ee, s));
+    }
     // with enough pairs of both kinds, the PT chain runs on the side stream
     // beside the EE chain, as in the planned step (their outputs meet in
     // atomics; their scratch is per kind); small calls stay on one stream,
@@ -455,28 +528,32 @@ eipc_status eipc_barrier_reduce(eipc_ctx *c, const eipc_scene *sc, const double 
     EIPC_TRY(b1);
     if (h.kind == 1) EIPC_TRY(launch_dense_mirror(c, sc->n_node, hess_dense, s));
     if (h.kind == 2) {
-      uint32_t st = 0;
-      EIPC_HIP(c, hipMemcpyAsync(&st, c->status, 4, hipMemcpyDeviceToHost, s));
-      EIPC_HIP(c, hipStreamSynchronize(s));
-      if ((st & ST_HASH_OVERFLOW) && attempt < 8) {
-        st &= ~ST_HASH_OVERFLOW;
+      bool full = false;
+      EIPC_TRY(bsr_read(c, sc->n_node, h, hess_bsr, col, &full, s));
+      if (full && attempt < 8) {
+        uint32_t st = (uint32_t)c->host_res[0] & ~ST_HASH_OVERFLOW;
         EIPC_HIP(c, hipMemcpyAsync(c->status, &st, 4, hipMemcpyHostToDevice, s));
+        EIPC_HIP(c, hipStreamSynchronize(s));
         c->hash_cap *= 4;
         continue;
       }
-      if (st & ST_HASH_OVERFLOW) return set_err(c, EIPC_ERR_CAPACITY, "reduced Hessian hash overflow");
-      EIPC_TRY(bsr_compact(c, sc->n_node, h, hess_bsr, s));
+      if (full) return set_err(c, EIPC_ERR_CAPACITY, "reduced Hessian hash overflow");
+      read = true;
     }
     break;
   }
-  if (n_active) {
-    int64_t cnt[2];
-    EIPC_HIP(c, hipMemcpyAsync(cnt, c->counters + 2, 16, hipMemcpyDeviceToHost, s));
+  if (!read && (n_active || hess_bsr)) {
+    Collect k;
+    k.add(c->status, 4);
+    k.add(c->status, 4);
+    for (int i = 0; i < col.n; ++i) k.add(col.p[i], col.bytes[i]);
+    EIPC_TRY(launch_collect(c, k, s));
     EIPC_HIP(c, hipStreamSynchronize(s));
-    *n_active = cnt[0] + cnt[1];
+    read = true;
   }
-  if (n_active || hess_bsr) {
-    eipc_status st = read_status(c, s);
+  if (n_active) *n_active = c->host_res[2] + c->host_res[3];
+  if (read) {
+    const eipc_status st = decode_status(c, (uint32_t)c->host_res[0], s);
     if (st != EIPC_OK && st != EIPC_WARN_CCD_CAPPED) return st;
   }
   return EIPC_OK;
@@ -498,25 +575,36 @@ eipc_status eipc_ccd_max_step(eipc_ctx *c, const eipc_scene *sc, const double *q
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3 + 1, &xs));
   EIPC_TRY(ensure_t(c, B_P, (size_t)n3 + 1, &ps));
   EIPC_TRY(ensure_t(c, B_X1, (size_t)n3 + 1, &x1s));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_embed(c, sc, dq, dx_off, ps, nullptr, s));
-  EIPC_TRY(launch_add_soa(c, n3, xs, ps, x1s, s));
-  int64_t npt = 0, nee = 0;
-  int32_t *cpt = nullptr, *cee = nullptr;
-  EIPC_TRY(broad_phase(c, sc, 0, xs, x1s, dhat, nullptr, 0, &npt, 0, s, B_CAND_PT, &cpt));
-  EIPC_TRY(broad_phase(c, sc, 1, xs, x1s, dhat, nullptr, 0, &nee, 0, s, B_CAND_EE, &cee));
+  EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
   const int nsc = n_scene_of(sc);
   uint64_t *abits;
   EIPC_TRY(ensure_t(c, B_ALPHA, (size_t)nsc, &abits));
   uint64_t tb;
   std::memcpy(&tb, &t_max, 8);
-  EIPC_TRY(fill_u64(c, abits, nsc, tb, s));
-  EIPC_TRY(launch_ccd(c, sc, 0, xs, ps, cpt, npt, sfac, t_max, max_iter, abits, nullptr, nullptr, s));
-  EIPC_TRY(launch_ccd(c, sc, 1, xs, ps, cee, nee, sfac, t_max, max_iter, abits, nullptr, nullptr, s));
-  EIPC_HIP(c, hipMemcpyAsync(alpha, abits, 8 * (size_t)nsc, hipMemcpyDeviceToHost, s));
-  EIPC_HIP(c, hipStreamSynchronize(s));
-  if (n_cand) *n_cand = npt + nee;
-  return read_status(c, s);
+  BPReq req[2] = {{0, nullptr, 0, B_CAND_PT, 0}, {0, nullptr, 0, B_CAND_EE, 0}};
+  // the advancement follows the broad phase on the device's own counts, and
+  // everything is read back at once
+  auto ccd = [&](const int32_t *const *lists, const int64_t *caps, const int64_t *const *d_n, Collect &col) {
+    FillList fl;
+    fl.add(abits, 8 * (size_t)nsc, tb);
+    fl.add(c->counters + 9, 16, 0);
+    EIPC_TRY(launch_fill(c, fl, s));
+    for (int kind = 0; kind < 2; ++kind)
+      if (lists[kind])
+        EIPC_TRY(launch_ccd(c, sc, kind, xs, ps, lists[kind], caps[kind], sfac, t_max, max_iter, abits, nullptr,
+                            nullptr, s, d_n[kind]));
+    col.add(c->status, 4);
+    if (nsc == 1)
+      col.add(abits, 8);
+    else
+      EIPC_HIP(c, hipMemcpyAsync(alpha, abits, 8 * (size_t)nsc, hipMemcpyDeviceToHost, s));
+    return (eipc_status)EIPC_OK;
+  };
+  EIPC_TRY(broad_phase(c, sc, xs, x1s, dhat, req, s, ccd));
+  const int64_t *w = c->host_res + c->collect_base;
+  if (nsc == 1) std::memcpy(alpha, &w[1], 8);
+  if (n_cand) *n_cand = req[0].n + req[1].n;
+  return decode_status(c, (uint32_t)w[0], s);
 }
 
 eipc_status eipc_barrier_hvp(eipc_ctx *c, const eipc_scene *sc, const double *q, const int32_t *pt, int64_t n_pt,
@@ -537,12 +625,15 @@ eipc_status eipc_barrier_hvp(eipc_ctx *c, const eipc_scene *sc, const double *q,
   double *xs, *xvs;
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3 + 1, &xs));
   EIPC_TRY(ensure_t(c, B_XV, (size_t)n3 + 1, &xvs));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_embed(c, sc, v, v_off, xvs, nullptr, s));
+  FillList fl;
+  fl.add(c->counters + 2, 2 * sizeof(int64_t), 0);
+  fl.add(out, sizeof(double) * 3 * (size_t)sc->n_node, 0);
+  fl.add(out_off, sizeof(double) * 3 * (size_t)sc->n_vert, 0);
+  for (int kind = 0; kind < 2; ++kind) EIPC_TRY(sort_clear(c, sc, kind, fl));
+  EIPC_TRY(launch_fill(c, fl, s));
+  EIPC_TRY(launch_embed_swept(c, sc, q, v, v_off, xs, xvs, nullptr, s));
   int32_t *act_pt, *typ_pt, *act_ee, *typ_ee;
   EIPC_TRY(narrow_both(c, sc, xs, pt, n_pt, ee, n_ee, dhat, &act_pt, &typ_pt, &act_ee, &typ_ee, s));
-  EIPC_TRY(launch_zero(c, out, sizeof(double) * 3 * (size_t)sc->n_node, s));
-  if (out_off) EIPC_TRY(launch_zero(c, out_off, sizeof(double) * 3 * (size_t)sc->n_vert, s));
   EIPC_TRY(launch_hvp(c, sc, 0, xs, xvs, pt, act_pt, typ_pt, c->counters + 2, n_pt, dhat, kappa, flags, out, out_off,
                       s));
   EIPC_TRY(launch_hvp(c, sc, 1, xs, xvs, ee, act_ee, typ_ee, c->counters + 3, n_ee, dhat, kappa, flags, out, out_off,
@@ -581,13 +672,14 @@ eipc_status eipc_barrier_hvp_noalloc(eipc_ctx *c, const eipc_scene *sc, const do
   int32_t *typ_pt = (int32_t *)(base + 256 + 2 * pos + lpt);
   int32_t *act_ee = (int32_t *)(base + 256 + 2 * pos + 2 * lpt);
   int32_t *typ_ee = (int32_t *)(base + 256 + 2 * pos + 2 * lpt + lee);
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_embed(c, sc, v, v_off, xvs, nullptr, s));
-  EIPC_TRY(launch_zero(c, cnt, 2 * sizeof(int64_t), s));  // the array keeps the last call's counts
+  FillList fl;
+  fl.add(cnt, 2 * sizeof(int64_t), 0);  // the array keeps the last call's counts
+  fl.add(out, sizeof(double) * 3 * (size_t)sc->n_node, 0);
+  fl.add(out_off, sizeof(double) * 3 * (size_t)sc->n_vert, 0);
+  EIPC_TRY(launch_fill(c, fl, s));
+  EIPC_TRY(launch_embed_swept(c, sc, q, v, v_off, xs, xvs, nullptr, s));
   EIPC_TRY(launch_narrow(c, sc, 0, xs, pt, n_pt, dhat, act_pt, typ_pt, cnt, s));
   EIPC_TRY(launch_narrow(c, sc, 1, xs, ee, n_ee, dhat, act_ee, typ_ee, cnt + 1, s));
-  EIPC_TRY(launch_zero(c, out, sizeof(double) * 3 * (size_t)sc->n_node, s));
-  if (out_off) EIPC_TRY(launch_zero(c, out_off, sizeof(double) * 3 * (size_t)sc->n_vert, s));
   EIPC_TRY(launch_hvp(c, sc, 0, xs, xvs, pt, act_pt, typ_pt, cnt, n_pt, dhat, kappa, flags, out, out_off, s, false));
   EIPC_TRY(launch_hvp(c, sc, 1, xs, xvs, ee, act_ee, typ_ee, cnt + 1, n_ee, dhat, kappa, flags, out, out_off, s,
                       false));
@@ -638,34 +730,36 @@ eipc_status eipc_friction_reduce(eipc_ctx *c, const eipc_scene *sc, const double
   double *e = (flags & EIPC_ENERGY) ? energy : nullptr;
   double *g = (flags & EIPC_GRAD) ? grad_q : nullptr;
   for (int attempt = 0;; ++attempt) {
-    if (e) EIPC_TRY(launch_zero(c, e, sizeof(double), s));
-    if (g) EIPC_TRY(launch_zero(c, g, sizeof(double) * n3, s));
+    FillList fl;
+    fl.add(e, sizeof(double), 0);
+    fl.add(g, sizeof(double) * n3, 0);
     HessOut h{0, nullptr, nullptr, nullptr, 0};
     if (want_h && hess_dense) {
-      EIPC_TRY(launch_zero(c, hess_dense, sizeof(double) * n3 * n3, s));
+      fl.add(hess_dense, sizeof(double) * n3 * n3, 0);
       h.kind = 1;
       h.dense = hess_dense;
     } else if (want_h) {
       int64_t cap = std::max<int64_t>(c->hash_cap, pow2_at_least(16 * (int64_t)sc->n_node));
       c->hash_cap = cap;
-      EIPC_TRY(hess_table(c, cap, h, s));
+      EIPC_TRY(hess_table(c, cap, h, fl));
+      EIPC_TRY(bsr_clear(c, sc->n_node, fl));
     }
+    EIPC_TRY(launch_fill(c, fl, s));
     EIPC_TRY(launch_friction(c, sc, 0, xs, pt, n_pt, lag_pt, mu, eps_h, e, g, h, s));
     EIPC_TRY(launch_friction(c, sc, 1, xs, ee, n_ee, lag_ee, mu, eps_h, e, g, h, s));
     if (h.kind == 1) EIPC_TRY(launch_dense_mirror(c, sc->n_node, hess_dense, s));
     if (h.kind == 2) {
-      uint32_t st = 0;
-      EIPC_HIP(c, hipMemcpyAsync(&st, c->status, 4, hipMemcpyDeviceToHost, s));
-      EIPC_HIP(c, hipStreamSynchronize(s));
-      if ((st & ST_HASH_OVERFLOW) && attempt < 8) {
-        st &= ~ST_HASH_OVERFLOW;
+      bool full = false;
+      EIPC_TRY(bsr_read(c, sc->n_node, h, hess_bsr, Collect(), &full, s));
+      if (full && attempt < 8) {
+        uint32_t st = (uint32_t)c->host_res[0] & ~ST_HASH_OVERFLOW;
         EIPC_HIP(c, hipMemcpyAsync(c->status, &st, 4, hipMemcpyHostToDevice, s));
+        EIPC_HIP(c, hipStreamSynchronize(s));
         c->hash_cap *= 4;
         continue;
       }
-      if (st & ST_HASH_OVERFLOW) return set_err(c, EIPC_ERR_CAPACITY, "reduced Hessian hash overflow");
-      EIPC_TRY(bsr_compact(c, sc->n_node, h, hess_bsr, s));
-      eipc_status st2 = read_status(c, s);
+      if (full) return set_err(c, EIPC_ERR_CAPACITY, "reduced Hessian hash overflow");
+      const eipc_status st2 = decode_status(c, (uint32_t)c->host_res[0], s);
       if (st2 != EIPC_OK && st2 != EIPC_WARN_CCD_CAPPED) return st2;
     }
     break;
@@ -691,12 +785,15 @@ eipc_status eipc_narrow_phase(eipc_ctx *c, const eipc_scene *sc, const double *q
   EIPC_TRY(launch_zero(c, c->counters + 2, 2 * sizeof(int64_t), s));
   EIPC_TRY(launch_narrow(c, sc, 0, xs, pt, n_pt, dhat, act_pt, type_pt, c->counters + 2, s));
   EIPC_TRY(launch_narrow(c, sc, 1, xs, ee, n_ee, dhat, act_ee, type_ee, c->counters + 3, s));
-  int64_t cnt[2];
-  EIPC_HIP(c, hipMemcpyAsync(cnt, c->counters + 2, 16, hipMemcpyDeviceToHost, s));
+  Collect col;
+  col.add(c->status, 4);
+  col.add(c->counters + 2, 8);
+  col.add(c->counters + 3, 8);
+  EIPC_TRY(launch_collect(c, col, s));
   EIPC_HIP(c, hipStreamSynchronize(s));
-  *n_act_pt = cnt[0];
-  *n_act_ee = cnt[1];
-  eipc_status st = read_status(c, s);
+  *n_act_pt = c->host_res[1];
+  *n_act_ee = c->host_res[2];
+  const eipc_status st = decode_status(c, (uint32_t)c->host_res[0], s);
   return st == EIPC_WARN_CCD_CAPPED ? EIPC_OK : st;
 }
 
@@ -732,15 +829,14 @@ eipc_status eipc_ccd_candidates(eipc_ctx *c, const eipc_scene *sc, const double 
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3 + 1, &xs));
   EIPC_TRY(ensure_t(c, B_P, (size_t)n3 + 1, &ps));
   EIPC_TRY(ensure_t(c, B_X1, (size_t)n3 + 1, &x1s));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_embed(c, sc, dq, dx_off, ps, nullptr, s));
-  EIPC_TRY(launch_add_soa(c, n3, xs, ps, x1s, s));
-  eipc_status s1 = broad_phase(c, sc, 0, xs, x1s, dhat, pt, cap_pt, n_pt, 1, s);
-  if ((s1 != EIPC_OK && s1 != EIPC_ERR_CAPACITY) || c->scratch_short) return s1;
-  eipc_status s2 = broad_phase(c, sc, 1, xs, x1s, dhat, ee, cap_ee, n_ee, 1, s);
-  if ((s2 != EIPC_OK && s2 != EIPC_ERR_CAPACITY) || c->scratch_short) return s2;
+  EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
+  BPReq req[2] = {{1, pt, cap_pt, -1, 0}, {1, ee, cap_ee, -1, 0}};
+  const eipc_status bs = broad_phase(c, sc, xs, x1s, dhat, req, s);
+  *n_pt = req[0].n;
+  *n_ee = req[1].n;
+  if ((bs != EIPC_OK && bs != EIPC_ERR_CAPACITY) || c->scratch_short) return bs;
   EIPC_HIP(c, hipStreamSynchronize(s));
-  if (s1 == EIPC_ERR_CAPACITY || s2 == EIPC_ERR_CAPACITY)
+  if (bs == EIPC_ERR_CAPACITY)
     return set_err(c, EIPC_ERR_CAPACITY, "swept candidates need %lld PT / %lld EE slots", (long long)*n_pt,
                    (long long)*n_ee);
   return EIPC_OK;
@@ -760,8 +856,7 @@ eipc_status eipc_ccd_toi(eipc_ctx *c, const eipc_scene *sc, const double *q, con
   double *xs, *ps;
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3 + 1, &xs));
   EIPC_TRY(ensure_t(c, B_P, (size_t)n3 + 1, &ps));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_embed(c, sc, dq, dx_off, ps, nullptr, s));
+  EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, nullptr, s));
   return launch_ccd(c, sc, kind, xs, ps, pairs, n, sfac, t_max, max_iter, nullptr, t, iters, s);
 }
 
@@ -870,8 +965,8 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
                         {(uint32_t)plan->buckets[3], plan->ent[3], plan->swept_ee, plan->qent[3]}};
   double *xs;
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3v + 1, &xs));
-  EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  EIPC_TRY(launch_zero(c, cn + 2, 7 * sizeof(int64_t), s));
+  FillList fl;  // everything the step clears, in one launch
+  fl.add(cn + 2, 9 * sizeof(int64_t), 0);
   int32_t *act_pt, *typ_pt, *act_ee, *typ_ee;
   EIPC_TRY(ensure_t(c, B_ACT_PT, (size_t)std::max<int64_t>(plan->act_pt, 1), &act_pt));
   EIPC_TRY(ensure_t(c, B_TYP_PT, (size_t)std::max<int64_t>(plan->act_pt, 1), &typ_pt));
@@ -879,13 +974,19 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
   EIPC_TRY(ensure_t(c, B_TYP_EE, (size_t)std::max<int64_t>(plan->act_ee, 1), &typ_ee));
   // barrier targets, cleared before any pair is added
   const int64_t n3 = 3 * (int64_t)sc->n_node;
-  if (energy) EIPC_TRY(launch_zero(c, energy, sizeof(double) * n_scene_of(sc), s));
+  fl.add(energy, sizeof(double) * n_scene_of(sc), 0);
   double *g = (flags & EIPC_GRAD) ? grad_q : nullptr;
-  if (g) EIPC_TRY(launch_zero(c, g, sizeof(double) * n3, s));
+  fl.add(g, sizeof(double) * n3, 0);
   HessOut h{0, nullptr, nullptr, nullptr, 0};
-  if (want_h) EIPC_TRY(hess_table(c, plan->hess_blocks, h, s));
+  if (want_h) {
+    EIPC_TRY(hess_table(c, plan->hess_blocks, h, fl));
+    EIPC_TRY(bsr_clear(c, sc->n_node, fl));
+  }
   const uint32_t f = flags & (want_h ? ~0u : ~(uint32_t)EIPC_HESS);
   const bool barrier = energy || g || want_h;
+  if (g || want_h)
+    for (int kind = 0; kind < 2; ++kind) EIPC_TRY(sort_clear(c, sc, kind, fl));
+  BPRun run[2];
   if (alpha) {
     // one swept broad phase per kind; candidates at q filtered from it pair
     // by pair in the same sweep as the step bound's first pass.  The PT
@@ -897,13 +998,15 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     int32_t *cpt, *cee;
     EIPC_TRY(ensure_t(c, B_P, (size_t)n3v + 1, &ps));
     EIPC_TRY(ensure_t(c, B_X1, (size_t)n3v + 1, &x1s));
-    EIPC_TRY(launch_embed(c, sc, dq, dx_off, ps, nullptr, s));
-    EIPC_TRY(launch_add_soa(c, n3v, xs, ps, x1s, s));
     EIPC_TRY(ensure_t(c, B_CAND_PT, (size_t)2 * std::max<int64_t>(plan->swept_pt, 1), &cpt));
     EIPC_TRY(ensure_t(c, B_CAND_EE, (size_t)2 * std::max<int64_t>(plan->swept_ee, 1), &cee));
     uint64_t tb;
     std::memcpy(&tb, &t_max, 8);
-    EIPC_TRY(fill_u64(c, (uint64_t *)alpha, n_scene_of(sc), tb, s));
+    fl.add(alpha, 8 * (size_t)n_scene_of(sc), tb);
+    for (int kind = 0; kind < 2; ++kind)
+      EIPC_TRY(bp_planned_begin(c, sc, kind, xs, x1s, dhat, bp[2 + kind], run[kind], fl));
+    EIPC_TRY(launch_fill(c, fl, s));
+    EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
     EIPC_HIP(c, hipEventRecord(c->fork_ev, s));
     EIPC_HIP(c, hipStreamWaitEvent(c->side, c->fork_ev, 0));
     auto chains = [&]() -> eipc_status {
@@ -913,8 +1016,7 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
         int32_t *act = kind == 0 ? act_pt : act_ee, *typ = kind == 0 ? typ_pt : typ_ee;
         const int64_t swept_cap = kind == 0 ? plan->swept_pt : plan->swept_ee;
         const int64_t act_cap = kind == 0 ? plan->act_pt : plan->act_ee;
-        EIPC_TRY(broad_phase(c, sc, kind, xs, x1s, dhat, cand, swept_cap, nullptr, 0, st, -1, nullptr,
-                             &bp[2 + kind], cn + 7 + kind));
+        EIPC_TRY(bp_planned_run(c, run[kind], cand, swept_cap, cn + 7 + kind, st));
         EIPC_TRY(launch_narrow_ccd(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, dhat, act, typ, act_cap,
                                    cn + 2 + kind, cn + 5 + kind, sfac, t_max, max_iter, (uint64_t *)alpha, st));
         EIPC_TRY(launch_ccd_long(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, sfac, t_max, max_iter,
@@ -947,8 +1049,12 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     c->step_pair_ctr[1] = 6;
     c->step_pair_cap[0] = plan->cand_pt;
     c->step_pair_cap[1] = plan->cand_ee;
-    EIPC_TRY(broad_phase(c, sc, 0, xs, nullptr, dhat, ppt, plan->cand_pt, nullptr, 0, s, -1, nullptr, &bp[0], cn + 5));
-    EIPC_TRY(broad_phase(c, sc, 1, xs, nullptr, dhat, pee, plan->cand_ee, nullptr, 0, s, -1, nullptr, &bp[1], cn + 6));
+    for (int kind = 0; kind < 2; ++kind)
+      EIPC_TRY(bp_planned_begin(c, sc, kind, xs, nullptr, dhat, bp[kind], run[kind], fl));
+    EIPC_TRY(launch_fill(c, fl, s));
+    EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
+    EIPC_TRY(bp_planned_run(c, run[0], ppt, plan->cand_pt, cn + 5, s));
+    EIPC_TRY(bp_planned_run(c, run[1], pee, plan->cand_ee, cn + 6, s));
     EIPC_TRY(launch_narrow(c, sc, 0, xs, ppt, plan->cand_pt, dhat, act_pt, typ_pt, cn + 2, s, cn + 5, plan->act_pt));
     EIPC_TRY(launch_narrow(c, sc, 1, xs, pee, plan->cand_ee, dhat, act_ee, typ_ee, cn + 3, s, cn + 6, plan->act_ee));
     if (barrier) {
@@ -958,7 +1064,7 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
                               s));
     }
   }
-  if (want_h) EIPC_TRY(bsr_compact(c, sc->n_node, h, hess_bsr, s, plan->nnzb));
+  if (want_h) EIPC_TRY(bsr_compact(c, sc->n_node, h, hess_bsr, s, plan->nnzb, c->status));
   for (int kind = 0; kind < 2; ++kind) {
     c->step_act[kind] = kind == 0 ? act_pt : act_ee;
     c->step_act_cap[kind] = kind == 0 ? plan->act_pt : plan->act_ee;
@@ -1017,10 +1123,10 @@ eipc_status eipc_plan_step(eipc_ctx *c, const eipc_scene *sc, const double *q, c
   double *xs;
   EIPC_TRY(ensure_t(c, B_X, (size_t)n3v + 1, &xs));
   EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
-  int64_t npt = 0, nee = 0;
-  int32_t *pt = nullptr, *ee = nullptr;
-  EIPC_TRY(broad_phase(c, sc, 0, xs, nullptr, dhat, nullptr, 0, &npt, 0, s, B_STEP_PT, &pt));
-  EIPC_TRY(broad_phase(c, sc, 1, xs, nullptr, dhat, nullptr, 0, &nee, 0, s, B_STEP_EE, &ee));
+  BPReq req[2] = {{0, nullptr, 0, B_STEP_PT, 0}, {0, nullptr, 0, B_STEP_EE, 0}};
+  EIPC_TRY(broad_phase(c, sc, xs, nullptr, dhat, req, s));
+  const int64_t npt = req[0].n, nee = req[1].n;
+  const int32_t *pt = req[0].out, *ee = req[1].out;
   p.cand_pt = grow(npt);
   p.cand_ee = grow(nee);
   for (int k = 0; k < 2; ++k) {
@@ -1047,14 +1153,11 @@ eipc_status eipc_plan_step(eipc_ctx *c, const eipc_scene *sc, const double *q, c
     double *ps, *x1s;
     EIPC_TRY(ensure_t(c, B_P, (size_t)n3v + 1, &ps));
     EIPC_TRY(ensure_t(c, B_X1, (size_t)n3v + 1, &x1s));
-    EIPC_TRY(launch_embed(c, sc, dq, dx_off, ps, nullptr, s));
-    EIPC_TRY(launch_add_soa(c, n3v, xs, ps, x1s, s));
-    int64_t spt = 0, see = 0;
-    int32_t *cpt = nullptr, *cee = nullptr;
-    EIPC_TRY(broad_phase(c, sc, 0, xs, x1s, dhat, nullptr, 0, &spt, 0, s, B_CAND_PT, &cpt));
-    EIPC_TRY(broad_phase(c, sc, 1, xs, x1s, dhat, nullptr, 0, &see, 0, s, B_CAND_EE, &cee));
-    p.swept_pt = grow(spt);
-    p.swept_ee = grow(see);
+    EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
+    BPReq sreq[2] = {{0, nullptr, 0, B_CAND_PT, 0}, {0, nullptr, 0, B_CAND_EE, 0}};
+    EIPC_TRY(broad_phase(c, sc, xs, x1s, dhat, sreq, s));
+    p.swept_pt = grow(sreq[0].n);
+    p.swept_ee = grow(sreq[1].n);
     for (int k = 2; k < 4; ++k) {
       p.ent[k] = grow(c->last_plan[k].ent_cap);
       p.qent[k] = grow(c->last_plan[k].qent_cap);

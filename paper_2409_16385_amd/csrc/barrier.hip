@@ -779,6 +779,18 @@ __global__ void k_pair_scatter(const int32_t *__restrict__ act, const int32_t *_
   }
 }
 
+// the counters of sort_active, to be cleared before it runs
+eipc_status sort_clear(eipc_ctx *c, const eipc_scene *sc, int kind, FillList &fl) {
+  const int nn = std::max(sc->n_node, 1);
+  const size_t bytes = (sizeof(int32_t) * (nn + 1) + 7) & ~(size_t)7;
+  int32_t *hist, *fill;
+  EIPC_TRY(ensure_t(c, kind ? B_SHIST_EE : B_SHIST, (size_t)nn + 1, &hist));
+  EIPC_TRY(ensure_t(c, kind ? B_SFILL_EE : B_SFILL, (size_t)nn + 1, &fill));
+  fl.add(hist, bytes, 0);
+  fl.add(fill, bytes, 0);
+  return EIPC_OK;
+}
+
 static eipc_status sort_active(eipc_ctx *c, const eipc_scene *sc, int kind, const int32_t *pairs, const int32_t *act,
                                const int32_t *typ, const int64_t *d_count, int64_t cap, const int32_t **act2,
                                const int32_t **typ2, const int4 **vid2, hipStream_t s) {
@@ -796,8 +808,6 @@ static eipc_status sort_active(eipc_ctx *c, const eipc_scene *sc, int kind, cons
   EIPC_TRY(ensure_t(c, e ? B_STYP_EE : B_STYP, (size_t)cap, &t2));
   EIPC_TRY(ensure_t(c, e ? B_SVIDU_EE : B_SVIDU, (size_t)cap, &vu));
   EIPC_TRY(ensure_t(c, e ? B_SVID_EE : B_SVID, (size_t)cap, &v2));
-  EIPC_TRY(launch_zero(c, hist, sizeof(int32_t) * (nn + 1), s));
-  EIPC_TRY(launch_zero(c, fill, sizeof(int32_t) * (nn + 1), s));
   const int blocks = (int)std::min<int64_t>(grid_for(cap, 256), 8 * (int64_t)c->num_cu);
   if (kind == 0)
     k_pair_keys<0><<<blocks, 256, 0, s>>>(pairs, act, d_count, cap, sc->faces, sc->edges, sc->W_rowptr, sc->W_col,
@@ -1193,7 +1203,19 @@ __global__ void k_bsr_gather(int64_t cap, const int32_t *rowptr32, int n_node, c
   }
 }
 
-eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out, hipStream_t s, int64_t nnzb_cap) {
+// the row counters of bsr_compact, to be cleared before it runs
+eipc_status bsr_clear(eipc_ctx *c, int n_node, FillList &fl) {
+  const size_t bytes = (sizeof(int32_t) * ((size_t)n_node + 1) + 7) & ~(size_t)7;
+  int32_t *rowcnt, *rowfill;
+  EIPC_TRY(ensure_t(c, B_ROWCNT, (size_t)n_node + 1, &rowcnt));
+  EIPC_TRY(ensure_t(c, B_ROWFILL, (size_t)n_node + 1, &rowfill));
+  fl.add(rowcnt, bytes, 0);
+  fl.add(rowfill, bytes, 0);
+  return EIPC_OK;
+}
+
+eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out, hipStream_t s, int64_t nnzb_cap,
+                        uint32_t *status) {
   const int64_t cap = (int64_t)h.hmask + 1;
   int32_t *rowcnt, *rowfill, *bcol, *rowptr32;
   int64_t *rowptr, *bsrc;
@@ -1201,8 +1223,6 @@ eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out
   EIPC_TRY(ensure_t(c, B_ROWCNT, (size_t)n_node + 1, &rowcnt));
   EIPC_TRY(ensure_t(c, B_ROWFILL, (size_t)n_node + 1, &rowfill));
   EIPC_TRY(ensure_t(c, B_ROWPTR, (size_t)n_node + 1, &rowptr));
-  EIPC_TRY(launch_zero(c, rowcnt, sizeof(int32_t) * (n_node + 1), s));
-  EIPC_TRY(launch_zero(c, rowfill, sizeof(int32_t) * (n_node + 1), s));
   k_hash_rowcount<<<grid_for(cap, 256), 256, 0, s>>>(cap, h.hkey, n_node, rowcnt);
   EIPC_HIP(c, hipGetLastError());
   EIPC_TRY(exclusive_scan(c, rowcnt, n_node, rowptr, s));
@@ -1224,7 +1244,7 @@ eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out
   k_hash_rowfill<<<grid_for(cap, 256), 256, 0, s>>>(cap, h.hkey, n_node, rowptr, rowfill, bcol, bsrc, nnzb_cap);
   EIPC_HIP(c, hipGetLastError());
   k_row_sort<<<grid_for((int64_t)(n_node + 1) * 64, 256), 256, 0, s>>>(n_node, rowptr, bcol, bsrc, bcol2, bsrc2,
-                                                                        rowptr32, nnzb_cap, c->status);
+                                                                        rowptr32, nnzb_cap, status);
   EIPC_HIP(c, hipGetLastError());
   if (nnzb_cap > 0) {
     k_bsr_gather<<<std::min(grid_for(nnzb_cap, 256), 16 * c->num_cu), 256, 0, s>>>(nnzb_cap, rowptr32, n_node, bsrc2,

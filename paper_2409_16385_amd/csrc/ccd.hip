@@ -217,6 +217,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == 0 ?
   __shared__ int s_nact;
   __shared__ int64_t s_abase;
   const int64_t n = *d_n < cap ? *d_n : cap;
+  if (*d_n > cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(status, ST_PLAN_OVERFLOW);
   const int lane = threadIdx.x & 63;
   bool capped = false;
   int64_t n_cand = 0;
@@ -346,7 +347,6 @@ eipc_status launch_narrow_ccd(eipc_ctx *c, const eipc_scene *sc, int kind, const
   int64_t *n_long = c->counters + 9 + kind;
   int32_t *longl;
   EIPC_TRY(ensure_t(c, kind == 0 ? B_CCD_LONG_PT : B_CCD_LONG_EE, (size_t)n, &longl));
-  EIPC_TRY(launch_zero(c, n_long, 8, s));
   unsigned long long *ab = (unsigned long long *)d_alpha_bits;
   const double d2 = dhat * dhat, h = 0.5 * dhat;
   {
@@ -398,7 +398,6 @@ eipc_status launch_ccd(eipc_ctx *c, const eipc_scene *sc, int kind, const double
     int64_t *n_long = c->counters + 9 + kind;
     int32_t *longl;
     EIPC_TRY(ensure_t(c, kind == 0 ? B_CCD_LONG_PT : B_CCD_LONG_EE, (size_t)n, &longl));
-    EIPC_TRY(launch_zero(c, n_long, 8, s));
     unsigned long long *ab = (unsigned long long *)d_alpha_bits;
     if (kind == 0) {
       k_ccd2<0, 0><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,

@@ -6,6 +6,7 @@
 
 #include <cstdarg>
 #include <cstdio>
+#include <functional>
 #include <vector>
 
 #include "eipc.h"
@@ -44,7 +45,8 @@ enum BufId {
   B_SVIDU, B_SVID,                                   // their vertex ids (unsorted, sorted)
   B_SKEY_EE, B_SHIST_EE, B_SFILL_EE, B_SSTART_EE, B_SACT_EE, B_STYP_EE, B_SVIDU_EE, B_SVID_EE,  // the same for EE
   B_CCD_LONG_PT, B_CCD_LONG_EE,                        // CCD pairs deferred to the second pass
-  B_LQTMP,                                             // unsorted candidates of large queries (sorted lists)
+  B_LQTMP,                                             // items per first index, unsorted (sorted lists)
+  B_SORT_LIST, B_SORT_SLOT, B_SORT_CNT_PT, B_SORT_CNT_EE,  // sorted lists: the appended list, slots, counts
   B_BP0,                               // broad-phase scratch: 4 slots (kind, swept) x BP_NBUF
   B_NUM = B_BP0 + 4 * 17
 };
@@ -127,6 +129,12 @@ struct eipc_ctx {
   // (the default: the fastest on every workload measured, small to batch)
   int query_mode[2] = {3, 3};
   eipc::BPPlan last_plan[4] = {};   // sizes seen by the last unplanned broad phases
+  eipc::BPPlan bp_guess[4] = {};    // capacities an unplanned broad phase starts from (0: from the scene)
+  int64_t nnzb_guess = 0;           // the same for the BSR blocks of a per-call reduction
+  // pinned words the device writes results to that the host waits for
+  // (launch_collect), and where the caller's words start after a broad phase's
+  int64_t *host_res = nullptr;
+  int collect_base = 0;
   bool prof = false;                        // record per-kernel events
   bool prof_serial = false;                 // planned step: both chains on the caller's stream
   std::vector<eipc::ProfRec> prof_pending;  // recorded, not yet read
@@ -227,21 +235,106 @@ inline int grid_for(int64_t n, int threads) {
 }
 
 // ---- geometry.hip ----
+struct ItemRec;
+struct Entry;
+struct QEntry;
+struct GridDev;
+// Scratch of one broad phase (kind, swept) kept in the context's buffers.
+struct BPScratch {
+  ItemRec *items;
+  int32_t *cnt, *large, *bcnt, *vbcnt, *qcnt, *qlarge;
+  int64_t *bstart, *qoff, *n_large, *n_qlarge;
+  Entry *ent;
+  QEntry *qent;
+  int32_t *big, *qbig;
+  int64_t *n_big, *n_qbig;  // {records, cells}
+  int64_t *n_ent;           // entries of the small records, per side
+  ItemRec *vrec;            // bucket join, PT: vertex records
+  int64_t *vbstart;         // bucket join, PT: vertex-hash bucket offsets
+  GridDev *g;
+  uint64_t *st;
+  unsigned long long *total;
+  uint32_t *flag;           // overflows of an unplanned pass (its counts tell which)
+};
+
+// One broad phase being set up: its inputs, sizes and scratch.
+struct BPRun {
+  const eipc_scene *sc;
+  int kind, slot, nq, ni;
+  const double *xs, *x1s;
+  double h;
+  uint32_t nb;                // hash buckets
+  int64_t ent_cap, qent_cap;  // item entries, query entries
+  bool vhash;                 // the query vertices are hashed too (PT join)
+  BPScratch b;
+  const int32_t *vscene() const { return sc->n_scene > 1 ? sc->vert_scene : nullptr; }
+};
 eipc_status launch_embed(eipc_ctx *c, const eipc_scene *sc, const double *q, const double *off, double *xs,
                          double *x_aos, hipStream_t s);
-eipc_status launch_add_soa(eipc_ctx *c, int64_t n, const double *a, const double *b, double *out, hipStream_t s);
 eipc_status exclusive_scan(eipc_ctx *c, const int32_t *in, int64_t n, int64_t *out, hipStream_t s);
 eipc_status launch_zero(eipc_ctx *c, void *p, size_t bytes, hipStream_t s);
-// Candidate pairs of one kind; swept when x1s != nullptr.  Unplanned
-// (plan == nullptr): synchronizes, writes the required count to *n_out and
-// the pairs when they fit (sorted per query when sort != 0), growing buffer
-// grow_id when given.  Planned: no synchronization and no allocation beyond
-// the plan's sizes; the count goes to device *d_total and an overflow
-// raises ST_PLAN_OVERFLOW.
-eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *x1s,
-                        double dhat, int32_t *out, int64_t cap, int64_t *n_out, int sort, hipStream_t s,
-                        int grow_id = -1, int32_t **grown = nullptr, const BPPlan *plan = nullptr,
-                        int64_t *d_total = nullptr);
+// x, p = W dq + dx_off and (x1s given) x + p in one pass
+eipc_status launch_embed_swept(eipc_ctx *c, const eipc_scene *sc, const double *q, const double *dq,
+                               const double *dx_off, double *xs, double *ps, double *x1s, hipStream_t s);
+// two scans side by side (in1 may be null)
+eipc_status exclusive_scan2(eipc_ctx *c, const int32_t *in0, int64_t n0, int64_t *out0, const int32_t *in1,
+                            int64_t n1, int64_t *out1, hipStream_t s);
+
+// Buffers to set to a 64-bit value, all in one launch (bytes a multiple of
+// 8; scratch buffers have room past their end for rounding up).
+struct FillSeg {
+  uint64_t *p;
+  int64_t n;
+  uint64_t v;
+  int blocks;
+};
+struct FillList {
+  FillSeg seg[24];
+  int n = 0;
+  void add(void *p, size_t bytes, uint64_t v) {
+    if (p && bytes) seg[n++] = FillSeg{(uint64_t *)p, (int64_t)(bytes / 8), v, 0};
+  }
+};
+eipc_status launch_fill(eipc_ctx *c, FillList &l, hipStream_t s);
+
+// Device words (4 or 8 bytes) for the host: launch_collect writes them to
+// ctx->host_res in order; the caller synchronizes and reads.
+struct Collect {
+  const void *p[32];
+  int bytes[32];
+  int n = 0;
+  int add(const void *q, int b) {
+    p[n] = q;
+    bytes[n] = b;
+    return n++;
+  }
+};
+eipc_status launch_collect(eipc_ctx *c, const Collect &col, hipStream_t s);
+
+// One kind's request to an unplanned broad phase.
+struct BPReq {
+  int sort;           // sorted by (first, second) into out (cap pairs); else unsorted into buffer grow_id
+  int32_t *out;       // sorted: the caller's list; unsorted: receives the list
+  int64_t cap;
+  int grow_id;
+  int64_t n;          // receives the number of pairs
+};
+// enqueues what follows on the lists (capacities, device counts: null when
+// the capacity is the count) and adds the words it wants read back
+using BPAfter = std::function<eipc_status(const int32_t *const *, const int64_t *, const int64_t *const *, Collect &)>;
+// Candidate pairs of both kinds; swept when x1s != nullptr.  Synchronizes.
+// EIPC_ERR_CAPACITY (counts set, nothing written) when a sorted list does
+// not fit.
+eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, const double *xs, const double *x1s, double dhat,
+                        BPReq req[2], hipStream_t s, const BPAfter &after = nullptr);
+// Planned: no synchronization and no allocation beyond the plan's sizes.
+// begin takes the scratch and adds what has to be cleared; run appends the
+// pairs (unsorted) and their count to *d_total, cleared by the caller.  The
+// count may pass the capacity: the consumers clamp it and raise
+// ST_PLAN_OVERFLOW.
+eipc_status bp_planned_begin(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *x1s,
+                             double dhat, const BPPlan &plan, BPRun &r, FillList &fl);
+eipc_status bp_planned_run(eipc_ctx *c, BPRun &r, int32_t *out, int64_t cap, int64_t *d_total, hipStream_t s);
 // Active subset of `n` pairs (at most `n`; min(n, *d_n) when d_n is given)
 // into act/typ of capacity act_cap (< 0: n).  With cand_count, the pairs
 // are swept candidates filtered by the candidate predicate at xs first and
@@ -278,8 +371,13 @@ eipc_status launch_expand(eipc_ctx *c, const eipc_scene *sc, int kind, const int
 // BSR view of the hashed blocks.  nnzb_cap < 0: sized on the host
 // (synchronizes); else fixed capacity, the count only on the device
 // (rowptr[n_node]) and out->nnzb = -1.
-eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out, hipStream_t s,
-                        int64_t nnzb_cap = -1);
+// status: takes ST_PLAN_OVERFLOW when the blocks pass the capacity.
+eipc_status bsr_compact(eipc_ctx *c, int n_node, const HessOut &h, eipc_bsr *out, hipStream_t s, int64_t nnzb_cap,
+                        uint32_t *status);
+// scratch counters to clear before launch_barrier / launch_hvp (per kind)
+// and before bsr_compact
+eipc_status sort_clear(eipc_ctx *c, const eipc_scene *sc, int kind, FillList &fl);
+eipc_status bsr_clear(eipc_ctx *c, int n_node, FillList &fl);
 eipc_status launch_hvp(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *xvs,
                        const int32_t *pairs, const int32_t *act, const int32_t *typ, const int64_t *d_count,
                        int64_t max_count, double dhat, double kappa, uint32_t flags, double *out,

@@ -59,15 +59,59 @@ eipc_status launch_embed(eipc_ctx *c, const eipc_scene *sc, const double *q, con
   return EIPC_OK;
 }
 
-__global__ void k_add(int64_t n, const double *a, const double *b, double *out) {
+// x = W q + off, p = W dq + dx_off and the end positions x1 = x + p (one
+// rounded add) in one pass over the rows of W (three launches and two reads
+// of W otherwise); the sums are k_embed's.
+__global__ void k_embed_swept(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                              const double *__restrict__ val, const double *__restrict__ q,
+                              const double *__restrict__ off, const double *__restrict__ dq,
+                              const double *__restrict__ dx_off, double *__restrict__ xs, double *__restrict__ ps,
+                              double *__restrict__ x1s, const int32_t *__restrict__ vscene, int n_scene,
+                              uint32_t *status) {
 #pragma clang fp contract(off)
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = a[i] + b[i];
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= n) return;
+  double a[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
+  const int k0 = rowptr[v], k1 = rowptr[v + 1];
+  if (k1 - k0 > 4 || k1 < k0) atomicOr(status, ST_BAD_W);
+  if (vscene && (unsigned)vscene[v] >= (unsigned)n_scene) atomicOr(status, ST_BAD_SCENE);
+  for (int k = k0; k < k1; ++k) {
+    const double w = val[k];
+    const int64_t c = 3 * (int64_t)col[k];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      a[i] = a[i] + w * q[c + i];
+      b[i] = b[i] + w * dq[c + i];
+    }
+  }
+  bool fin = true;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (off) a[i] = a[i] + off[3 * (int64_t)v + i];
+    if (dx_off) b[i] = b[i] + dx_off[3 * (int64_t)v + i];
+    fin = fin && isfinite(a[i]) && isfinite(b[i]);
+  }
+  double2 *r = reinterpret_cast<double2 *>(xs + (int64_t)PSTRIDE * v);
+  r[0] = double2{a[0], a[1]};
+  r[1] = double2{a[2], 0.0};
+  r = reinterpret_cast<double2 *>(ps + (int64_t)PSTRIDE * v);
+  r[0] = double2{b[0], b[1]};
+  r[1] = double2{b[2], 0.0};
+  if (x1s) {
+    r = reinterpret_cast<double2 *>(x1s + (int64_t)PSTRIDE * v);
+    r[0] = double2{a[0] + b[0], a[1] + b[1]};
+    r[1] = double2{a[2] + b[2], 0.0};
+  }
+  if (!fin) atomicOr(status, ST_NONFINITE);
 }
 
-eipc_status launch_add_soa(eipc_ctx *c, int64_t n, const double *a, const double *b, double *out, hipStream_t s) {
-  if (n == 0) return EIPC_OK;
-  k_add<<<grid_for(n, 256), 256, 0, s>>>(n, a, b, out);
+eipc_status launch_embed_swept(eipc_ctx *c, const eipc_scene *sc, const double *q, const double *dq,
+                               const double *dx_off, double *xs, double *ps, double *x1s, hipStream_t s) {
+  if (sc->n_vert == 0) return EIPC_OK;
+  ProfScope prof(c, K_EMBED, s);
+  k_embed_swept<<<grid_for(sc->n_vert, 256), 256, 0, s>>>(sc->n_vert, sc->W_rowptr, sc->W_col, sc->W_val, q,
+                                                           sc->x_off, dq, dx_off, xs, ps, x1s, vscene_of(sc),
+                                                           n_scene_of(sc), c->status);
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
@@ -99,6 +143,34 @@ eipc_status launch_zero(eipc_ctx *c, void *p, size_t bytes, hipStream_t s) {
     k_zero_bytes<<<grid_for((int64_t)bytes, 256), 256, 0, s>>>((uint8_t *)p, (int64_t)bytes);
     EIPC_HIP(c, hipGetLastError());
   }
+  return EIPC_OK;
+}
+
+// Every buffer that a call clears, in one launch: a launch of its own each
+// costs about 4 us, which small scenes feel.
+constexpr int FILL_WORDS = 2048;  // 8-byte words per workgroup and round
+__global__ __launch_bounds__(256) void k_fill_list(FillList l) {
+  int b = blockIdx.x, k = 0;
+  while (k + 1 < l.n && b >= l.seg[k].blocks) b -= l.seg[k++].blocks;
+  const FillSeg g = l.seg[k];
+  for (int64_t base = (int64_t)b * FILL_WORDS; base < g.n; base += (int64_t)g.blocks * FILL_WORDS)
+#pragma unroll
+    for (int u = 0; u < FILL_WORDS / 256; ++u) {
+      const int64_t i = base + u * 256 + threadIdx.x;
+      if (i < g.n) g.p[i] = g.v;
+    }
+}
+
+eipc_status launch_fill(eipc_ctx *c, FillList &l, hipStream_t s) {
+  if (l.n == 0) return EIPC_OK;
+  int64_t blocks = 0;
+  for (int k = 0; k < l.n; ++k) {
+    l.seg[k].blocks = (int)std::min<int64_t>((l.seg[k].n + FILL_WORDS - 1) / FILL_WORDS, 2048);
+    blocks += l.seg[k].blocks;
+  }
+  k_fill_list<<<(unsigned)blocks, 256, 0, s>>>(l);
+  EIPC_HIP(c, hipGetLastError());
+  l.n = 0;
   return EIPC_OK;
 }
 
@@ -135,72 +207,116 @@ __device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t *smem, int
   return r;
 }
 
-__global__ void k_scan_partial(const int32_t *in, int64_t n, int64_t *bsum) {
-  __shared__ int64_t sm[17];
-  int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_E;
-  int64_t acc = 0;
-#pragma unroll
-  for (int e = 0; e < SCAN_E; ++e)
-    if (base + e < n) acc += in[base + e];
-  int64_t tot;
-  block_excl_scan(acc, sm, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
+// Up to two scans side by side (grid y).  Arrays of up to SCAN_ONE entries:
+// one launch, one workgroup each.  Larger ones: two launches over at most
+// SCAN_BLOCKS ranges; the second sums the ranges before its own itself (at
+// most four loads a thread), so no launch between them scans the sums.
+constexpr int64_t SCAN_ONE = 32768;
+constexpr int SCAN_BLOCKS = 1024;
+struct ScanArgs {
+  const int32_t *in[2];
+  int64_t n[2];
+  int64_t *out[2];
+  int64_t *bsum[2];
+};
 
-__global__ void k_scan_top(int64_t *bsum, int64_t nb) {
+__global__ __launch_bounds__(1024) void k_scan_one(ScanArgs a) {
   __shared__ int64_t sm[17];
+  const int32_t *in = a.in[blockIdx.y];
+  const int64_t n = a.n[blockIdx.y];
+  int64_t *out = a.out[blockIdx.y];
   int64_t carry = 0;
-  for (int64_t base = 0; base < nb; base += blockDim.x) {
-    int64_t i = base + threadIdx.x;
-    int64_t v = i < nb ? bsum[i] : 0;
-    int64_t tot;
-    int64_t ex = block_excl_scan(v, sm, &tot);
-    if (i < nb) bsum[i] = ex + carry;
+  for (int64_t b0 = 0; b0 < n; b0 += 1024 * SCAN_E) {
+    const int64_t base = b0 + threadIdx.x * SCAN_E;
+    int32_t v[SCAN_E];
+    int64_t acc = 0, tot;
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      v[e] = base + e < n ? in[base + e] : 0;
+      acc += v[e];
+    }
+    int64_t ex = carry + block_excl_scan(acc, sm, &tot);
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      if (base + e < n) out[base + e] = ex;
+      ex += v[e];
+    }
     carry += tot;
   }
-  if (threadIdx.x == 0) bsum[nb] = carry;
+  if (threadIdx.x == 0) out[n] = carry;
 }
 
-__global__ void k_scan_final(const int32_t *in, int64_t n, const int64_t *bsum, int64_t nb, int64_t *out) {
+// tiles of a workgroup's range: consecutive, the same number for each
+__device__ __forceinline__ int64_t scan_range(int64_t n, int64_t nb) {
+  return ((n + SCAN_TILE - 1) / SCAN_TILE + nb - 1) / nb * SCAN_TILE;
+}
+
+__global__ __launch_bounds__(SCAN_T) void k_scan_partial(ScanArgs a) {
   __shared__ int64_t sm[17];
-  int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_E;
-  int64_t vals[SCAN_E];
+  const int32_t *in = a.in[blockIdx.y];
+  const int64_t n = a.n[blockIdx.y], per = scan_range(n, gridDim.x);
+  const int64_t r0 = blockIdx.x * per, r1 = r0 + per < n ? r0 + per : n;
   int64_t acc = 0;
-#pragma unroll
-  for (int e = 0; e < SCAN_E; ++e) {
-    vals[e] = (base + e < n) ? in[base + e] : 0;
-    acc += vals[e];
-  }
+  for (int64_t i = r0 + threadIdx.x; i < r1; i += SCAN_T) acc += in[i];
   int64_t tot;
-  int64_t ex = block_excl_scan(acc, sm, &tot) + bsum[blockIdx.x];
-#pragma unroll
-  for (int e = 0; e < SCAN_E; ++e) {
-    if (base + e < n) out[base + e] = ex;
-    ex += vals[e];
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = bsum[nb];
+  block_excl_scan(acc, sm, &tot);
+  if (threadIdx.x == 0) a.bsum[blockIdx.y][blockIdx.x] = tot;
 }
 
-eipc_status exclusive_scan(eipc_ctx *c, const int32_t *in, int64_t n, int64_t *out, hipStream_t s) {
-  int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-  if (nb < 1) nb = 1;
+__global__ __launch_bounds__(SCAN_T) void k_scan_final(ScanArgs a) {
+  __shared__ int64_t sm[17];
+  const int32_t *in = a.in[blockIdx.y];
+  int64_t *out = a.out[blockIdx.y];
+  const int64_t *bsum = a.bsum[blockIdx.y];
+  const int64_t n = a.n[blockIdx.y], per = scan_range(n, gridDim.x);
+  const int64_t r0 = blockIdx.x * per, r1 = r0 + per < n ? r0 + per : n;
+  int64_t before = 0, carry, tot;
+  for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += SCAN_T) before += bsum[k];
+  block_excl_scan(before, sm, &carry);
+  for (int64_t b0 = r0; b0 < r1; b0 += SCAN_TILE) {
+    const int64_t base = b0 + threadIdx.x * SCAN_E;
+    int32_t v[SCAN_E];
+    int64_t acc = 0;
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      v[e] = base + e < n ? in[base + e] : 0;
+      acc += v[e];
+    }
+    int64_t ex = carry + block_excl_scan(acc, sm, &tot);
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      if (base + e < n) out[base + e] = ex;
+      ex += v[e];
+    }
+    carry += tot;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = carry;
+}
+
+eipc_status exclusive_scan2(eipc_ctx *c, const int32_t *in0, int64_t n0, int64_t *out0, const int32_t *in1,
+                            int64_t n1, int64_t *out1, hipStream_t s) {
+  const int ny = in1 ? 2 : 1;
+  ScanArgs a{{in0, in1}, {n0, n1}, {out0, out1}, {nullptr, nullptr}};
+  const int64_t n = std::max(n0, in1 ? n1 : 0);
+  if (n <= SCAN_ONE) {
+    k_scan_one<<<dim3(1, ny), 1024, 0, s>>>(a);
+    EIPC_HIP(c, hipGetLastError());
+    return EIPC_OK;
+  }
+  const int64_t nb = std::min<int64_t>((n + SCAN_TILE - 1) / SCAN_TILE, SCAN_BLOCKS);
   int64_t *bsum;
-  EIPC_TRY(ensure_t(c, s == c->side ? B_SCANTMP_SIDE : B_SCANTMP, (size_t)nb + 1, &bsum));
-  k_scan_partial<<<(unsigned)nb, SCAN_T, 0, s>>>(in, n, bsum);
+  EIPC_TRY(ensure_t(c, s == c->side ? B_SCANTMP_SIDE : B_SCANTMP, (size_t)(ny * nb), &bsum));
+  a.bsum[0] = bsum;
+  a.bsum[1] = bsum + nb;
+  k_scan_partial<<<dim3((unsigned)nb, ny), SCAN_T, 0, s>>>(a);
   EIPC_HIP(c, hipGetLastError());
-  k_scan_top<<<1, 1024, 0, s>>>(bsum, nb);
-  EIPC_HIP(c, hipGetLastError());
-  k_scan_final<<<(unsigned)nb, SCAN_T, 0, s>>>(in, n, bsum, nb, out);
+  k_scan_final<<<dim3((unsigned)nb, ny), SCAN_T, 0, s>>>(a);
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
 
-// device-side candidate count for the next stage, clamped to the capacity
-// (an overflow is raised for the caller to re-plan)
-__global__ void k_copy_count(const int64_t *src, int64_t *dst, int64_t cap, uint32_t *status) {
-  const int64_t v = *src;
-  if (v > cap) atomicOr(status, ST_PLAN_OVERFLOW);
-  *dst = v < cap ? v : cap;
+eipc_status exclusive_scan(eipc_ctx *c, const int32_t *in, int64_t n, int64_t *out, hipStream_t s) {
+  return exclusive_scan2(c, in, n, out, nullptr, 0, nullptr, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -243,27 +359,6 @@ __device__ __forceinline__ void prim_box(const int *vid, const double *xs, const
   }
 }
 
-template <int NV>
-__global__ void k_items(int n, const int32_t *__restrict__ idx, const double *__restrict__ xs,
-                        const double *__restrict__ x1s, int n_vert, double h, const int32_t *__restrict__ rowptr,
-                        const int32_t *__restrict__ vscene, ItemRec *__restrict__ rec) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int vid[NV];
-#pragma unroll
-  for (int a = 0; a < NV; ++a) vid[a] = idx[(int64_t)NV * i + a];
-  ItemRec r;
-  prim_box<NV>(vid, xs, x1s, n_vert, h, r.lo, r.hi);
-  int dof = 0;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    r.v[a] = a < NV ? vid[a] : -1;
-    if (a < NV) dof |= has_dof(rowptr, vid[a]);
-  }
-  r.tag = dof | (scene_of(vscene, vid[0]) << 1);
-  rec[i] = r;
-}
-
 __device__ __forceinline__ uint64_t ord_key(double v) {
   uint64_t b = __double_as_longlong(v);
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
@@ -273,33 +368,64 @@ __device__ __forceinline__ double ord_dec(uint64_t k) {
   return __longlong_as_double(b);
 }
 
-// stats (uint64 view): [0..2] min lo (ordered), [3..5] max hi (ordered);
-// double view [6..8] sum of item extents.  Items from records, or vertex
-// (point) boxes when rec == nullptr.  Grid-stride, reduced per workgroup,
-// one atomic per workgroup and value.
-constexpr int STAT_T = 256;
-__global__ __launch_bounds__(STAT_T) void k_box_stats(int n, const ItemRec *__restrict__ rec,
-                                                      const double *__restrict__ xs, const double *__restrict__ x1s,
-                                                      int n_vert, double h, uint64_t *st, int with_ext) {
+// Box records of the items (KIND 0: faces, 1: edges) and, for KIND 0, of the
+// vertices (kept when vrec is given), with the statistics of the grid in the
+// same pass: the first gi workgroups take the items, the others the
+// vertices.  Statistics, STAT_COPIES copies of nine words, all starting from
+// zero: [0..2] max of the complemented order key of lo (its min), [3..5] max
+// of the key of hi, [6..8] sum of the item extents.  Workgroups end with nine
+// atomics; their number is bounded and the copies keep the queue on a word
+// to a few hundred (the statistics alone took 25 us of a config 2 chain when
+// they read the records back in a launch of their own).
+constexpr int STAT_T = 256, STAT_COPIES = 4, STAT_BLOCKS = 1024;
+template <int KIND>
+__global__ __launch_bounds__(STAT_T) void k_items(int n, const int32_t *__restrict__ idx, int n_vert,
+                                                  const double *__restrict__ xs, const double *__restrict__ x1s,
+                                                  double h, const int32_t *__restrict__ rowptr,
+                                                  const int32_t *__restrict__ vscene, ItemRec *__restrict__ rec,
+                                                  ItemRec *__restrict__ vrec, int gi, uint64_t *st) {
+  constexpr int NV = KIND == 0 ? 3 : 2;
   __shared__ double s_red[STAT_T / 64][9];
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, ex[3] = {0, 0, 0};
-  for (int i = blockIdx.x * STAT_T + threadIdx.x; i < n; i += gridDim.x * STAT_T) {
-    double l[3], u[3];
-    if (rec) {
+  if ((int)blockIdx.x < gi) {
+    for (int i = blockIdx.x * STAT_T + threadIdx.x; i < n; i += gi * STAT_T) {
+      int vid[NV];
+#pragma unroll
+      for (int a = 0; a < NV; ++a) vid[a] = idx[(int64_t)NV * i + a];
+      ItemRec r;
+      prim_box<NV>(vid, xs, x1s, n_vert, h, r.lo, r.hi);
+      int dof = 0;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        l[a] = rec[i].lo[a];
-        u[a] = rec[i].hi[a];
+        r.v[a] = a < NV ? vid[a < NV ? a : 0] : -1;
+        if (a < NV) dof |= has_dof(rowptr, vid[a < NV ? a : 0]);
       }
-    } else {
-      int v = i;
-      prim_box<1>(&v, xs, x1s, n_vert, h, l, u);
-    }
+      r.tag = dof | (scene_of(vscene, vid[0]) << 1);
+      rec[i] = r;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = fmin(lo[a], l[a]);
-      hi[a] = fmax(hi[a], u[a]);
-      ex[a] += u[a] - l[a];
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = fmin(lo[a], r.lo[a]);
+        hi[a] = fmax(hi[a], r.hi[a]);
+        ex[a] += r.hi[a] - r.lo[a];
+      }
+    }
+  } else {
+    const int gv = gridDim.x - gi;
+    for (int i = ((int)blockIdx.x - gi) * STAT_T + threadIdx.x; i < n_vert; i += gv * STAT_T) {
+      ItemRec r;
+      prim_box<1>(&i, xs, x1s, n_vert, h, r.lo, r.hi);
+      if (vrec) {
+        r.v[0] = i;
+        r.v[1] = -1;
+        r.v[2] = -1;
+        r.tag = (int)has_dof(rowptr, i) | (scene_of(vscene, i) << 1);
+        vrec[i] = r;
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = fmin(lo[a], r.lo[a]);
+        hi[a] = fmax(hi[a], r.hi[a]);
+      }
     }
   }
 #pragma unroll
@@ -320,33 +446,18 @@ __global__ __launch_bounds__(STAT_T) void k_box_stats(int n, const ItemRec *__re
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < STAT_T / 64; ++k)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        lo[a] = fmin(lo[a], s_red[k][a]);
-        hi[a] = fmax(hi[a], s_red[k][3 + a]);
-        ex[a] += s_red[k][6 + a];
-      }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      atomicMin((unsigned long long *)&st[a], (unsigned long long)ord_key(lo[a]));
-      atomicMax((unsigned long long *)&st[3 + a], (unsigned long long)ord_key(hi[a]));
-      if (with_ext) atomicAdd((double *)&st[6 + a], ex[a]);
-    }
-  }
-}
-
-// a bounded number of workgroups: each ends with 9 atomics on the same 9
-// words, and too few leave each thread hundreds of items on large batches
-static int stat_blocks(int n) { return std::max(1, std::min(grid_for(n, STAT_T), 256)); }
-
-__global__ void k_stats_init(uint64_t *st) {
-  int t = threadIdx.x;
-  if (t < 3) {
-    st[t] = ~0ull;
-    st[3 + t] = 0ull;
-    ((double *)st)[6 + t] = 0.0;
+  if (threadIdx.x < 9) {
+    // one lane per statistic
+    const int t = threadIdx.x;
+    double v = s_red[0][t];
+    for (int k = 1; k < STAT_T / 64; ++k) v = t < 3 ? fmin(v, s_red[k][t]) : (t < 6 ? fmax(v, s_red[k][t]) : v + s_red[k][t]);
+    uint64_t *p = st + 9 * (blockIdx.x % STAT_COPIES) + t;
+    if (t < 3)
+      atomicMax((unsigned long long *)p, (unsigned long long)~ord_key(v));
+    else if (t < 6)
+      atomicMax((unsigned long long *)p, (unsigned long long)ord_key(v));
+    else if (v != 0.0)
+      atomicAdd((double *)p, v);
   }
 }
 
@@ -364,43 +475,64 @@ constexpr int GRID_AXIS_MAX = 1 << 16;
 // cell edge: cell_scale times the mean item box extent (largest axis of the
 // mean), at least 1e-6 of the scene span, grown until every axis has at
 // most 2^16 cells
-__global__ void k_grid_params(const uint64_t *st, int n_items, double cell_scale, GridDev *g, uint32_t *status) {
-  if (threadIdx.x != 0) return;
-  double lo[3], hi[3], ext[3];
-  bool ok = true;
-  for (int a = 0; a < 3; ++a) {
-    lo[a] = ord_dec(st[a]);
-    hi[a] = ord_dec(st[3 + a]);
-    ext[a] = ((const double *)st)[6 + a];
-    ok = ok && isfinite(lo[a]) && isfinite(hi[a]);
-  }
-  GridDev r;
-  r.bad = ok ? 0 : 1;
-  if (!ok) {
-    atomicOr(status, ST_NONFINITE);
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = 0.0;
-      hi[a] = 0.0;
+// (from the statistics, by every workgroup that needs them first: nine lanes
+// fold the copies, one forms the grid)
+__device__ __forceinline__ void grid_params(const uint64_t *st, int n_items, double cell_scale, GridDev *g,
+                                            double *s_stat) {
+  if (threadIdx.x < 9) {
+    const int t = threadIdx.x;
+    uint64_t w[STAT_COPIES];
+#pragma unroll
+    for (int k = 0; k < STAT_COPIES; ++k) w[k] = st[9 * k + t];
+    if (t < 6) {
+      uint64_t m = w[0];
+#pragma unroll
+      for (int k = 1; k < STAT_COPIES; ++k) m = m > w[k] ? m : w[k];
+      s_stat[t] = ord_dec(t < 3 ? ~m : m);
+    } else {
+      double e = 0.0;
+#pragma unroll
+      for (int k = 0; k < STAT_COPIES; ++k) e += __longlong_as_double(w[k]);
+      s_stat[t] = e;
     }
   }
-  double cell = cell_scale * fmax(ext[0], fmax(ext[1], ext[2])) / (double)(n_items > 0 ? n_items : 1);
-  double span = fmax(hi[0] - lo[0], fmax(hi[1] - lo[1], hi[2] - lo[2]));
-  cell = fmax(cell, span * 1e-6);
-  if (!(cell > 0.0) || !isfinite(cell)) cell = 1.0;
-  for (int it = 0; it < 64; ++it) {
-    bool fits = true;
-    for (int a = 0; a < 3; ++a)
-      if (floor((hi[a] - lo[a]) / cell) + 1.0 > (double)GRID_AXIS_MAX) fits = false;
-    if (fits) break;
-    cell *= 2.0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double lo[3], hi[3], ext[3];
+    bool ok = true;
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = s_stat[a];
+      hi[a] = s_stat[3 + a];
+      ext[a] = s_stat[6 + a];
+      ok = ok && isfinite(lo[a]) && isfinite(hi[a]);
+    }
+    GridDev r;
+    r.bad = ok ? 0 : 1;
+    if (!ok)
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = 0.0;
+        hi[a] = 0.0;
+      }
+    double cell = cell_scale * fmax(ext[0], fmax(ext[1], ext[2])) / (double)(n_items > 0 ? n_items : 1);
+    double span = fmax(hi[0] - lo[0], fmax(hi[1] - lo[1], hi[2] - lo[2]));
+    cell = fmax(cell, span * 1e-6);
+    if (!(cell > 0.0) || !isfinite(cell)) cell = 1.0;
+    for (int it = 0; it < 64; ++it) {
+      bool fits = true;
+      for (int a = 0; a < 3; ++a)
+        if (floor((hi[a] - lo[a]) / cell) + 1.0 > (double)GRID_AXIS_MAX) fits = false;
+      if (fits) break;
+      cell *= 2.0;
+    }
+    for (int a = 0; a < 3; ++a) {
+      r.o[a] = lo[a];
+      double d = floor((hi[a] - lo[a]) / cell) + 1.0;
+      r.dim[a] = (int)fmin(d, (double)GRID_AXIS_MAX);
+    }
+    r.inv_h = 1.0 / cell;
+    *g = r;
   }
-  for (int a = 0; a < 3; ++a) {
-    r.o[a] = lo[a];
-    double d = floor((hi[a] - lo[a]) / cell) + 1.0;
-    r.dim[a] = (int)fmin(d, (double)GRID_AXIS_MAX);
-  }
-  r.inv_h = 1.0 / cell;
-  *g = r;
+  __syncthreads();
 }
 
 __device__ __forceinline__ int cell_of(double v, double o, double inv_h, int dim) {
@@ -424,62 +556,12 @@ __device__ __forceinline__ void cell_range(const GridDev &g, const double *lo, c
   }
 }
 
-// Items covering up to MAX_ITEM_CELLS cells are hashed one thread per
-// item; larger ones with at most 64 cells per axis (the reach of the 6-bit
-// offsets of an entry) and at most BIG_CELLS cells are hashed one wavefront
-// per item (the big list, n_big = {items, cells}); the rest (the large
-// list) are tested against every query instead.
-__global__ void k_item_cells(int n, const ItemRec *__restrict__ rec, const GridDev *__restrict__ gp, int32_t *cnt,
-                             int32_t *large, int64_t *n_large, int32_t *big, int64_t *n_big) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const GridDev g = *gp;
-  int c0[3], c1[3];
-  cell_range(g, rec[i].lo, rec[i].hi, c0, c1);
-  const int sx = c1[0] - c0[0] + 1, sy = c1[1] - c0[1] + 1, sz = c1[2] - c0[2] + 1;
-  const int64_t nc = (int64_t)sx * sy * sz;
-  if (nc <= MAX_ITEM_CELLS) {
-    cnt[i] = (int32_t)nc;
-    return;
-  }
-  cnt[i] = 0;
-  if (sx <= 64 && sy <= 64 && sz <= 64 && nc <= BIG_CELLS) {
-    const int slot = (int)atomicAdd((unsigned long long *)&n_big[0], 1ull);
-    big[slot] = i;
-    atomicAdd((unsigned long long *)&n_big[1], (unsigned long long)nc);
-  } else {
-    const int slot = (int)atomicAdd((unsigned long long *)n_large, 1ull);
-    large[slot] = i;
-  }
-}
-
 // the cells of a big item, one lane per cell
 __device__ __forceinline__ void big_cell(const int *c0, const int *c1, int c, int &x, int &y, int &z) {
   const int sx = c1[0] - c0[0] + 1, sy = c1[1] - c0[1] + 1;
   x = c0[0] + c % sx;
   y = c0[1] + (c / sx) % sy;
   z = c0[2] + c / (sx * sy);
-}
-
-__global__ void k_big_hist(const int32_t *__restrict__ big, const int64_t *__restrict__ n_big,
-                           const ItemRec *__restrict__ rec, const GridDev *__restrict__ gp, uint32_t bmask,
-                           int32_t *bcnt) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nbig = n_big[0];
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nbig; w += nw) {
-    const int i = big[w];
-    const GridDev g = *gp;
-    const int sc = rec[i].tag >> 1;
-    int c0[3], c1[3];
-    cell_range(g, rec[i].lo, rec[i].hi, c0, c1);
-    const int nc = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
-    for (int c = lane; c < nc; c += 64) {
-      int x, y, z;
-      big_cell(c0, c1, c, x, y, z);
-      atomicAdd(&bcnt[cell_hash(x, y, z, sc) & bmask], 1);
-    }
-  }
 }
 
 // Workgroup-local bucket table: the items of a workgroup are neighbours
@@ -513,36 +595,119 @@ __device__ __forceinline__ int lt_find(const uint32_t *key, uint32_t b) {
   return -1;
 }
 
-__global__ __launch_bounds__(LT_T) void k_item_hist(int n, const ItemRec *__restrict__ rec,
-                                                    const GridDev *__restrict__ gp, uint32_t bmask,
-                                                    const int32_t *cnt, int32_t *bcnt) {
+// One side of a hash: the items, or the query vertices over the same grid.
+struct HSide {
+  int n;
+  const ItemRec *rec;
+  int32_t *cnt;      // cells per record, 0: not hashed one thread per record
+  int32_t *large;    // records tested against everything
+  int64_t *n_large;
+  int32_t *big;      // records hashed one wavefront each
+  int64_t *n_big;    // {records, cells}
+  int32_t *bcnt;     // entries per bucket; counted down again by the fill
+  int64_t *bstart;
+  struct Entry *ent;
+  int64_t ent_cap;
+};
+struct HSides {
+  HSide s[2];
+  int blocks0;  // workgroups of the first side (the rest: the second)
+};
+
+// Items covering up to MAX_ITEM_CELLS cells are hashed one thread per
+// item; larger ones with at most 64 cells per axis (the reach of the 6-bit
+// offsets of an entry) and at most BIG_CELLS cells are hashed one wavefront
+// per item (the big list, n_big = {items, cells}); the rest (the large
+// list) are tested against every query instead.
+// A first launch counts the cells and lists big and large records (count)
+// and counts the entries per bucket (hist): one pass, or two where the
+// number of buckets has to follow the number of entries.
+__global__ __launch_bounds__(LT_T) void k_cells(HSides hs, const uint64_t *st, int n_items, double cell_scale,
+                                                GridDev *gp, uint32_t bmask, bool count, bool hist, int64_t *n_ent,
+                                                uint32_t *status) {
   __shared__ uint32_t s_key[LT_SLOTS];
   __shared__ int32_t s_cnt[LT_SLOTS];
-  for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T) {
-    s_key[k] = 0u;
-    s_cnt[k] = 0;
+  __shared__ GridDev s_g;
+  __shared__ double s_stat[9];
+  __shared__ int s_big[LT_T];
+  __shared__ int s_nbig, s_ent;
+  const bool second = (int)blockIdx.x >= hs.blocks0;
+  const HSide &h = hs.s[second ? 1 : 0];
+  if (hist)
+    for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T) {
+      s_key[k] = 0u;
+      s_cnt[k] = 0;
+    }
+  if (threadIdx.x == 0) {
+    s_nbig = 0;
+    s_ent = 0;
+  }
+  if (count) {
+    grid_params(st, n_items, cell_scale, &s_g, s_stat);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *gp = s_g;
+      if (s_g.bad) atomicOr(status, ST_NONFINITE);
+    }
+  } else if (threadIdx.x == 0) {
+    s_g = *gp;
   }
   __syncthreads();
-  const int i = blockIdx.x * LT_T + threadIdx.x;
-  if (i < n && cnt[i] != 0) {
-    const GridDev g = *gp;
-    const int sc = rec[i].tag >> 1;
+  const GridDev g = s_g;
+  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * LT_T + threadIdx.x;
+  if (i < h.n) {
     int c0[3], c1[3];
-    cell_range(g, rec[i].lo, rec[i].hi, c0, c1);
-    for (int z = c0[2]; z <= c1[2]; ++z)
-      for (int y = c0[1]; y <= c1[1]; ++y)
-        for (int x = c0[0]; x <= c1[0]; ++x) {
-          const uint32_t b = cell_hash(x, y, z, sc) & bmask;
-          const int t = lt_insert(s_key, b);
-          if (t >= 0)
-            atomicAdd(&s_cnt[t], 1);
-          else
-            atomicAdd(&bcnt[b], 1);
-        }
+    cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
+    const int sx = c1[0] - c0[0] + 1, sy = c1[1] - c0[1] + 1, sz = c1[2] - c0[2] + 1;
+    const int64_t nc = (int64_t)sx * sy * sz;
+    // non-finite boxes: nothing is hashed (the error is reported)
+    const bool small = nc <= MAX_ITEM_CELLS && !g.bad;
+    const bool big = !small && sx <= 64 && sy <= 64 && sz <= 64 && nc <= BIG_CELLS && !g.bad;
+    if (count) {
+      h.cnt[i] = small ? (int32_t)nc : 0;
+      if (big) {
+        const int slot = (int)atomicAdd((unsigned long long *)&h.n_big[0], 1ull);
+        h.big[slot] = i;
+        atomicAdd((unsigned long long *)&h.n_big[1], (unsigned long long)nc);
+      } else if (!small && !g.bad) {
+        h.large[(int)atomicAdd((unsigned long long *)h.n_large, 1ull)] = i;
+      }
+      if (n_ent && small) atomicAdd(&s_ent, (int)nc);
+    }
+    if (hist && big) s_big[atomicAdd(&s_nbig, 1)] = i;
+    if (hist && small) {
+      const int sc = h.rec[i].tag >> 1;
+      for (int z = c0[2]; z <= c1[2]; ++z)
+        for (int y = c0[1]; y <= c1[1]; ++y)
+          for (int x = c0[0]; x <= c1[0]; ++x) {
+            const uint32_t b = cell_hash(x, y, z, sc) & bmask;
+            const int t = lt_insert(s_key, b);
+            if (t >= 0)
+              atomicAdd(&s_cnt[t], 1);
+            else
+              atomicAdd(&h.bcnt[b], 1);
+          }
+    }
   }
   __syncthreads();
+  if (n_ent && threadIdx.x == 0 && s_ent)
+    atomicAdd((unsigned long long *)&n_ent[second ? 1 : 0], (unsigned long long)s_ent);
+  if (!hist) return;
   for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T)
-    if (s_key[k] != 0u) atomicAdd(&bcnt[s_key[k] - 1u], s_cnt[k]);
+    if (s_key[k] != 0u) atomicAdd(&h.bcnt[s_key[k] - 1u], s_cnt[k]);
+  // the workgroup's big records: a wavefront each, adds that return nothing
+  const int lane = threadIdx.x & 63;
+  for (int w = threadIdx.x >> 6; w < s_nbig; w += LT_T / 64) {
+    const int ib = s_big[w];
+    const int sc = h.rec[ib].tag >> 1;
+    int c0[3], c1[3];
+    cell_range(g, h.rec[ib].lo, h.rec[ib].hi, c0, c1);
+    const int nc = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
+    for (int c = lane; c < nc; c += 64) {
+      int x, y, z;
+      big_cell(c0, c1, c, x, y, z);
+      atomicAdd(&h.bcnt[cell_hash(x, y, z, sc) & bmask], 1);
+    }
+  }
 }
 
 // Hash entry: one (item, cell) pair.  The offset of the cell from the
@@ -553,34 +718,36 @@ struct Entry {
   int32_t dlo;  // cell minus the item's lower cell, 6 bits per axis
 };
 
-__global__ __launch_bounds__(LT_T) void k_item_fill(int n, const ItemRec *__restrict__ rec,
-                                                    const GridDev *__restrict__ gp, uint32_t bmask,
-                                                    const int32_t *cnt, const int64_t *bstart, int32_t *bfill,
-                                                    Entry *ent, int64_t ent_cap, uint32_t *status) {
+// Places the entries: a bucket's count is taken down from its end, so the
+// counters need no second array and end at zero.
+__global__ __launch_bounds__(LT_T) void k_item_fill(HSides hs, const GridDev *__restrict__ gp, uint32_t bmask,
+                                                    uint32_t *status) {
   __shared__ uint32_t s_key[LT_SLOTS];
   __shared__ int32_t s_cnt[LT_SLOTS];
   __shared__ int32_t s_base[LT_SLOTS];
+  const bool second = (int)blockIdx.x >= hs.blocks0;
+  const HSide &h = hs.s[second ? 1 : 0];
   for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T) {
     s_key[k] = 0u;
     s_cnt[k] = 0;
   }
   __syncthreads();
-  const int i = blockIdx.x * LT_T + threadIdx.x;
-  const bool live = i < n && cnt[i] != 0;
+  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * LT_T + threadIdx.x;
+  const bool live = i < h.n && h.cnt[i] != 0;
   GridDev g;
   int sc = 0, c0[3] = {0, 0, 0}, c1[3] = {-1, -1, -1};
   if (live) {
     g = *gp;
-    sc = rec[i].tag >> 1;
-    cell_range(g, rec[i].lo, rec[i].hi, c0, c1);
+    sc = h.rec[i].tag >> 1;
+    cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
   }
   auto put = [&](int64_t slot, int x, int y, int z) {
-    if (slot < ent_cap) {
+    if (slot < h.ent_cap) {
       Entry en;
       en.cell = cell_key(x, y, z, sc);
       en.item = i;
       en.dlo = (x - c0[0]) | ((y - c0[1]) << 6) | ((z - c0[2]) << 12);
-      ent[slot] = en;
+      h.ent[slot] = en;
     } else {
       atomicOr(status, ST_PLAN_OVERFLOW);
     }
@@ -595,12 +762,12 @@ __global__ __launch_bounds__(LT_T) void k_item_fill(int n, const ItemRec *__rest
         if (t >= 0)
           atomicAdd(&s_cnt[t], 1);
         else
-          put(bstart[b] + atomicAdd(&bfill[b], 1), x, y, z);
+          put(h.bstart[b] + atomicSub(&h.bcnt[b], 1) - 1, x, y, z);
       }
   __syncthreads();
   // reserve each bucket's range once
   for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T)
-    if (s_key[k] != 0u) s_base[k] = atomicAdd(&bfill[s_key[k] - 1u], s_cnt[k]);
+    if (s_key[k] != 0u) s_base[k] = atomicSub(&h.bcnt[s_key[k] - 1u], s_cnt[k]) - s_cnt[k];
   __syncthreads();
   // place: rank within the workgroup's range from the LDS count
   for (int z = c0[2]; z <= c1[2]; ++z)
@@ -608,34 +775,34 @@ __global__ __launch_bounds__(LT_T) void k_item_fill(int n, const ItemRec *__rest
       for (int x = c0[0]; x <= c1[0]; ++x) {
         const uint32_t b = cell_hash(x, y, z, sc) & bmask;
         const int t = lt_find(s_key, b);
-        if (t >= 0) put(bstart[b] + s_base[t] + atomicSub(&s_cnt[t], 1) - 1, x, y, z);
+        if (t >= 0) put(h.bstart[b] + s_base[t] + atomicSub(&s_cnt[t], 1) - 1, x, y, z);
       }
 }
 
-__global__ void k_big_fill(const int32_t *__restrict__ big, const int64_t *__restrict__ n_big,
-                           const ItemRec *__restrict__ rec, const GridDev *__restrict__ gp, uint32_t bmask,
-                           const int64_t *bstart, int32_t *bfill, Entry *ent, int64_t ent_cap, uint32_t *status) {
+// big records, one wavefront each (grid y: the side)
+__global__ void k_big_fill(HSides hs, const GridDev *__restrict__ gp, uint32_t bmask, uint32_t *status) {
+  const HSide &h = hs.s[blockIdx.y];
   const int lane = threadIdx.x & 63;
-  const int64_t nbig = n_big[0];
+  const int64_t nbig = h.n_big[0];
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nbig; w += nw) {
-    const int i = big[w];
+    const int i = h.big[w];
     const GridDev g = *gp;
-    const int sc = rec[i].tag >> 1;
+    const int sc = h.rec[i].tag >> 1;
     int c0[3], c1[3];
-    cell_range(g, rec[i].lo, rec[i].hi, c0, c1);
+    cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
     const int nc = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
     for (int c = lane; c < nc; c += 64) {
       int x, y, z;
       big_cell(c0, c1, c, x, y, z);
       const uint32_t b = cell_hash(x, y, z, sc) & bmask;
-      const int64_t slot = bstart[b] + atomicAdd(&bfill[b], 1);
-      if (slot < ent_cap) {
+      const int64_t slot = h.bstart[b] + atomicSub(&h.bcnt[b], 1) - 1;
+      if (slot < h.ent_cap) {
         Entry en;
         en.cell = cell_key(x, y, z, sc);
         en.item = i;
         en.dlo = (x - c0[0]) | ((y - c0[1]) << 6) | ((z - c0[2]) << 12);
-        ent[slot] = en;
+        h.ent[slot] = en;
       } else {
         atomicOr(status, ST_PLAN_OVERFLOW);
       }
@@ -643,8 +810,6 @@ __global__ void k_big_fill(const int32_t *__restrict__ big, const int64_t *__res
   }
 }
 
-// The hash of n records (count, histogram, scan, fill), small items one
-// thread each and big items one wavefront each.
 constexpr int BIG_BLOCKS = 256;
 
 __device__ __forceinline__ bool overlap(const double *qlo, const double *qhi, const ItemRec &r) {
@@ -1515,356 +1680,524 @@ __global__ __launch_bounds__(JT) void k_join(JoinArgs ja, int32_t *__restrict__ 
   wave_out_flush(wout, wcnt, total, out, cap);
 }
 
-// vertex records for the PT query hash (box of the point, swept when x1s)
-__global__ void k_vert_items(int n, const double *__restrict__ xs, const double *__restrict__ x1s, int n_vert,
-                             double h, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ vscene,
-                             ItemRec *__restrict__ rec) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  ItemRec r;
-  prim_box<1>(&i, xs, x1s, n_vert, h, r.lo, r.hi);
-  r.v[0] = i;
-  r.v[1] = -1;
-  r.v[2] = -1;
-  r.tag = (int)has_dof(rowptr, i) | (scene_of(vscene, i) << 1);
-  rec[i] = r;
+static BPRun bp_run(const eipc_scene *sc, int kind, const double *xs, const double *x1s, double dhat, bool join) {
+  BPRun r{};
+  r.sc = sc;
+  r.kind = kind;
+  r.slot = kind + 2 * (x1s != nullptr);
+  r.nq = kind == 0 ? sc->n_vert : sc->n_edge;
+  r.ni = kind == 0 ? sc->n_face : sc->n_edge;
+  r.xs = xs;
+  r.x1s = x1s;
+  r.h = 0.5 * dhat;
+  r.nb = 1024;
+  r.ent_cap = 1;
+  r.qent_cap = 1;
+  r.vhash = kind == 0 && join;
+  return r;
 }
 
-// Scratch of one broad phase (kind, swept) kept in the context's buffers.
-struct BPScratch {
-  ItemRec *items;
-  int32_t *cnt, *large, *bcnt, *bfill, *qcnt, *qlarge;
-  int64_t *cell_off, *bstart, *qoff, *n_large, *n_qlarge;
-  Entry *ent;
-  QEntry *qent;
-  int32_t *big, *qbig;
-  int64_t *n_big, *n_qbig;  // {items, cells}
-  ItemRec *vrec;     // bucket join, PT: vertex records
-  int64_t *vbstart;  // bucket join, PT: vertex-hash bucket offsets
-  GridDev *g;
-  uint64_t *st;
-  unsigned long long *total;
-};
-
-static eipc_status bp_scratch(eipc_ctx *c, int nq, int ni, uint32_t nb, int64_t ent_cap, int slot, BPScratch &b,
-                              int64_t qent_cap = 1) {
-  const int base = slot * BP_NBUF;
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 0), (size_t)ni, &b.items));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 1), (size_t)ni, &b.cnt));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 2), (size_t)ni, &b.large));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 3), (size_t)ni + 1, &b.cell_off));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 4), (size_t)nb, &b.bcnt));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 5), (size_t)nb, &b.bfill));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 6), (size_t)nb + 1, &b.bstart));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 7), (size_t)std::max<int64_t>(ent_cap, 1), &b.ent));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 8), (size_t)nq, &b.qcnt));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 9), (size_t)nq + 1, &b.qoff));
+static eipc_status bp_scratch(eipc_ctx *c, BPRun &r) {
+  const int base = B_BP0 + r.slot * BP_NBUF;
+  const size_t nq = (size_t)r.nq, ni = (size_t)r.ni;
+  BPScratch &b = r.b;
+  EIPC_TRY(ensure_t(c, (BufId)(base + 0), ni, &b.items));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 1), ni, &b.cnt));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 2), ni, &b.large));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 4), (size_t)r.nb, &b.bcnt));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 5), r.vhash ? (size_t)r.nb : 1, &b.vbcnt));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 6), (size_t)r.nb + 1, &b.bstart));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 7), (size_t)std::max<int64_t>(r.ent_cap, 1), &b.ent));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 8), nq, &b.qcnt));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 9), nq + 1, &b.qoff));
   char *small;
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 10), 512, &small));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 10), 512, &small));
   b.g = (GridDev *)small;
-  b.st = (uint64_t *)(small + 128);
-  b.n_large = (int64_t *)(small + 256);
-  b.total = (unsigned long long *)(small + 264);
-  b.n_qlarge = (int64_t *)(small + 272);
-  b.n_big = (int64_t *)(small + 280);
-  b.n_qbig = (int64_t *)(small + 296);
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 11), (size_t)nq, &b.qlarge));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 12), (size_t)std::max<int64_t>(qent_cap, 1), &b.qent));
-  const bool vhash = (slot & 1) == 0 && c->query_mode[0] == 3;
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 13), vhash ? (size_t)nq : 1, &b.vrec));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 14), vhash ? (size_t)nb + 1 : 1, &b.vbstart));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 15), (size_t)ni, &b.big));
-  EIPC_TRY(ensure_t(c, (BufId)(B_BP0 + base + 16), vhash ? (size_t)nq : 1, &b.qbig));
+  b.n_large = (int64_t *)(small + 64);
+  b.total = (unsigned long long *)(small + 72);
+  b.n_qlarge = (int64_t *)(small + 80);
+  b.n_big = (int64_t *)(small + 88);
+  b.n_qbig = (int64_t *)(small + 104);
+  b.n_ent = (int64_t *)(small + 120);
+  b.flag = (uint32_t *)(small + 136);
+  b.st = (uint64_t *)(small + 160);
+  static_assert(sizeof(GridDev) <= 64 && 160 + 9 * 8 * STAT_COPIES <= 512, "small scratch");
+  EIPC_TRY(ensure_t(c, (BufId)(base + 11), nq, &b.qlarge));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 12), (size_t)std::max<int64_t>(r.qent_cap, 1), &b.qent));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 13), r.vhash ? nq : 1, &b.vrec));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 14), r.vhash ? (size_t)r.nb + 1 : 1, &b.vbstart));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 15), ni, &b.big));
+  EIPC_TRY(ensure_t(c, (BufId)(base + 16), r.vhash ? nq : 1, &b.qbig));
   return EIPC_OK;
 }
 
-eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *x1s,
-                        double dhat, int32_t *out, int64_t cap, int64_t *n_out, int sort, hipStream_t s,
-                        int grow_id, int32_t **grown, const BPPlan *plan, int64_t *d_total) {
-  const int nq = kind == 0 ? sc->n_vert : sc->n_edge;
-  const int ni = kind == 0 ? sc->n_face : sc->n_edge;
-  const int slot = kind + 2 * (x1s != nullptr);
-  if (n_out) *n_out = 0;
-  if (nq == 0 || ni == 0) {
-    if (d_total) EIPC_TRY(launch_zero(c, d_total, 8, s));
-    if (!plan) c->last_plan[slot] = BPPlan{1024, 1, 0, 1};
+static void bp_clear(const BPRun &r, FillList &fl, bool small, bool buckets) {
+  if (small) fl.add(r.b.g, 512, 0);
+  if (buckets) {
+    fl.add(r.b.bcnt, sizeof(int32_t) * (size_t)r.nb, 0);
+    if (r.vhash) fl.add(r.b.vbcnt, sizeof(int32_t) * (size_t)r.nb, 0);
+  }
+}
+
+static HSides bp_sides(const BPRun &r) {
+  const BPScratch &b = r.b;
+  HSides h{};
+  h.s[0] = HSide{r.ni, b.items, b.cnt, b.large, b.n_large, b.big, b.n_big, b.bcnt, b.bstart, b.ent, r.ent_cap};
+  h.s[1] = HSide{r.vhash ? r.nq : 0, b.vrec,  b.qcnt,    b.qlarge, b.n_qlarge, b.qbig,
+                 b.n_qbig,           b.vbcnt, b.vbstart, reinterpret_cast<Entry *>(b.qent), r.qent_cap};
+  h.blocks0 = grid_for(r.ni, LT_T);
+  return h;
+}
+static unsigned bp_side_blocks(const BPRun &r) {
+  return (unsigned)(grid_for(r.ni, LT_T) + (r.vhash ? grid_for(r.nq, LT_T) : 0));
+}
+
+static eipc_status bp_items(eipc_ctx *c, const BPRun &r, hipStream_t s) {
+  const eipc_scene *sc = r.sc;
+  const int gi = std::min(grid_for(r.ni, STAT_T), STAT_BLOCKS);
+  const int gv = r.kind == 0 ? std::min(grid_for(r.nq, STAT_T), STAT_BLOCKS) : 0;
+  if (r.kind == 0)
+    k_items<0><<<gi + gv, STAT_T, 0, s>>>(r.ni, sc->faces, sc->n_vert, r.xs, r.x1s, r.h, sc->W_rowptr, r.vscene(),
+                                          r.b.items, r.vhash ? r.b.vrec : nullptr, gi, r.b.st);
+  else
+    k_items<1><<<gi, STAT_T, 0, s>>>(r.ni, sc->edges, sc->n_vert, r.xs, r.x1s, r.h, sc->W_rowptr, r.vscene(),
+                                     r.b.items, nullptr, gi, r.b.st);
+  EIPC_HIP(c, hipGetLastError());
+  return EIPC_OK;
+}
+
+static eipc_status bp_cells(eipc_ctx *c, const BPRun &r, bool count, bool hist, int64_t *n_ent, uint32_t *status,
+                            hipStream_t s) {
+  k_cells<<<bp_side_blocks(r), LT_T, 0, s>>>(bp_sides(r), r.b.st, r.ni, c->cell_scale, r.b.g, r.nb - 1, count, hist,
+                                             n_ent, status);
+  EIPC_HIP(c, hipGetLastError());
+  return EIPC_OK;
+}
+
+// bucket offsets and entries from the counts
+static eipc_status bp_entries(eipc_ctx *c, const BPRun &r, uint32_t *status, hipStream_t s) {
+  const BPScratch &b = r.b;
+  EIPC_TRY(exclusive_scan2(c, b.bcnt, r.nb, b.bstart, r.vhash ? b.vbcnt : nullptr, r.nb, b.vbstart, s));
+  const HSides h = bp_sides(r);
+  k_item_fill<<<bp_side_blocks(r), LT_T, 0, s>>>(h, b.g, r.nb - 1, status);
+  EIPC_HIP(c, hipGetLastError());
+  k_big_fill<<<dim3(BIG_BLOCKS, r.vhash ? 2 : 1), 256, 0, s>>>(h, b.g, r.nb - 1, status);
+  EIPC_HIP(c, hipGetLastError());
+  return EIPC_OK;
+}
+
+static QueryArgs bp_query_args(const BPRun &r) {
+  return QueryArgs{r.b.g,      r.nb - 1,      r.b.bstart, r.b.ent, r.ent_cap, r.b.large, r.b.n_large, r.b.items,
+                   r.sc->W_rowptr, r.vscene(), nullptr,   nullptr, nullptr,   nullptr,   r.ni};
+}
+
+// queries too large to bin or hash, one wavefront each, appended
+static eipc_status bp_large(eipc_ctx *c, const BPRun &r, const int32_t *list, const int64_t *n_list, int32_t *out,
+                            int64_t cap, unsigned long long *total, hipStream_t s) {
+  const QueryArgs qa = bp_query_args(r);
+  const int g = 2 * c->num_cu, nv = r.sc->n_vert;
+  if (r.kind == 0)
+    k_query_lq<0, 2><<<g, QT, 0, s>>>(list, n_list, r.xs, r.x1s, nv, r.h, qa, nullptr, nullptr, nullptr, out, cap, total);
+  else
+    k_query_lq<1, 2><<<g, QT, 0, s>>>(list, n_list, r.xs, r.x1s, nv, r.h, qa, nullptr, nullptr, nullptr, out, cap, total);
+  EIPC_HIP(c, hipGetLastError());
+  return EIPC_OK;
+}
+
+// the bucket join of a built hash, appended to out (*total counts past cap)
+static eipc_status bp_join(eipc_ctx *c, const BPRun &r, int32_t *out, int64_t cap, unsigned long long *total,
+                           hipStream_t s) {
+  const BPScratch &b = r.b;
+  ProfScope ps(c, r.kind == 0 ? K_QUERY_WRITE_PT : K_QUERY_WRITE_EE, s);
+  if (r.kind == 0) {
+    const JoinArgs ja{reinterpret_cast<const Entry *>(b.qent), b.vbstart + r.nb, r.qent_cap, b.vrec, b.bstart, b.ent,
+                      r.ent_cap, b.items, b.large, b.n_large, r.nb - 1};
+    k_join<0><<<grid_for(r.qent_cap, JT), JT, 0, s>>>(ja, out, cap, total);
+    EIPC_HIP(c, hipGetLastError());
+    return bp_large(c, r, b.qlarge, b.n_qlarge, out, cap, total, s);
+  }
+  const JoinArgs ja{b.ent, b.bstart + r.nb, r.ent_cap, b.items, b.bstart, b.ent, r.ent_cap, b.items, b.large,
+                    b.n_large, r.nb - 1};
+  k_join<1><<<grid_for(r.ent_cap, JT), JT, 0, s>>>(ja, out, cap, total);
+  EIPC_HIP(c, hipGetLastError());
+  return bp_large(c, r, b.large, b.n_large, out, cap, total, s);
+}
+
+// the other work splits (tuning): per query, per (query, cell) thread or
+// wavefront.  exact: the query entries are counted and sized first
+// (synchronizes), else qent_cap is the plan's.
+static eipc_status bp_append_split(eipc_ctx *c, BPRun &r, bool exact, int32_t *out, int64_t cap,
+                                   unsigned long long *total, uint32_t *status, hipStream_t s) {
+  const int qmode = c->query_mode[r.kind], nv = r.sc->n_vert, nq = r.nq;
+  const QueryArgs qa = bp_query_args(r);
+  ProfScope ps(c, r.kind == 0 ? K_QUERY_WRITE_PT : K_QUERY_WRITE_EE, s);
+  if (qmode == 0) {
+    QueryArgs qdef = qa;  // hands queries of many cells to k_query_lq
+    qdef.defer = r.b.qlarge;
+    qdef.n_defer = r.b.n_qlarge;
+    EIPC_TRY(launch_zero(c, r.b.n_qlarge, 8, s));  // the list is rebuilt by every attempt
+    if (r.kind == 0)
+      k_query_sm<0><<<grid_for(nq, QT), QT, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qdef, out, cap, total);
+    else
+      k_query_sm<1><<<grid_for(nq, QT), QT, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qdef, out, cap, total);
+    EIPC_HIP(c, hipGetLastError());
+    return bp_large(c, r, r.b.qlarge, r.b.n_qlarge, out, cap, total, s);
+  }
+  const int gq = grid_for(nq, 256);
+  EIPC_TRY(launch_zero(c, r.b.n_qlarge, 8, s));
+  if (r.kind == 0)
+    k_qcells<0><<<gq, 256, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qa, r.b.qcnt, r.b.qlarge, r.b.n_qlarge);
+  else
+    k_qcells<1><<<gq, 256, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qa, r.b.qcnt, r.b.qlarge, r.b.n_qlarge);
+  EIPC_HIP(c, hipGetLastError());
+  EIPC_TRY(exclusive_scan(c, r.b.qcnt, nq, r.b.qoff, s));
+  if (exact) {
+    int64_t tq = 0;
+    EIPC_HIP(c, hipMemcpyAsync(&tq, r.b.qoff + nq, 8, hipMemcpyDeviceToHost, s));
+    EIPC_HIP(c, hipStreamSynchronize(s));
+    r.qent_cap = std::max<int64_t>(tq, 1);
+    EIPC_TRY(bp_scratch(c, r));
+  }
+  if (r.kind == 0)
+    k_qlist<0><<<gq, 256, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qa, r.b.qcnt, r.b.qoff, r.b.qent, r.qent_cap, status);
+  else
+    k_qlist<1><<<gq, 256, 0, s>>>(nq, r.xs, r.x1s, nv, r.h, qa, r.b.qcnt, r.b.qoff, r.b.qent, r.qent_cap, status);
+  EIPC_HIP(c, hipGetLastError());
+  if (qmode == 2) {
+    const int gw = (int)std::min<int64_t>(grid_for(r.qent_cap * 64, QT), 32 * (int64_t)c->num_cu);
+    if (r.kind == 0)
+      k_query_wave<0><<<gw, QT, 0, s>>>(r.b.qoff + nq, r.qent_cap, r.b.qent, r.xs, r.x1s, nv, r.h, qa, out, cap, total);
+    else
+      k_query_wave<1><<<gw, QT, 0, s>>>(r.b.qoff + nq, r.qent_cap, r.b.qent, r.xs, r.x1s, nv, r.h, qa, out, cap, total);
+  } else {
+    const int ge = (int)std::min<int64_t>(grid_for(r.qent_cap, QT), 64 * (int64_t)c->num_cu);
+    if (r.kind == 0)
+      k_query_ent<0><<<ge, QT, 0, s>>>(r.b.qoff + nq, r.qent_cap, r.b.qent, r.xs, r.x1s, nv, r.h, qa, out, cap, total);
+    else
+      k_query_ent<1><<<ge, QT, 0, s>>>(r.b.qoff + nq, r.qent_cap, r.b.qent, r.xs, r.x1s, nv, r.h, qa, out, cap, total);
+  }
+  EIPC_HIP(c, hipGetLastError());
+  return bp_large(c, r, r.b.qlarge, r.b.n_qlarge, out, cap, total, s);
+}
+
+// ---- planned (capacities known, nothing read by the host) ----
+
+eipc_status bp_planned_begin(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *x1s,
+                             double dhat, const BPPlan &plan, BPRun &r, FillList &fl) {
+  r = bp_run(sc, kind, xs, x1s, dhat, c->query_mode[kind] == 3);
+  if (r.nq == 0 || r.ni == 0) return EIPC_OK;
+  r.nb = plan.nb;
+  r.ent_cap = plan.ent_cap;
+  r.qent_cap = plan.qent_cap;
+  EIPC_TRY(bp_scratch(c, r));
+  bp_clear(r, fl, true, true);
+  return EIPC_OK;
+}
+
+eipc_status bp_planned_run(eipc_ctx *c, BPRun &r, int32_t *out, int64_t cap, int64_t *d_total, hipStream_t s) {
+  if (r.nq == 0 || r.ni == 0) return EIPC_OK;  // *d_total was cleared by the caller
+  EIPC_TRY(bp_items(c, r, s));
+  EIPC_TRY(bp_cells(c, r, true, true, nullptr, c->status, s));
+  EIPC_TRY(bp_entries(c, r, c->status, s));
+  if (c->query_mode[r.kind] == 3) return bp_join(c, r, out, cap, (unsigned long long *)d_total, s);
+  return bp_append_split(c, r, false, out, cap, (unsigned long long *)d_total, c->status, s);
+}
+
+// ---- sorted lists from an appended one ----
+// The join's pairs are put in order by counting: each pair takes a slot of
+// its first index (k_sort_slot), the slots' items are gathered per first
+// index (k_sort_gather), and each pair's place is the number of smaller
+// items of its first index (the items of one are distinct).  About 10 items
+// per index on the benchmark scenes, read from cache.  The two passes of the
+// per-query kernels (count, then write and insertion-sort) that this
+// replaces took 3.9 ms for config 2's lists.
+__global__ __launch_bounds__(256) void k_sort_slot(const int2 *__restrict__ list, const unsigned long long *total,
+                                                   int64_t cap, int32_t *cnt, int32_t *__restrict__ slot) {
+  const int64_t n = (int64_t)*total;
+  if (n > cap) return;  // the list is cut: run again with a larger one
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    slot[i] = atomicAdd(&cnt[list[i].x], 1);
+}
+__global__ __launch_bounds__(256) void k_sort_gather(const int2 *__restrict__ list, const unsigned long long *total,
+                                                     int64_t cap, const int64_t *__restrict__ off,
+                                                     const int32_t *__restrict__ slot, int32_t *__restrict__ tmp) {
+  const int64_t n = (int64_t)*total;
+  if (n > cap) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int2 p = list[i];
+    tmp[off[p.x] + slot[i]] = p.y;
+  }
+}
+// nothing is written when the output is too small
+__global__ __launch_bounds__(256) void k_sort_rank(const int2 *__restrict__ list, const unsigned long long *total,
+                                                   int64_t cap, const int64_t *__restrict__ off,
+                                                   const int32_t *__restrict__ tmp, int2 *__restrict__ out,
+                                                   int64_t out_cap) {
+  const int64_t n = (int64_t)*total;
+  if (n > cap || n > out_cap) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int2 p = list[i];
+    const int64_t o0 = off[p.x], o1 = off[p.x + 1];
+    int64_t rank = 0;
+    int64_t j = o0;
+    for (; j + 4 <= o1; j += 4)
+      rank += (int)(tmp[j] < p.y) + (int)(tmp[j + 1] < p.y) + (int)(tmp[j + 2] < p.y) + (int)(tmp[j + 3] < p.y);
+    for (; j < o1; ++j) rank += tmp[j] < p.y;
+    out[o0 + rank] = p;
+  }
+}
+
+// ---- unplanned ----
+
+// Sized step by step with the host reading the counts: no buffer is larger
+// than its content (arena mode, where a caller's reservation was made for
+// that, and the tuning work splits).  Sorted lists by two per-query passes.
+static eipc_status bp_exact(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const double *x1s,
+                            double dhat, BPReq &q, hipStream_t s) {
+  const bool join = !q.sort && c->query_mode[kind] == 3;
+  BPRun r = bp_run(sc, kind, xs, x1s, dhat, join);
+  q.n = 0;
+  if (r.nq == 0 || r.ni == 0) {
+    c->last_plan[r.slot] = BPPlan{1024, 1, 0, 1};
     return EIPC_OK;
   }
-  const double h = 0.5 * dhat;
-  const int32_t *vsc = sc->n_scene > 1 ? sc->vert_scene : nullptr;
-  // phase 1: items, statistics, grid parameters, cell counts (always)
-  BPScratch b;
-  uint32_t nb = plan ? plan->nb : 1024;
-  int64_t ent_cap = plan ? plan->ent_cap : 1;
-  EIPC_TRY(bp_scratch(c, nq, ni, nb, ent_cap, slot, b, plan ? plan->qent_cap : 1));
-  if (kind == 0)
-    k_items<3><<<grid_for(ni, 256), 256, 0, s>>>(ni, sc->faces, xs, x1s, sc->n_vert, h, sc->W_rowptr, vsc, b.items);
-  else
-    k_items<2><<<grid_for(ni, 256), 256, 0, s>>>(ni, sc->edges, xs, x1s, sc->n_vert, h, sc->W_rowptr, vsc, b.items);
-  EIPC_HIP(c, hipGetLastError());
-  k_stats_init<<<1, 64, 0, s>>>(b.st);
-  k_box_stats<<<stat_blocks(ni), STAT_T, 0, s>>>(ni, b.items, nullptr, nullptr, 0, h, b.st, 1);
-  if (kind == 0) k_box_stats<<<stat_blocks(nq), STAT_T, 0, s>>>(nq, nullptr, xs, x1s, sc->n_vert, h, b.st, 0);
-  k_grid_params<<<1, 64, 0, s>>>(b.st, ni, c->cell_scale, b.g, c->status);
-  EIPC_TRY(launch_zero(c, b.n_large, 56, s));
-  k_item_cells<<<grid_for(ni, 256), 256, 0, s>>>(ni, b.items, b.g, b.cnt, b.large, b.n_large, b.big, b.n_big);
-  EIPC_HIP(c, hipGetLastError());
-  EIPC_TRY(exclusive_scan(c, b.cnt, ni, b.cell_off, s));
-  if (!plan) {
-    // size the hash from the entry count (synchronizes)
-    int64_t hv[2];
-    int64_t hbig[2];
-    GridDev gh;
-    EIPC_HIP(c, hipMemcpyAsync(&hv[0], b.cell_off + ni, 8, hipMemcpyDeviceToHost, s));
-    EIPC_HIP(c, hipMemcpyAsync(hbig, b.n_big, 16, hipMemcpyDeviceToHost, s));
-    EIPC_HIP(c, hipMemcpyAsync(&gh, b.g, sizeof(GridDev), hipMemcpyDeviceToHost, s));
-    EIPC_HIP(c, hipStreamSynchronize(s));
-    if (gh.bad) {
-      EIPC_TRY(launch_zero(c, c->status, 4, s));  // reported here instead
-      return set_err(c, EIPC_ERR_NONFINITE, "non-finite primitive boxes");
-    }
-    hv[0] += hbig[1];
-    ent_cap = std::max<int64_t>(hv[0], 1);
-    nb = (uint32_t)hash_buckets(hv[0]);
-    EIPC_TRY(bp_scratch(c, nq, ni, nb, ent_cap, slot, b));
-    c->last_plan[slot].nb = nb;
-    c->last_plan[slot].ent_cap = ent_cap;
+  BPPlan &seen = c->last_plan[r.slot];
+  FillList fl;
+  EIPC_TRY(bp_scratch(c, r));
+  bp_clear(r, fl, true, false);
+  EIPC_TRY(launch_fill(c, fl, s));
+  EIPC_TRY(bp_items(c, r, s));
+  EIPC_TRY(bp_cells(c, r, true, false, r.b.n_ent, r.b.flag, s));
+  // the scratch header: grid, counters and entry counts
+  struct alignas(8) Head {
+    char b[160];
+  } hd;
+  EIPC_HIP(c, hipMemcpyAsync(&hd, r.b.g, sizeof(Head), hipMemcpyDeviceToHost, s));
+  EIPC_HIP(c, hipStreamSynchronize(s));
+  auto word = [&](const void *d) {
+    int64_t v;
+    std::memcpy(&v, hd.b + ((const char *)d - (const char *)r.b.g), 8);
+    return v;
+  };
+  GridDev gh;
+  std::memcpy((void *)&gh, hd.b, sizeof(gh));
+  if (gh.bad) {
+    EIPC_TRY(launch_zero(c, c->status, 4, s));  // reported here instead
+    return set_err(c, EIPC_ERR_NONFINITE, "non-finite primitive boxes");
   }
-  const uint32_t bmask = nb - 1;
-  EIPC_TRY(launch_zero(c, b.bcnt, sizeof(int32_t) * nb, s));
-  EIPC_TRY(launch_zero(c, b.bfill, sizeof(int32_t) * nb, s));
-  k_item_hist<<<grid_for(ni, LT_T), LT_T, 0, s>>>(ni, b.items, b.g, bmask, b.cnt, b.bcnt);
-  k_big_hist<<<BIG_BLOCKS, 256, 0, s>>>(b.big, b.n_big, b.items, b.g, bmask, b.bcnt);
-  EIPC_HIP(c, hipGetLastError());
-  EIPC_TRY(exclusive_scan(c, b.bcnt, nb, b.bstart, s));
-  k_item_fill<<<grid_for(ni, LT_T), LT_T, 0, s>>>(ni, b.items, b.g, bmask, b.cnt, b.bstart, b.bfill, b.ent, ent_cap,
-                                                 c->status);
-  k_big_fill<<<BIG_BLOCKS, 256, 0, s>>>(b.big, b.n_big, b.items, b.g, bmask, b.bstart, b.bfill, b.ent, ent_cap,
-                                        c->status);
-  EIPC_HIP(c, hipGetLastError());
-  QueryArgs qa{b.g, bmask, b.bstart, b.ent, ent_cap, b.large, b.n_large, b.items, sc->W_rowptr, vsc, nullptr,
-               nullptr, nullptr, nullptr, ni};
-  QueryArgs qdef = qa;  // per-query kernels hand queries of many cells to k_query_lq
-  qdef.defer = b.qlarge;
-  qdef.n_defer = b.n_qlarge;
-  const int glq = 2 * c->num_cu;
-  const int n_vert = sc->n_vert;
-  if (!sort) {
-    // single pass, unsorted append; per query, per (query, cell) or as a
-    // bucket join
-    const int qmode = c->query_mode[kind];
-    const bool cellpar = qmode == 1 || qmode == 2;
-    int64_t qent_cap = plan ? plan->qent_cap : 1;
-    const int gq = grid_for(nq, 256);
-    if (qmode == 3) {
-      if (kind == 0) {
-        // vertex hash over the same grid and buckets as the faces
-        k_vert_items<<<gq, 256, 0, s>>>(nq, xs, x1s, n_vert, h, sc->W_rowptr, vsc, b.vrec);
-        k_item_cells<<<gq, 256, 0, s>>>(nq, b.vrec, b.g, b.qcnt, b.qlarge, b.n_qlarge, b.qbig, b.n_qbig);
-        EIPC_HIP(c, hipGetLastError());
-        if (!plan) {
-          EIPC_TRY(exclusive_scan(c, b.qcnt, nq, b.qoff, s));
-          int64_t tq = 0, tbig[2];
-          EIPC_HIP(c, hipMemcpyAsync(&tq, b.qoff + nq, 8, hipMemcpyDeviceToHost, s));
-          EIPC_HIP(c, hipMemcpyAsync(tbig, b.n_qbig, 16, hipMemcpyDeviceToHost, s));
-          EIPC_HIP(c, hipStreamSynchronize(s));
-          qent_cap = std::max<int64_t>(tq + tbig[1], 1);
-          c->last_plan[slot].qent_cap = qent_cap;
-          EIPC_TRY(bp_scratch(c, nq, ni, nb, ent_cap, slot, b, qent_cap));
-        }
-        EIPC_TRY(launch_zero(c, b.bcnt, sizeof(int32_t) * nb, s));
-        EIPC_TRY(launch_zero(c, b.bfill, sizeof(int32_t) * nb, s));
-        k_item_hist<<<grid_for(nq, LT_T), LT_T, 0, s>>>(nq, b.vrec, b.g, bmask, b.qcnt, b.bcnt);
-        k_big_hist<<<BIG_BLOCKS, 256, 0, s>>>(b.qbig, b.n_qbig, b.vrec, b.g, bmask, b.bcnt);
-        EIPC_HIP(c, hipGetLastError());
-        EIPC_TRY(exclusive_scan(c, b.bcnt, nb, b.vbstart, s));
-        k_item_fill<<<grid_for(nq, LT_T), LT_T, 0, s>>>(nq, b.vrec, b.g, bmask, b.qcnt, b.vbstart, b.bfill,
-                                       reinterpret_cast<Entry *>(b.qent), qent_cap, c->status);
-        k_big_fill<<<BIG_BLOCKS, 256, 0, s>>>(b.qbig, b.n_qbig, b.vrec, b.g, bmask, b.vbstart, b.bfill,
-                                              reinterpret_cast<Entry *>(b.qent), qent_cap, c->status);
-        EIPC_HIP(c, hipGetLastError());
-      } else if (!plan) {
-        c->last_plan[slot].qent_cap = 1;
-      }
-    } else if (!cellpar) {
-      if (!plan) c->last_plan[slot].qent_cap = 1;
-    } else {
-    if (kind == 0)
-      k_qcells<0><<<gq, 256, 0, s>>>(nq, xs, x1s, n_vert, h, qa, b.qcnt, b.qlarge, b.n_qlarge);
-    else
-      k_qcells<1><<<gq, 256, 0, s>>>(nq, xs, x1s, n_vert, h, qa, b.qcnt, b.qlarge, b.n_qlarge);
-    EIPC_HIP(c, hipGetLastError());
-    EIPC_TRY(exclusive_scan(c, b.qcnt, nq, b.qoff, s));
-    if (!plan) {
-      int64_t tq = 0;
-      EIPC_HIP(c, hipMemcpyAsync(&tq, b.qoff + nq, 8, hipMemcpyDeviceToHost, s));
-      EIPC_HIP(c, hipStreamSynchronize(s));
-      qent_cap = std::max<int64_t>(tq, 1);
-      c->last_plan[slot].qent_cap = qent_cap;
-      EIPC_TRY(bp_scratch(c, nq, ni, nb, ent_cap, slot, b, qent_cap));
-    }
-    if (kind == 0)
-      k_qlist<0><<<gq, 256, 0, s>>>(nq, xs, x1s, n_vert, h, qa, b.qcnt, b.qoff, b.qent, qent_cap, c->status);
-    else
-      k_qlist<1><<<gq, 256, 0, s>>>(nq, xs, x1s, n_vert, h, qa, b.qcnt, b.qoff, b.qent, qent_cap, c->status);
-    EIPC_HIP(c, hipGetLastError());
-    }
-    QueryArgs qlq = qa;  // queries too large to bin, run per query
-    qlq.qlist = b.qlarge;
-    qlq.n_qlist = b.n_qlarge;
-    int64_t capa = cap;
-    if (plan) {
-      capa = plan->cand_cap;
-    } else if (grow_id >= 0) {
-      capa = (int64_t)(c->buf[grow_id].bytes / 8);
-      if (capa > 64) capa -= 16;
-      EIPC_TRY(ensure_t(c, (BufId)grow_id, (size_t)std::max<int64_t>(2 * capa, 2), &out));
+  const int64_t n_ent = word(r.b.n_ent) + word(r.b.n_big + 1);
+  r.ent_cap = std::max<int64_t>(n_ent, 1);
+  r.nb = (uint32_t)hash_buckets(n_ent);
+  if (r.vhash) r.qent_cap = std::max<int64_t>(word(r.b.n_ent + 1) + word(r.b.n_qbig + 1), 1);
+  EIPC_TRY(bp_scratch(c, r));
+  seen.nb = r.nb;
+  seen.ent_cap = r.ent_cap;
+  bp_clear(r, fl, false, true);
+  EIPC_TRY(launch_fill(c, fl, s));
+  EIPC_TRY(bp_cells(c, r, false, true, nullptr, r.b.flag, s));
+  EIPC_TRY(bp_entries(c, r, r.b.flag, s));
+  int64_t total = 0;
+  if (!q.sort) {
+    int64_t cap = q.cap;
+    int32_t *out = q.out;
+    if (q.grow_id >= 0) {
+      cap = (int64_t)(c->buf[q.grow_id].bytes / 8);
+      if (cap > 64) cap -= 16;
+      EIPC_TRY(ensure_t(c, (BufId)q.grow_id, (size_t)std::max<int64_t>(2 * cap, 2), &out));
     }
     for (int attempt = 0; attempt < 2; ++attempt) {
-      EIPC_TRY(launch_zero(c, b.total, 8, s));
-      {
-        ProfScope ps(c, kind == 0 ? K_QUERY_WRITE_PT : K_QUERY_WRITE_EE, s);
-        const int ge = (int)std::min<int64_t>(grid_for(qent_cap, QT), 64 * (int64_t)c->num_cu);
-        if (qmode == 3) {
-          QueryArgs qlj = qa;  // queries too large to hash, run per query
-          if (kind == 0) {
-            const JoinArgs ja{reinterpret_cast<const Entry *>(b.qent), b.vbstart + nb, qent_cap, b.vrec, b.bstart,
-                              b.ent, ent_cap, b.items, b.large, b.n_large, bmask};
-            k_join<0><<<grid_for(qent_cap, JT), JT, 0, s>>>(ja, out, capa, b.total);
-            qlj.qlist = b.qlarge;
-            qlj.n_qlist = b.n_qlarge;
-          } else {
-            const JoinArgs ja{b.ent, b.bstart + nb, ent_cap, b.items, b.bstart, b.ent, ent_cap, b.items, b.large,
-                              b.n_large, bmask};
-            k_join<1><<<grid_for(ent_cap, JT), JT, 0, s>>>(ja, out, capa, b.total);
-            qlj.qlist = b.large;
-            qlj.n_qlist = b.n_large;
-          }
-          EIPC_HIP(c, hipGetLastError());
-          if (kind == 0)
-            k_query_lq<0, 2><<<glq, QT, 0, s>>>(qlj.qlist, qlj.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-          else
-            k_query_lq<1, 2><<<glq, QT, 0, s>>>(qlj.qlist, qlj.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-        } else if (!cellpar) {
-          // the deferred list is rebuilt by every attempt
-          EIPC_TRY(launch_zero(c, b.n_qlarge, 8, s));
-          if (kind == 0)
-            k_query_sm<0><<<grid_for(nq, QT), QT, 0, s>>>(nq, xs, x1s, n_vert, h, qdef, out, capa, b.total);
-          else
-            k_query_sm<1><<<grid_for(nq, QT), QT, 0, s>>>(nq, xs, x1s, n_vert, h, qdef, out, capa, b.total);
-          EIPC_HIP(c, hipGetLastError());
-          if (kind == 0)
-            k_query_lq<0, 2><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-          else
-            k_query_lq<1, 2><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-        } else if (c->query_mode[kind] == 2) {
-          const int gw = (int)std::min<int64_t>(grid_for(qent_cap * 64, QT), 32 * (int64_t)c->num_cu);
-          if (kind == 0)
-            k_query_wave<0><<<gw, QT, 0, s>>>(b.qoff + nq, qent_cap, b.qent, xs, x1s, n_vert, h, qa, out, capa,
-                                              b.total);
-          else
-            k_query_wave<1><<<gw, QT, 0, s>>>(b.qoff + nq, qent_cap, b.qent, xs, x1s, n_vert, h, qa, out, capa,
-                                              b.total);
-          EIPC_HIP(c, hipGetLastError());
-          if (kind == 0)
-            k_query_lq<0, 2><<<glq, QT, 0, s>>>(qlq.qlist, qlq.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-          else
-            k_query_lq<1, 2><<<glq, QT, 0, s>>>(qlq.qlist, qlq.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                                nullptr, out, capa, b.total);
-        } else {
-        if (kind == 0)
-          k_query_ent<0><<<ge, QT, 0, s>>>(b.qoff + nq, qent_cap, b.qent, xs, x1s, n_vert, h, qa, out, capa,
-                                           b.total);
-        else
-          k_query_ent<1><<<ge, QT, 0, s>>>(b.qoff + nq, qent_cap, b.qent, xs, x1s, n_vert, h, qa, out, capa,
-                                           b.total);
-        EIPC_HIP(c, hipGetLastError());
-        if (kind == 0)
-          k_query_lq<0, 2><<<glq, QT, 0, s>>>(qlq.qlist, qlq.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                              nullptr, out, capa, b.total);
-        else
-          k_query_lq<1, 2><<<glq, QT, 0, s>>>(qlq.qlist, qlq.n_qlist, xs, x1s, n_vert, h, qa, nullptr, nullptr,
-                                              nullptr, out, capa, b.total);
-        }
-      }
-      EIPC_HIP(c, hipGetLastError());
-      if (plan) {
-        // device-side count for the consumer; overflow is detected there
-        k_copy_count<<<1, 1, 0, s>>>((const int64_t *)b.total, d_total, capa, c->status);
-        EIPC_HIP(c, hipGetLastError());
-        return EIPC_OK;
-      }
-      int64_t total = 0;
-      EIPC_HIP(c, hipMemcpyAsync(&total, b.total, 8, hipMemcpyDeviceToHost, s));
+      EIPC_TRY(launch_zero(c, r.b.total, 8, s));
+      if (join)
+        EIPC_TRY(bp_join(c, r, out, cap, r.b.total, s));
+      else
+        EIPC_TRY(bp_append_split(c, r, true, out, cap, r.b.total, r.b.flag, s));
+      EIPC_HIP(c, hipMemcpyAsync(&total, r.b.total, 8, hipMemcpyDeviceToHost, s));
       EIPC_HIP(c, hipStreamSynchronize(s));
-      if (n_out) *n_out = total;
-      if (total <= capa) {
-        if (grown) *grown = out;
-        c->last_plan[slot].cand_cap = total;
+      seen.qent_cap = r.qent_cap;
+      q.n = total;
+      if (total <= cap) {
+        if (q.grow_id >= 0) q.out = out;
+        seen.cand_cap = total;
         return EIPC_OK;
       }
-      if (grow_id < 0) return EIPC_ERR_CAPACITY;
-      capa = total + total / 4 + 1024;
-      EIPC_TRY(ensure_t(c, (BufId)grow_id, (size_t)2 * capa, &out));
+      if (q.grow_id < 0) return EIPC_ERR_CAPACITY;
+      cap = total + total / 4 + 1024;
+      EIPC_TRY(ensure_t(c, (BufId)q.grow_id, (size_t)2 * cap, &out));
     }
     return set_err(c, EIPC_ERR_CAPACITY, "candidate append did not converge");
   }
+  const QueryArgs qa = bp_query_args(r);
+  QueryArgs qdef = qa;  // per-query kernels hand queries of many cells to k_query_lq
+  qdef.defer = r.b.qlarge;
+  qdef.n_defer = r.b.n_qlarge;
+  const int glq = 2 * c->num_cu, nv = sc->n_vert, nq = r.nq;
+  const double h = r.h;
+  const BPScratch &b = r.b;
   {
     ProfScope ps(c, kind == 0 ? K_QUERY_COUNT_PT : K_QUERY_COUNT_EE, s);
     if (kind == 0) {
-      launch_query<0, 0>(nq, xs, x1s, n_vert, h, qdef, b.qcnt, nullptr, nullptr, 0, nullptr, c->status, s);
-      k_query_lq<0, 0><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, b.qcnt, nullptr, nullptr,
-                                          nullptr, 0, nullptr);
+      launch_query<0, 0>(nq, xs, x1s, nv, h, qdef, b.qcnt, nullptr, nullptr, 0, nullptr, c->status, s);
+      k_query_lq<0, 0><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, nv, h, qa, b.qcnt, nullptr, nullptr, nullptr,
+                                          0, nullptr);
     } else {
-      launch_query<1, 0>(nq, xs, x1s, n_vert, h, qdef, b.qcnt, nullptr, nullptr, 0, nullptr, c->status, s);
-      k_query_lq<1, 0><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, b.qcnt, nullptr, nullptr,
-                                          nullptr, 0, nullptr);
+      launch_query<1, 0>(nq, xs, x1s, nv, h, qdef, b.qcnt, nullptr, nullptr, 0, nullptr, c->status, s);
+      k_query_lq<1, 0><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, nv, h, qa, b.qcnt, nullptr, nullptr, nullptr,
+                                          0, nullptr);
     }
   }
   EIPC_HIP(c, hipGetLastError());
   EIPC_TRY(exclusive_scan(c, b.qcnt, nq, b.qoff, s));
-  if (plan) {
-    cap = plan->cand_cap;
-  } else {
-    int64_t total = 0;
-    EIPC_HIP(c, hipMemcpyAsync(&total, b.qoff + nq, 8, hipMemcpyDeviceToHost, s));
-    EIPC_HIP(c, hipStreamSynchronize(s));
-    if (n_out) *n_out = total;
-    c->last_plan[slot].cand_cap = total;
-    if (grow_id >= 0) {
-      EIPC_TRY(ensure_t(c, (BufId)grow_id, (size_t)std::max<int64_t>(2 * total, 2), &out));
-      cap = total;
-      *grown = out;
-    }
-    if (total > cap || out == nullptr) return total > cap ? EIPC_ERR_CAPACITY : EIPC_OK;
-    if (total == 0) return EIPC_OK;
-  }
+  EIPC_HIP(c, hipMemcpyAsync(&total, b.qoff + nq, 8, hipMemcpyDeviceToHost, s));
+  EIPC_HIP(c, hipStreamSynchronize(s));
+  q.n = total;
+  seen.cand_cap = total;
+  if (total > q.cap) return EIPC_ERR_CAPACITY;
+  if (total == 0 || q.out == nullptr) return EIPC_OK;
   {
     int32_t *tmp;
-    EIPC_TRY(ensure_t(c, B_LQTMP, (size_t)std::max<int64_t>(cap, 1), &tmp));
+    EIPC_TRY(ensure_t(c, B_LQTMP, (size_t)std::max<int64_t>(q.cap, 1), &tmp));
     ProfScope ps(c, kind == 0 ? K_QUERY_WRITE_PT : K_QUERY_WRITE_EE, s);
     if (kind == 0) {
-      launch_query<0, 1>(nq, xs, x1s, n_vert, h, qdef, b.qcnt, b.qoff, out, cap, nullptr, c->status, s);
-      k_query_lq<0, 1><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, nullptr, b.qoff, tmp,
-                                          nullptr, cap, nullptr);
+      launch_query<0, 1>(nq, xs, x1s, nv, h, qdef, b.qcnt, b.qoff, q.out, q.cap, nullptr, c->status, s);
+      k_query_lq<0, 1><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, nv, h, qa, nullptr, b.qoff, tmp, nullptr,
+                                          q.cap, nullptr);
     } else {
-      launch_query<1, 1>(nq, xs, x1s, n_vert, h, qdef, b.qcnt, b.qoff, out, cap, nullptr, c->status, s);
-      k_query_lq<1, 1><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, n_vert, h, qa, nullptr, b.qoff, tmp,
-                                          nullptr, cap, nullptr);
+      launch_query<1, 1>(nq, xs, x1s, nv, h, qdef, b.qcnt, b.qoff, q.out, q.cap, nullptr, c->status, s);
+      k_query_lq<1, 1><<<glq, QT, 0, s>>>(b.qlarge, b.n_qlarge, xs, x1s, nv, h, qa, nullptr, b.qoff, tmp, nullptr,
+                                          q.cap, nullptr);
     }
-    k_seg_rank<<<glq, RANK_T, 0, s>>>(b.qlarge, b.n_qlarge, b.qcnt, b.qoff, tmp, out, cap);
+    k_seg_rank<<<glq, RANK_T, 0, s>>>(b.qlarge, b.n_qlarge, b.qcnt, b.qoff, tmp, q.out, q.cap);
   }
   EIPC_HIP(c, hipGetLastError());
-  if (plan) {
-    k_copy_count<<<1, 1, 0, s>>>(b.qoff + nq, d_total, cap, c->status);
-    EIPC_HIP(c, hipGetLastError());
-  }
   return EIPC_OK;
+}
+
+// Both kinds with one synchronization: every buffer is sized from the last
+// pass on this context (or the scene's size on the first), the kernels keep
+// within it and count what they need, and a pass that needed more is run
+// again.  Results do not depend on the sizes.  `after` enqueues what follows
+// (the lists and their device counts), so that it is read back together.
+eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, const double *xs, const double *x1s, double dhat,
+                        BPReq req[2], hipStream_t s, const BPAfter &after) {
+  const bool exact = c->arena || (!req[0].sort && c->query_mode[0] != 3) || (!req[1].sort && c->query_mode[1] != 3);
+  if (exact) {
+    eipc_status out = EIPC_OK;
+    for (int kind = 0; kind < 2; ++kind) {
+      const eipc_status st = bp_exact(c, sc, kind, xs, x1s, dhat, req[kind], s);
+      if ((st != EIPC_OK && st != EIPC_ERR_CAPACITY) || c->scratch_short) return st;
+      if (st != EIPC_OK) out = st;
+    }
+    if (out != EIPC_OK || !after) return out;
+    const int32_t *lists[2] = {req[0].out, req[1].out};
+    const int64_t caps[2] = {req[0].n, req[1].n};
+    const int64_t *none[2] = {nullptr, nullptr};
+    Collect col;
+    c->collect_base = 0;
+    EIPC_TRY(after(lists, caps, none, col));
+    EIPC_TRY(launch_collect(c, col, s));
+    EIPC_HIP(c, hipStreamSynchronize(s));
+    return EIPC_OK;
+  }
+  for (int attempt = 0; attempt < 8; ++attempt) {
+    BPRun run[2];
+    FillList fl;
+    int32_t *list[2] = {nullptr, nullptr}, *slot[2] = {nullptr, nullptr}, *tmp[2] = {nullptr, nullptr},
+            *cnt[2] = {nullptr, nullptr};
+    int64_t cap[2] = {0, 0};
+    for (int kind = 0; kind < 2; ++kind) {
+      BPReq &q = req[kind];
+      BPRun &r = run[kind];
+      r = bp_run(sc, kind, xs, x1s, dhat, true);
+      if (r.nq == 0 || r.ni == 0) continue;
+      BPPlan &g = c->bp_guess[r.slot];
+      // about 4 to 8 cells per item at the default cell size
+      r.ent_cap = std::max<int64_t>(g.ent_cap, 8 * (int64_t)r.ni + 1024);
+      r.qent_cap = r.vhash ? std::max<int64_t>(g.qent_cap, 4 * (int64_t)r.nq + 1024) : 1;
+      r.nb = (uint32_t)hash_buckets(8 * (int64_t)r.ni);
+      cap[kind] = std::max<int64_t>(g.cand_cap, 4 * (int64_t)r.nq + 4096);
+      EIPC_TRY(bp_scratch(c, r));
+      bp_clear(r, fl, true, true);
+      if (q.sort) {
+        EIPC_TRY(ensure_t(c, B_SORT_LIST, (size_t)2 * cap[kind], &list[kind]));
+        EIPC_TRY(ensure_t(c, B_SORT_SLOT, (size_t)cap[kind], &slot[kind]));
+        EIPC_TRY(ensure_t(c, B_LQTMP, (size_t)cap[kind], &tmp[kind]));
+        EIPC_TRY(ensure_t(c, kind == 0 ? B_SORT_CNT_PT : B_SORT_CNT_EE, (size_t)r.nq, &cnt[kind]));
+        fl.add(cnt[kind], (sizeof(int32_t) * (size_t)r.nq + 7) & ~(size_t)7, 0);
+      } else {
+        EIPC_TRY(ensure_t(c, (BufId)q.grow_id, (size_t)2 * cap[kind], &list[kind]));
+      }
+    }
+    EIPC_TRY(launch_fill(c, fl, s));
+    Collect col;
+    for (int kind = 0; kind < 2; ++kind) {
+      BPReq &q = req[kind];
+      BPRun &r = run[kind];
+      if (r.nq == 0 || r.ni == 0) continue;
+      const BPScratch &b = r.b;
+      EIPC_TRY(bp_items(c, r, s));
+      EIPC_TRY(bp_cells(c, r, true, true, nullptr, b.flag, s));
+      EIPC_TRY(bp_entries(c, r, b.flag, s));
+      EIPC_TRY(bp_join(c, r, list[kind], cap[kind], b.total, s));
+      if (q.sort) {
+        ProfScope ps(c, kind == 0 ? K_QUERY_COUNT_PT : K_QUERY_COUNT_EE, s);
+        const int g = (int)std::min<int64_t>(grid_for(cap[kind], 256), 16 * (int64_t)c->num_cu);
+        const int2 *l2 = (const int2 *)list[kind];
+        k_sort_slot<<<g, 256, 0, s>>>(l2, b.total, cap[kind], cnt[kind], slot[kind]);
+        EIPC_HIP(c, hipGetLastError());
+        EIPC_TRY(exclusive_scan(c, cnt[kind], r.nq, b.qoff, s));
+        k_sort_gather<<<g, 256, 0, s>>>(l2, b.total, cap[kind], b.qoff, slot[kind], tmp[kind]);
+        EIPC_HIP(c, hipGetLastError());
+        k_sort_rank<<<g, 256, 0, s>>>(l2, b.total, cap[kind], b.qoff, tmp[kind], (int2 *)q.out, q.out ? q.cap : 0);
+        EIPC_HIP(c, hipGetLastError());
+      }
+      col.add(&b.g->bad, 4);
+      col.add(b.total, 8);
+      col.add(b.bstart + r.nb, 8);
+      col.add(r.vhash ? b.vbstart + r.nb : b.bstart, 8);
+    }
+    const int head = col.n;
+    if (after) {
+      const int32_t *lists[2] = {list[0], list[1]};
+      const int64_t *d_n[2] = {(const int64_t *)run[0].b.total, (const int64_t *)run[1].b.total};
+      EIPC_TRY(after(lists, cap, d_n, col));
+    }
+    EIPC_TRY(launch_collect(c, col, s));
+    EIPC_HIP(c, hipStreamSynchronize(s));
+    bool again = false, full = false;
+    int at = 0;
+    for (int kind = 0; kind < 2; ++kind) {
+      BPReq &q = req[kind];
+      BPRun &r = run[kind];
+      q.n = 0;
+      if (r.nq == 0 || r.ni == 0) {
+        c->last_plan[r.slot] = BPPlan{1024, 1, 0, 1};
+        continue;
+      }
+      const int64_t *w = c->host_res + at;
+      at += 4;
+      if (w[0]) {
+        EIPC_TRY(launch_zero(c, c->status, 4, s));  // reported here instead
+        return set_err(c, EIPC_ERR_NONFINITE, "non-finite primitive boxes");
+      }
+      const int64_t total = w[1], ent = std::max<int64_t>(w[2], 1), qent = r.vhash ? std::max<int64_t>(w[3], 1) : 1;
+      BPPlan &g = c->bp_guess[r.slot];
+      const bool cut = ent > r.ent_cap || qent > r.qent_cap;
+      if (ent > r.ent_cap) g.ent_cap = ent + ent / 4 + 1024;
+      if (qent > r.qent_cap) g.qent_cap = qent + qent / 4 + 1024;
+      if (total > cap[kind]) g.cand_cap = total + total / 4 + 1024;
+      again = again || cut || total > cap[kind];
+      q.n = total;
+      c->last_plan[r.slot] = BPPlan{(uint32_t)hash_buckets(ent), ent, total, qent};
+      if (!q.sort)
+        q.out = list[kind];
+      else if (total > q.cap)
+        full = true;
+    }
+    if (again) continue;
+    c->collect_base = head;
+    return full ? EIPC_ERR_CAPACITY : EIPC_OK;
+  }
+  return set_err(c, EIPC_ERR_CAPACITY, "candidate append did not converge");
 }
 
 // ---------------------------------------------------------------------------
@@ -1903,6 +2236,8 @@ __global__ void k_narrow(int64_t cap, const int64_t *d_n, const int32_t *__restr
   __shared__ int s_nact;
   __shared__ int64_t s_abase;
   const int64_t n = d_n ? (*d_n < cap ? *d_n : cap) : cap;
+  // a planned list that was cut
+  if (d_n && *d_n > cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(status, ST_PLAN_OVERFLOW);
   const int lane = threadIdx.x & 63;
   int64_t n_cand = 0;
   if (threadIdx.x == 0) s_nact = 0;
