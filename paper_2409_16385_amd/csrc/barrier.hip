@@ -8,6 +8,8 @@
 
 namespace eipc {
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 constexpr int BR_THREADS = 256;
 constexpr int LGT = 512;    // LDS node-vector table entries (14 KiB)
 constexpr int MAX_PROBE = 32;       // LDS tables (a miss falls back to the global table)
@@ -269,23 +271,43 @@ __device__ __forceinline__ void agg_scene_add(double *out, bool valid, int scene
 // Reduction through W (Eq. 17) of per-pair term records (gamma, X in the Q
 // basis; TERM_REC doubles per pair).
 //
-// A workgroup accumulates into LDS over a contiguous range of pairs in
-// locality order.  Nodes, not blocks, are looked up: a node's local index
-// is its slot in a small open-addressing table of LN slots (installed by
+// A contraction on the FP64 matrix cores.  With z_I = sum_{slots of node I}
+// w Q[a] (3 numbers per node and pair) a pair adds
+//   B(I, J)[r][c] += sum_{alpha, beta} z_I[alpha] X[3 alpha + r][3 beta + c] z_J[beta]
+// to the 3x3 block of its nodes I and J.  Pairs come in locality order: a run
+// of tens of them touches 16 nodes or fewer (47 to 94 pairs on the grasp).
+// A wavefront keeps a table of up to 16 nodes and, for each of the six (r, c)
+// with r <= c, the 16 x 16 matrix over (I, J) in four registers per lane;
+// four pairs are one product with K = (pair, alpha) = 12:
+//   C_rc += Z^T T_rc,  T_rc[(pair, alpha)][J] = sum_beta X z_J[beta],
+// three v_mfma_f64_16x16x4 for each (r, c) and three for the gradient.  Only
+// when a pair's nodes no longer fit the table do its blocks leave the
+// registers, for the workgroup's LDS accumulator.
+// The accumulator: nodes, not blocks, are looked up; a node's local index is
+// its slot in a small open-addressing table of LN slots (installed by
 // compare-and-swap), and the blocks of local nodes a <= b live in a dense
-// packed upper triangle of LN x LN 3x3 FP64 blocks addressed
-// arithmetically, the gradient in LN 3-vectors.  A node that finds no slot
-// (the table is full) goes straight to the outputs.  Between steps the
-// accumulator is flushed into the outputs once it holds more than LN / 2
-// nodes (each touched block once).
+// packed upper triangle of LN x LN 3x3 FP64 blocks addressed arithmetically,
+// the gradient in LN 3-vectors.  A node that finds no slot (the table is
+// full) goes straight to the outputs.  Between steps the accumulator is
+// flushed into the outputs once it holds more than LN / 2 nodes (each
+// touched block once).
+// What bounds it, 352,809 edge pairs of the grasp (310 us, 92,789 products,
+// 10,101 tables put out; 2,048 wavefronts at a time): 35% of a wavefront's
+// time in the products (21 instructions of 64 cycles each, shared by two
+// wavefronts), 20% in waits for records and rows of W, 15% at the barriers
+// of unequal runs, 8% in finding slots, 6% in putting tables out.  The
+// earlier form, one block per lane and 9 LDS atomics per block and pair (41
+// blocks a pair), was bound by those atomics at 37 cycles per wavefront
+// instruction: 405 us.
 // ---------------------------------------------------------------------------
 constexpr int EX_T = 512;                // eight wavefronts, two per SIMD
-constexpr int EX_PPG = 8;                // pairs per 16-lane group and step
-constexpr int EX_STEP = EX_T / 16 * EX_PPG;  // pairs per step (256)
-constexpr int LN = 60;                   // local node slots
-constexpr int LNB = LN * (LN + 1) / 2;   // their upper 3x3 blocks (129 KiB)
+constexpr int EX_W = EX_T / 64;
+constexpr int EX_PB = 4;                 // pairs per product
+constexpr int EX_STEP = EX_W * 128;      // pairs per step
+constexpr int EX_NS = 16;                // nodes of a wavefront's table
+constexpr int LN = 56;                   // local node slots
+constexpr int LNB = LN * (LN + 1) / 2;   // their upper 3x3 blocks (112 KiB)
 constexpr int LN_PROBE = 16;
-constexpr int EX_TRI = 16 * 17 / 2;      // blocks of a pair's (at most 16) merged nodes
 
 struct LocalAcc {
   int *nkey;               // LN: node of the slot, -1 = empty
@@ -333,346 +355,211 @@ __device__ __forceinline__ void local_init(const LocalAcc &L) {
   if (threadIdx.x == 0) *L.count = 0;
 }
 
-// All threads of the workgroup call (between barriers).
+// What a flush keeps in LDS meanwhile (in the wavefronts' staging, free
+// between barriers): the touched blocks and where they go.
+struct FlushList {
+  int64_t dst[LNB];   // kind 2: table slot; kind 1: I * n_node + J
+  uint16_t blk[LNB];  // local block | 0x8000: stored transposed to its rows
+  int n;
+};
+
+// All threads of the workgroup call (between barriers).  First the touched
+// blocks' global slots (table reads; a read issued after adds would wait for
+// all of them), then the adds with consecutive lanes on consecutive entries
+// of a block: the memory takes a wavefront's adds by the line, so that a
+// block's nine adds are two requests and not nine.
 __device__ __forceinline__ void local_flush(const LocalAcc &L, const HessOut &h, int n_node, double *grad,
-                                            uint32_t *status) {
-  // per thread up to FU blocks at a time: first their global slots (table
-  // reads), then their adds.  A table read issued after adds would wait
-  // for all of them: vector memory operations retire in order.
-  constexpr int FU = 4;
-  for (int base = 0; base < LNB; base += FU * (int)blockDim.x) {
-    int64_t dst[FU];  // kind 2: table slot; kind 1: I * n_node + J; -1: none
-    bool tr[FU];
-#pragma unroll
-    for (int u = 0; u < FU; ++u) {
-      const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
-      dst[u] = -1;
-      tr[u] = false;
-      if (idx < LNB && L.touched[idx]) {
-        // row a of the packed triangle: start(a) = a (2 LN - a + 1) / 2 <= idx
-        int a = (int)((2.0 * LN + 1.0 - sqrt((2.0 * LN + 1.0) * (2.0 * LN + 1.0) - 8.0 * idx)) * 0.5);
-        if (a < 0) a = 0;
-        while (a + 1 < LN && ltri(a + 1, a + 1) <= idx) ++a;
-        while (a > 0 && ltri(a, a) > idx) --a;
-        const int b = a + (idx - ltri(a, a));
-        const int na = L.nkey[a], nb = L.nkey[b];
-        tr[u] = na > nb;
-        const int64_t I = tr[u] ? nb : na, J = tr[u] ? na : nb;
-        if (h.kind == 1) {
-          dst[u] = I * n_node + J;
-        } else if (h.kind == 2) {
-          dst[u] = table_slot64((long long *)h.hkey, h.hmask, (long long)(I * n_node + J), GLOBAL_PROBE);
-          if (dst[u] < 0) atomicOr(status, ST_HASH_OVERFLOW);
-        }
-        if (dst[u] < 0) {
-#pragma unroll
-          for (int t = 0; t < 9; ++t) L.bval[9 * idx + t] = 0.0;
-          L.touched[idx] = 0;
-        }
-      }
+                                            uint32_t *status, FlushList &F) {
+  if (threadIdx.x == 0) F.n = 0;
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < LNB; idx += blockDim.x) {
+    if (!L.touched[idx]) continue;
+    // row a of the packed triangle: start(a) = a (2 LN - a + 1) / 2 <= idx
+    int a = (int)((2.0 * LN + 1.0 - sqrt((2.0 * LN + 1.0) * (2.0 * LN + 1.0) - 8.0 * idx)) * 0.5);
+    if (a < 0) a = 0;
+    while (a + 1 < LN && ltri(a + 1, a + 1) <= idx) ++a;
+    while (a > 0 && ltri(a, a) > idx) --a;
+    const int b = a + (idx - ltri(a, a));
+    const int na = L.nkey[a], nb = L.nkey[b];
+    const bool tr = na > nb;
+    const int64_t I = tr ? nb : na, J = tr ? na : nb;
+    int64_t dst = -1;
+    if (h.kind == 1) {
+      dst = I * n_node + J;
+    } else if (h.kind == 2) {
+      dst = table_slot64((long long *)h.hkey, h.hmask, (long long)(I * n_node + J), GLOBAL_PROBE);
+      if (dst < 0) atomicOr(status, ST_HASH_OVERFLOW);
     }
-#pragma unroll
-    for (int u = 0; u < FU; ++u) {
-      const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
-      if (dst[u] < 0) continue;
-      double B[9];
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) B[3 * r + c] = tr[u] ? L.bval[9 * idx + 3 * c + r] : L.bval[9 * idx + 3 * r + c];
+    L.touched[idx] = 0;
+    if (dst < 0) {
 #pragma unroll
       for (int t = 0; t < 9; ++t) L.bval[9 * idx + t] = 0.0;
-      L.touched[idx] = 0;
-      if (h.kind == 1) {
-        const int64_t n3 = 3 * (int64_t)n_node, I = dst[u] / n_node, J = dst[u] % n_node;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) atomicAdd(&h.dense[(3 * I + i) * n3 + 3 * J + j], B[3 * i + j]);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 9; ++t) atomicAdd(&h.hval[9 * dst[u] + t], B[t]);
-      }
+      continue;
     }
-  }
-  __syncthreads();  // nkey is read above and reset below
-  for (int li = threadIdx.x; li < LN; li += blockDim.x) {
-    const int node = L.nkey[li];
-    if (node >= 0 && grad) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) atomicAdd(&grad[3 * (int64_t)node + c], L.gval[3 * li + c]);
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) L.gval[3 * li + c] = 0.0;
-    L.nkey[li] = -1;
+    const int k = atomicAdd(&F.n, 1);
+    F.dst[k] = dst;
+    F.blk[k] = (uint16_t)(idx | (tr ? 0x8000 : 0));
   }
   __syncthreads();
+  const int ne = 9 * F.n;
+  for (int i = threadIdx.x; i < ne; i += blockDim.x) {
+    const int k = i / 9, e = i - 9 * k;
+    const int blk = F.blk[k], idx = blk & 0x7fff;
+    const int r = e / 3, c = e - 3 * r;
+    const int64_t dst = F.dst[k];
+    double *v = &L.bval[9 * idx + ((blk & 0x8000) ? 3 * c + r : e)];
+    if (h.kind == 1) {
+      const int64_t n3 = 3 * (int64_t)n_node, I = dst / n_node, J = dst % n_node;
+      atomicAdd(&h.dense[(3 * I + r) * n3 + 3 * J + c], *v);
+    } else {
+      atomicAdd(&h.hval[9 * dst + e], *v);
+    }
+    *v = 0.0;
+  }
+  for (int i = threadIdx.x; i < 3 * LN; i += blockDim.x) {
+    const int node = L.nkey[i / 3];
+    if (node >= 0 && grad) atomicAdd(&grad[3 * (int64_t)node + i % 3], L.gval[i]);
+    L.gval[i] = 0.0;
+  }
+  __syncthreads();  // nkey is read above and reset below
+  for (int li = threadIdx.x; li < LN; li += blockDim.x) L.nkey[li] = -1;
   if (threadIdx.x == 0) *L.count = 0;
 }
 
-__device__ __forceinline__ int permute_lane(int v, int dst) { return __builtin_amdgcn_ds_permute(dst << 2, v); }
-__device__ __forceinline__ double permute_lane(double v, int dst) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_ds_permute(dst << 2, (int)(unsigned)(b & 0xffffffffll));
-  const int hi = __builtin_amdgcn_ds_permute(dst << 2, (int)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// J with J(J+1)/2 <= t < (J+1)(J+2)/2, for 0 <= t < 256
-__device__ __forceinline__ int tri_root(int t) {
-  int J = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-  if (((J + 1) * (J + 2)) / 2 <= t) ++J;
-  if ((J * (J + 1)) / 2 > t) --J;
-  return J;
-}
-
-// The wavefront's pairs are held by lanes 16g + p, p < EX_PPG (pair i0 +
-// g EX_PPG + p, `own` when it exists) and taken in EX_PPG passes: in pass p
-// the sixteen lanes of group g (lanes 16g .. 16g+15) serve the pair of lane
-// 16g + p, lane s holding slot s = (vertex s / 4, weight s % 4): its node
-// and z_s = w_s Q[a] (3 numbers).
-// The slots are sorted by node (bitonic on the packed key node * 16 + s),
-// runs of equal nodes summed (the run's last lane keeps the total), and the
-// m distinct nodes packed in order onto lanes 0 .. m-1 of the group, which
-// look up their local indices.  Node I's gradient is sum_alpha z_I[alpha]
-// gamma_alpha; the merged nodes are staged in LDS and the m(m+1)/2 blocks
-// I <= J dealt to the group's lanes (block t on lane t mod 16, its (I, J)
-// from a table),
-//   B(I, J) = sum_{alpha, beta} z_I[alpha] z_J[beta] X[alpha][beta].
-// All 64 lanes call, in wavefront-uniform control flow.
-// A merged node of a pass, staged in LDS for the group's block lanes.
-struct NodeRec {
-  double z[3];
-  int node;  // NO_NODE past the group's m nodes
-  int li;    // local index, -1 = none
+// A wavefront's staging of one product's pairs.
+struct ExStage {
+  double x[EX_PB][54];          // [alpha][(r, c)][beta]
+  double g[EX_PB][9];           // gamma
+  double w[EX_PB][EX_NS][4];    // weight of (table slot, vertex)
 };
 
-// One block of the pass: B(I, J) = sum_{alpha, beta} z_I[alpha] z_J[beta]
-// X[alpha][beta] into the accumulator.  A local block holds the rows of the
-// lower local index: when that is J's, B(J, I) = B(I, J)^T is formed
-// directly by exchanging the two nodes' roles (X is symmetric), so no
-// element is picked by a run-time index.
-__device__ __forceinline__ void expand_block(const LocalAcc &L, const HessOut &h, int n_node, uint32_t *status,
-                                             const double *Xo, const NodeRec &RI, const NodeRec &RJ) {
-  const bool both = RI.li >= 0 && RJ.li >= 0;
-  const bool tr = both && RI.li > RJ.li;
-  double w[9];
-#pragma unroll
-  for (int al = 0; al < 3; ++al)
-#pragma unroll
-    for (int be = 0; be < 3; ++be) w[3 * al + be] = (tr ? RJ.z[al] : RI.z[al]) * (tr ? RI.z[be] : RJ.z[be]);
-  double B[9];
-#pragma unroll
-  for (int r = 0; r < 3; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int al = 0; al < 3; ++al)
-#pragma unroll
-        for (int be = 0; be < 3; ++be) acc += w[3 * al + be] * Xo[pidx(3 * al + r, 3 * be + c)];
-      B[3 * r + c] = acc;
-    }
-  if (both) {
-    const int slot = tr ? ltri(RJ.li, RI.li) : ltri(RI.li, RJ.li);
-#pragma unroll
-    for (int u = 0; u < 9; ++u) atomicAdd(&L.bval[9 * slot + u], B[u]);
-    L.touched[slot] = 1;
-  } else {
-    global_block_add(h, n_node, RI.node, RJ.node, B, status);
-  }
-}
+// (r, c) of the six products, r <= c
+__device__ __forceinline__ constexpr int ex_r(int k) { return k < 3 ? 0 : (k < 5 ? 1 : 2); }
+__device__ __forceinline__ constexpr int ex_c(int k) { return k < 3 ? k : (k < 5 ? k - 2 : 2); }
 
-__device__ __forceinline__ void expand_wave(const LocalAcc &L, const HessOut &h, int n_node, double *grad,
-                                            uint32_t *status, const int32_t *__restrict__ rowptr,
-                                            const int32_t *__restrict__ col, const double *__restrict__ val,
-                                            bool own, const int *vid, const double *__restrict__ rec, int64_t i0,
-                                            bool want_g, bool want_h, NodeRec *nstage,
-                                            const uint16_t *__restrict__ tri_ij) {
-  const int lane = threadIdx.x & 63;
-  const int s = lane & 15;
-  const int gbase = lane & ~15;
-  const int a = s >> 2, k = s & 3;
-  const uint64_t own_mask = __ballot(own);
-  // The slot data of pass p (row of the slot's vertex, then its node and
-  // weight) is loaded one and two passes ahead, so its latency hides behind
-  // the previous pass.
-  auto slot_vertex = [&](int p) {
-    const int owner = gbase + p;
-    const int v0 = __shfl(vid[0], owner, 64), v1 = __shfl(vid[1], owner, 64);
-    const int v2 = __shfl(vid[2], owner, 64), v3 = __shfl(vid[3], owner, 64);
-    return a == 0 ? v0 : (a == 1 ? v1 : (a == 2 ? v2 : v3));
-  };
-  int row_k0, row_n;  // row of pass p + 1
-  int cur_node = NO_NODE;
-  double cur_w = 0.0;  // slot of pass p
-  {
-    const int v = slot_vertex(0);
-    const int k0 = rowptr[v];
-    const int cnt = rowptr[v + 1] - k0;
-    if ((own_mask >> gbase) & 1ull && k < cnt) {
-      cur_node = col[k0 + k];
-      cur_w = val[k0 + k];
-    }
-    const int v1 = slot_vertex(1 < EX_PPG ? 1 : 0);
-    row_k0 = rowptr[v1];
-    row_n = rowptr[v1 + 1] - row_k0;
-  }
-  for (int p = 0; p < EX_PPG; ++p) {
-    // pairs fill the owner lanes in order: an empty pass ends the wavefront's work
-    if (((own_mask >> p) & 0x0001000100010001ull) == 0) break;
-    const int owner = gbase + p;
-    const bool active = (own_mask >> owner) & 1ull;
-    // the owner's terms (the sixteen lanes read the same record; a group
-    // without a pair reads the wavefront's first and ignores it)
-    const double2 *r2 =
-        (const double2 *)(rec + (i0 + (active ? (gbase >> 4) * EX_PPG + p : 0)) * TERM_REC);
-    double tv[54];
+// The wavefront's products into the workgroup's accumulator.  Lane (I = 4 e
+// + lane / 16, J = lane % 16) holds B(I, J)[r][c] for r <= c, which is also
+// B(J, I)[c][r]: of a stored block the lane whose row comes first adds the
+// six entries r <= c and the other the three below the diagonal.
+template <bool HESS>
+__device__ __forceinline__ void expand_out(const LocalAcc &L, const HessOut &h, int n_node, double *grad,
+                                           uint32_t *status, int tab, int cnt, uint32_t touched, const v4d *acc,
+                                           v4d accg, bool want_g) {
+  const int lane = threadIdx.x & 63, J = lane & 15;
+  const int li = local_index(L, tab, lane < cnt);  // lanes 0 .. 15
+  const int nJ = __shfl(tab, J, 64), lJ = __shfl(li, J, 64);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const double2 t2 = r2[q];
-      tv[2 * q] = t2.x;
-      tv[2 * q + 1] = t2.y;
+  for (int e = 0; e < 4; ++e) {
+    const int I = 4 * e + (lane >> 4);
+    const int nI = __shfl(tab, I, 64), lI = __shfl(li, I, 64);
+    const uint32_t tI = (uint32_t)__shfl((int)touched, I, 64);
+    if (want_g && I < cnt && J < 3) {
+      if (lI >= 0)
+        atomicAdd(&L.gval[3 * lI + J], accg[e]);
+      else
+        atomicAdd(&grad[3 * (int64_t)nI + J], accg[e]);
     }
-    if (want_h) {
+    if (!HESS || !((tI >> J) & 1u)) continue;
+    const bool both = lI >= 0 && lJ >= 0;
+    const bool up = both ? lI <= lJ : nI <= nJ, low = both ? lI >= lJ : nI >= nJ;  // both on the diagonal
+    if (both) {
+      const int slot = lI <= lJ ? ltri(lI, lJ) : ltri(lJ, lI);
+      double *B = L.bval + 9 * slot;
 #pragma unroll
-      for (int q = 5; q < 27; ++q) {
-        const double2 t2 = r2[q];
-        tv[2 * q] = t2.x;
-        tv[2 * q + 1] = t2.y;
+      for (int k = 0; k < 6; ++k) {
+        const int r = ex_r(k), c = ex_c(k);
+        if (up) atomicAdd(&B[3 * r + c], acc[k][e]);
+        if (low && r < c) atomicAdd(&B[3 * c + r], acc[k][e]);
       }
-    }
-    // prefetch: the slot of pass p + 1, the row of pass p + 2
-    int nxt_node = NO_NODE;
-    double nxt_w = 0.0;
-    if (p + 1 < EX_PPG) {
-      if ((own_mask >> (owner + 1)) & 1ull && k < row_n) {
-        nxt_node = col[row_k0 + k];
-        nxt_w = val[row_k0 + k];
-      }
-      if (p + 2 < EX_PPG) {
-        const int v2 = slot_vertex(p + 2);
-        row_k0 = rowptr[v2];
-        row_n = rowptr[v2 + 1] - row_k0;
-      }
-    }
-    int node = cur_node;
-    double z[3];
-#pragma unroll
-    for (int al = 0; al < 3; ++al) z[al] = 0.5 * (double)qsign(a, al) * cur_w;
-    cur_node = nxt_node;
-    cur_w = nxt_w;
-    // sort the group's slots by node: bitonic on the packed key node * 16 +
-    // slot (unique in the group, empty slots last), then each position
-    // takes its slot's z
-    uint32_t pk = node == NO_NODE ? (0xfffffff0u | (uint32_t)s) : (((uint32_t)node << 4) | (uint32_t)s);
-#pragma unroll
-    for (int kk = 2; kk <= 16; kk <<= 1)
-#pragma unroll
-      for (int j = kk >> 1; j > 0; j >>= 1) {
-        const uint32_t po = (uint32_t)__shfl_xor((int)pk, j, 64);
-        const bool up = (s & kk) == 0, low = (s & j) == 0;
-        const bool take = (low == up) ? (po < pk) : (po > pk);
-        pk = take ? po : pk;
-      }
-    node = (pk >> 4) == 0x0fffffffu ? NO_NODE : (int)(pk >> 4);
-    {
-      const int src = gbase + (int)(pk & 15u);
-#pragma unroll
-      for (int al = 0; al < 3; ++al) z[al] = __shfl(z[al], src, 64);
-    }
-    // sum runs of equal nodes; the run's last lane holds the total
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-      const int pn = __shfl_up(node, off, 16);
-      double pz[3];
-#pragma unroll
-      for (int al = 0; al < 3; ++al) pz[al] = __shfl_up(z[al], off, 16);
-      if (s >= off && pn == node) {
-#pragma unroll
-        for (int al = 0; al < 3; ++al) z[al] += pz[al];
-      }
-    }
-    const int nn = __shfl_down(node, 1, 16);
-    const bool mine = node != NO_NODE && (s == 15 || nn != node);
-    // pack the distinct nodes onto lanes 0..m-1 of the group, in order (a
-    // permutation of the group's lanes)
-    const uint32_t gm = (uint32_t)(__ballot(mine) >> gbase) & 0xffffu;
-    const int m = __popc(gm);
-    const int below = __popc(gm & ((1u << s) - 1u));
-    const int dst = gbase + (mine ? below : m + (s - below));
-    const int pnode = permute_lane(node, dst);
-    double cz[3];
-#pragma unroll
-    for (int al = 0; al < 3; ++al) cz[al] = permute_lane(z[al], dst);
-    const bool has = s < m;
-    const int cnode = has ? pnode : NO_NODE;
-    const int cli = local_index(L, cnode, has);
-    if (want_g && has) {
-      double g[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) g[c] = cz[0] * tv[c] + cz[1] * tv[3 + c] + cz[2] * tv[6 + c];
-      if (cli >= 0) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) atomicAdd(&L.gval[3 * cli + c], g[c]);
+      L.touched[slot] = 1;
+    } else {
+      const int64_t R = up ? nI : nJ, C = up ? nJ : nI;
+      double *B;
+      int64_t ld = 3;
+      if (h.kind == 1) {
+        ld = 3 * (int64_t)n_node;
+        B = h.dense + 3 * R * ld + 3 * C;
       } else {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) atomicAdd(&grad[3 * (int64_t)cnode + c], g[c]);
-      }
-    }
-    if (want_h) {
-      // the group's merged nodes go to its LDS stage (the previous pass's
-      // reads of it come first in the wavefront's program order)
-      NodeRec *ns = nstage + gbase;
-      if (has) {
-        NodeRec r;
-        r.z[0] = cz[0];
-        r.z[1] = cz[1];
-        r.z[2] = cz[2];
-        r.node = cnode;
-        r.li = cli;
-        ns[s] = r;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const double *Xo = tv + 9;
-      const int nb = (m * (m + 1)) >> 1;
-      for (int t0 = 0;; t0 += 16) {
-        const int t = t0 + s;
-        const bool vb = t < nb;
-        if (!__any(vb)) break;
-        if (vb) {
-          const uint32_t ij = tri_ij[t];
-          expand_block(L, h, n_node, status, Xo, ns[ij & 15u], ns[ij >> 8]);
+        const int64_t slot = table_slot64((long long *)h.hkey, h.hmask, (long long)(R * n_node + C), GLOBAL_PROBE);
+        if (slot < 0) {
+          atomicOr(status, ST_HASH_OVERFLOW);
+          continue;
         }
+        B = h.hval + 9 * slot;
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const int r = ex_r(k), c = ex_c(k);
+        if (up) atomicAdd(&B[r * ld + c], acc[k][e]);
+        if (low && r < c) atomicAdd(&B[c * ld + r], acc[k][e]);
       }
     }
   }
 }
 
-// Reduction of per-pair term records (pairs in locality order with their
-// vertex ids): a workgroup takes a contiguous range, 32 pairs per
-// wavefront and step.  Instantiated per pair kind (the code is the same)
-// so that the two launches of a step carry their own names in kernel
-// traces.
-template <int KIND>
-__global__ __launch_bounds__(EX_T) void k_expand(
+// A pair whose record is not finite, straight to the outputs and entry by
+// entry: in a product it would reach every node of the table (0 x Inf).  The
+// pair's 16 entries of W are nd and wv of 16 lanes from l0.
+template <bool HESS>
+__device__ __forceinline__ void expand_alone(const double *R, int nd, double wv, int l0, const HessOut &h, int n_node,
+                                             double *grad, uint32_t *status, bool want_g) {
+  const int lane = threadIdx.x & 63;
+  // Q = S / 2 with the Hadamard signs
+  auto Q = [](int a, int k) { return ((k != 1 && a >= 2) != (k != 0 && (a & 1))) ? -0.5 : 0.5; };
+  if (want_g && lane >= l0 && lane < l0 + 16 && nd >= 0) {
+    const int a = (lane & 15) >> 2;
+#pragma unroll 1
+    for (int r = 0; r < 3; ++r)
+      atomicAdd(&grad[3 * (int64_t)nd + r], wv * (Q(a, 0) * R[r] + Q(a, 1) * R[3 + r] + Q(a, 2) * R[6 + r]));
+  }
+  if (!HESS) return;
+#pragma unroll 1
+  for (int t = lane; t < 256; t += 64) {
+    const int p = t >> 4, q = t & 15;
+    const int64_t I = __shfl(nd, l0 + p, 64), J = __shfl(nd, l0 + q, 64);
+    const double wp = __shfl(wv, l0 + p, 64), wq = __shfl(wv, l0 + q, 64);
+    if (I < 0 || J < 0 || I > J) continue;
+    double *B;
+    int64_t ld = 3;
+    if (h.kind == 1) {
+      ld = 3 * (int64_t)n_node;
+      B = h.dense + 3 * I * ld + 3 * J;
+    } else {
+      const int64_t slot = table_slot64((long long *)h.hkey, h.hmask, (long long)(I * n_node + J), GLOBAL_PROBE);
+      if (slot < 0) {
+        atomicOr(status, ST_HASH_OVERFLOW);
+        continue;
+      }
+      B = h.hval + 9 * slot;
+    }
+#pragma unroll 1
+    for (int e = 0; e < 9; ++e) {
+      const int r = e / 3, c = e % 3;
+      double v = 0.0;
+#pragma unroll 1
+      for (int k = 0; k < 9; ++k) v += Q(p >> 2, k / 3) * R[9 + pidx(3 * (k / 3) + r, 3 * (k % 3) + c)] * Q(q >> 2, k % 3);
+      atomicAdd(&B[r * ld + c], wp * v * wq);
+    }
+  }
+}
+
+// Instantiated per pair kind (the code is the same) so that the two launches
+// of a step carry their own names in kernel traces.
+template <int KIND, bool HESS>
+__global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_expand(
     const int4 *__restrict__ vid4, const int64_t *__restrict__ d_count, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ col, const double *__restrict__ val, int n_node, const double *__restrict__ rec,
-    int64_t cap, bool want_g, bool want_h, double *grad, HessOut h, uint32_t *status) {
+    int64_t cap, bool want_g, double *grad, HessOut h, uint32_t *status) {
   __shared__ int s_nkey[LN];
   __shared__ double s_bval[LNB * 9];
   __shared__ double s_gval[LN * 3];
   __shared__ unsigned char s_touched[LNB];
   __shared__ int s_count;
-  __shared__ NodeRec s_nodes[EX_T];       // per wavefront: 4 groups x 16
-  __shared__ uint16_t s_tri[EX_TRI];      // block t -> I | J << 8, I <= J < 16
+  __shared__ union __align__(16) {
+    ExStage stage[EX_W];
+    FlushList flush;
+  } s_u;
   LocalAcc L{s_nkey, s_bval, s_touched, s_gval, &s_count};
-  for (int t = threadIdx.x; t < EX_TRI; t += blockDim.x) {
-    const int J = tri_root(t);
-    s_tri[t] = (uint16_t)((t - ((J * (J + 1)) >> 1)) | (J << 8));
-  }
   local_init(L);
   __syncthreads();
   // consecutive ranges on one XCD (workgroups are dealt to the 8 XCDs in turn)
@@ -682,25 +569,224 @@ __global__ __launch_bounds__(EX_T) void k_expand(
   const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 63) / 64 * 64;
   const int64_t r0 = (int64_t)rid * per;
   const int64_t r1 = r0 + per < n ? r0 + per : n;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // the wavefront's number as a scalar: its ranges and loops are then uniform
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  ExStage &S = s_u.stage[wave];
+  const int es = lane & 15, ea = es >> 2, ek = es & 3;  // this lane's (vertex, weight) of a pair
+  const int lk = lane >> 4;
+  // what this lane loads of a product's records: 216 entries of X in the
+  // staged order and 36 of gamma, by the pair and the place in its record
+  uint32_t xpr[4], xat[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int idx = lane + 64 * i < 54 * EX_PB ? lane + 64 * i : 0;
+    const int e = idx % 54, al = e / 18, k = (e % 18) / 3, be = e % 3;
+    const int u = 3 * al + (k < 3 ? 0 : (k < 5 ? 1 : 2)), v = 3 * be + (k < 3 ? k : (k < 5 ? k - 2 : 2));
+    xpr[i] = idx / 54;
+    xat[i] = 9 + pidx(u, v);
+  }
+  const uint32_t gpr = lane < 9 * EX_PB ? lane / 9 : 0, gat = lane % 9;
+  int tab = -1, cnt = 0;     // the table: lane l holds slot l % 16; nodes in it
+  uint32_t touched = 0;      // slots that share a pair with this lane's
+  v4d acc[6], accg;
+  auto clear = [&]() {
+    tab = -1;
+    cnt = 0;
+    touched = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[k] = v4d{0.0, 0.0, 0.0, 0.0};
+    accg = v4d{0.0, 0.0, 0.0, 0.0};
+  };
+  clear();
+  auto fence = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
   for (int64_t base = r0; base < r1; base += EX_STEP) {
-    const int64_t wb = base + 4 * EX_PPG * wave;
-    if (wb < r1) {
-      const int64_t i = wb + (lane >> 4) * EX_PPG + (lane & 15);
-      const bool live = (lane & 15) < EX_PPG && i < r1;
-      int vid[4] = {0, 0, 0, 0};
-      if (live) {
-        const int4 v4 = vid4[i];
-        vid[0] = v4.x;
-        vid[1] = v4.y;
-        vid[2] = v4.z;
-        vid[3] = v4.w;
+    // the step's pairs in equal runs over the wavefronts
+    const int left = (int)(r1 - base < EX_STEP ? r1 - base : EX_STEP);
+    const int run = (left + EX_W - 1) / EX_W;
+    const int p0 = run * wave < left ? run * wave : left;
+    const int p1 = p0 + run < left ? p0 + run : left;
+    const bool last_step = base + EX_STEP >= r1;
+    const int32_t *vids = reinterpret_cast<const int32_t *>(vid4 + base);
+    const double *recs = rec + base * TERM_REC;
+    // The vertex, its row of W and the row's entry are three dependent loads,
+    // each issued one product ahead of the next.  Every load is issued by
+    // every lane, at a place that is always there (a load under a condition
+    // ends the block, and with it the loads in flight).
+    // None of their results is touched before its product.
+    int vid = 0, rk = 0, rn = 0, node = 0;
+    bool has = false;
+    double wt = 0.0, xr[4] = {0.0, 0.0, 0.0, 0.0}, gr = 0.0;
+    auto load_vid = [&](int i) { vid = vids[4 * (uint32_t)(i + lk < p1 ? i + lk : p1 - 1) + ea]; };
+    auto load_row = [&]() {
+      rk = rowptr[vid];
+      rn = rowptr[vid + 1];
+    };
+    auto load_entry = [&](int i) {
+      has = i + lk < p1 && rk + ek < rn;
+      const int32_t *cp = has ? col + (rk + ek) : vids;
+      const double *vp = has ? val + (rk + ek) : recs;
+      node = *cp;
+      wt = *vp;
+    };
+    auto load_rec = [&](int i) {
+      const uint32_t most = (uint32_t)(p1 - 1 - i);  // pairs past the run: its last one, not used
+      const double *R = recs + (uint32_t)(TERM_REC * i);
+      if (HESS) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xr[k] = R[TERM_REC * (xpr[k] < most ? xpr[k] : most) + xat[k]];
       }
-      expand_wave(L, h, n_node, grad, status, rowptr, col, val, live, vid, rec, wb, want_g, want_h,
-                  s_nodes + 64 * wave, s_tri);
+      gr = R[TERM_REC * (gpr < most ? gpr : most) + gat];
+    };
+    if (p0 < p1) {
+      load_vid(p0);
+      load_row();
+      load_vid(p0 + EX_PB);
+      load_entry(p0);
+      load_row();
+      load_vid(p0 + 2 * EX_PB);
+      load_rec(p0);
+    }
+    int i0 = p0;           // the next product's first pair
+    uint32_t pending = 0;  // its pairs that are not taken yet
+    int nd = -1, slot = -1;
+    double wv = 0.0;
+    // one loop with one place where the table leaves the registers (code of
+    // that size more than once does not fit the instruction cache)
+    for (;;) {
+      if (pending == 0 && i0 < p1) {
+        const int np = p1 - i0 < EX_PB ? p1 - i0 : EX_PB;
+        uint32_t bad = 0;  // pairs whose records are not finite
+        {
+          uint32_t nf = fabs(gr) < INFINITY ? 0u : 1u << gpr;
+          if (HESS) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) nf |= fabs(xr[k]) < INFINITY ? 0u : 1u << xpr[k];
+          }
+          if (__any(nf != 0)) {
+#pragma unroll 1
+            for (int j = 0; j < EX_PB; ++j) bad |= __any((nf >> j) & 1u) ? 1u << j : 0u;
+            if (HESS) {
+#pragma unroll
+              for (int k = 0; k < 4; ++k) xr[k] = (bad >> xpr[k]) & 1u ? 0.0 : xr[k];
+            }
+            gr = (bad >> gpr) & 1u ? 0.0 : gr;
+          }
+        }
+        fence();  // the previous product has read its stage
+        if (HESS) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (lane + 64 * k < 54 * EX_PB) (&S.x[0][0])[lane + 64 * k] = xr[k];
+        }
+        if (lane < 9 * EX_PB) (&S.g[0][0])[lane] = gr;
+        nd = has ? node : -1;
+        wv = has ? wt : 0.0;
+        // in registers of their own before the next loads: copied after
+        // them, they would wait for them
+        asm volatile("" : "+v"(nd), "+v"(wv));
+        i0 += EX_PB;
+        load_entry(i0);
+        load_row();
+        load_vid(i0 + 2 * EX_PB);
+        load_rec(i0 < p1 ? i0 : p1 - 1);
+        pending = (1u << np) - 1u;
+        if (bad != 0) {
+#pragma unroll 1
+          for (uint32_t b = bad & pending; b != 0; b &= b - 1) {
+            const int j = __ffs(b) - 1;
+            expand_alone<HESS>(recs + (int64_t)TERM_REC * (i0 - EX_PB + j), nd, wv, 16 * j, h, n_node, grad, status,
+                               want_g);
+          }
+          if ((bad >> lk) & 1u) nd = -1;
+          pending &= ~bad;
+          if (pending == 0) continue;
+        }
+        slot = -1;
+#pragma unroll
+        for (int j = 0; j < EX_NS; ++j) slot = nd == __builtin_amdgcn_readlane(tab, j) ? j : slot;
+        if (nd < 0) slot = -1;
+      }
+      // pairs in order, as long as their nodes fit the table
+      uint32_t take = pending;
+      int pj = -1, c_before = 0;
+      for (uint64_t mm; (mm = __ballot(nd >= 0 && slot < 0)) != 0;) {
+        const int l = __builtin_ctzll(mm);
+        if ((l >> 4) != pj) {
+          pj = l >> 4;
+          c_before = cnt;
+        }
+        if (cnt == EX_NS) {  // give back what this pair took
+          if (es >= c_before) tab = -1;
+          if (slot >= c_before) slot = -1;
+          cnt = c_before;
+          take &= (1u << pj) - 1u;
+          break;
+        }
+        const int nn = __builtin_amdgcn_readlane(nd, l);
+        if (es == cnt) tab = nn;
+        if (nd == nn) slot = cnt;
+        ++cnt;
+      }
+      if (take == 0) {
+        // the table is full (an empty one holds any pair's 16 nodes), or the
+        // run is done
+        if (pending == 0 && !last_step) break;  // the next step goes on with this table
+        expand_out<HESS>(L, h, n_node, grad, status, tab, cnt, touched, acc, accg, want_g);
+        clear();
+        slot = -1;
+        if (pending == 0) break;
+        continue;
+      }
+      pending &= ~take;
+      const bool mine = nd >= 0 && ((take >> lk) & 1u);
+      fence();
+      {
+        double2 *w2 = reinterpret_cast<double2 *>(&S.w[0][0][0]);
+        w2[lane] = double2{0.0, 0.0};
+        w2[lane + 64] = double2{0.0, 0.0};
+      }
+      fence();
+      if (mine) atomicAdd(&S.w[lk][slot][ea], wv);
+      fence();
+      // nodes that share a pair: the pair's slots, over its 16 lanes
+      int m = mine ? 1 << slot : 0;
+      m |= __builtin_amdgcn_update_dpp(0, m, 0x128, 0xf, 0xf, false);  // row_ror:8
+      m |= __builtin_amdgcn_update_dpp(0, m, 0x124, 0xf, 0xf, false);  // row_ror:4
+      m |= __builtin_amdgcn_update_dpp(0, m, 0x122, 0xf, 0xf, false);  // row_ror:2
+      m |= __builtin_amdgcn_update_dpp(0, m, 0x121, 0xf, 0xf, false);  // row_ror:1
+#pragma unroll
+      for (int j = 0; j < EX_PB; ++j) {
+        const uint32_t mj = (uint32_t)__builtin_amdgcn_readlane(m, 16 * j);
+        touched |= (mj >> es) & 1u ? mj : 0u;
+      }
+      if (mine) nd = -1;
+#pragma unroll
+      for (int st = 0; st < 3; ++st) {
+        const int ka = 4 * st + lk, pr = ka / 3, al = ka - 3 * pr;
+        const double *w = S.w[pr][es];
+        const double w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+        // Q = S / 2 with the Hadamard signs
+        const double z0 = 0.5 * ((w0 + w1) - (w2 + w3)), z1 = 0.5 * ((w0 - w1) + (w2 - w3)),
+                     z2 = 0.5 * ((w0 - w1) - (w2 - w3));
+        const double za = al == 0 ? z0 : (al == 1 ? z1 : z2);
+        if (HESS) {
+          const double *x = S.x[pr] + 18 * al;
+          double t[6];
+#pragma unroll
+          for (int k = 0; k < 6; ++k) t[k] = x[3 * k] * z0 + x[3 * k + 1] * z1 + x[3 * k + 2] * z2;
+#pragma unroll
+          for (int k = 0; k < 6; ++k) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(za, t[k], acc[k], 0, 0, 0);
+        }
+        const double t = es < 3 ? S.g[pr][3 * al + es] : 0.0;
+        accg = __builtin_amdgcn_mfma_f64_16x16x4f64(za, t, accg, 0, 0, 0);
+      }
     }
     __syncthreads();
-    if (base + EX_STEP >= r1 || s_count > LN / 2) local_flush(L, h, n_node, want_g ? grad : nullptr, status);
+    if (base + EX_STEP >= r1 || s_count > LN / 2) local_flush(L, h, n_node, want_g ? grad : nullptr, status, s_u.flush);
     __syncthreads();
   }
 }
@@ -717,18 +803,23 @@ __global__ __launch_bounds__(EX_T) void k_expand(
 __device__ __forceinline__ int wave_key_add(int *ctr, int key, bool valid) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
-  int res = 0;
+  // group the lanes first, then one atomic instruction for all groups (an
+  // atomic inside the loop waits once per distinct key)
+  int leader_of = lane, rank = 0, count = 0;
   uint64_t pending = __ballot(valid);
   while (pending) {
     const int leader = __ffsll((unsigned long long)pending) - 1;
-    const int lk = __shfl(key, leader, 64);
+    const int lk = __builtin_amdgcn_readlane(key, __builtin_amdgcn_readfirstlane(leader));
     const uint64_t m = __ballot(valid && key == lk) & pending;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&ctr[lk], __popcll(m));
-    base = __shfl(base, leader, 64);
-    if ((m >> lane) & 1ull) res = base + __popcll(m & lt);
+    if ((m >> lane) & 1ull) {
+      leader_of = leader;
+      rank = __popcll(m & lt);
+    }
+    if (lane == leader) count = __popcll(m);
     pending &= ~m;
   }
+  const int base = count > 0 ? atomicAdd(&ctr[key], count) : 0;
+  const int res = __shfl(base, leader_of, 64) + rank;
   return res;
 }
 
@@ -1073,12 +1164,21 @@ eipc_status launch_expand(eipc_ctx *c, const eipc_scene *sc, int kind, const int
   const int blocks =
       (int)std::max<int64_t>(1, std::min<int64_t>(grid_for(cap, 64), (int64_t)c->wg_per_cu[1] * c->num_cu));
   ProfScope ps(c, kind == 0 ? K_EXPAND_PT : K_EXPAND_EE, s);
-  if (kind == 0)
-    k_expand<0><<<blocks, EX_T, 0, s>>>(vid4, d_count, sc->W_rowptr, sc->W_col, sc->W_val, sc->n_node, rec, cap,
-                                        want_g, want_h, grad, h, c->status);
-  else
-    k_expand<1><<<blocks, EX_T, 0, s>>>(vid4, d_count, sc->W_rowptr, sc->W_col, sc->W_val, sc->n_node, rec, cap,
-                                        want_g, want_h, grad, h, c->status);
+#define EX_CALL(KIND, H)                                                                                              \
+  k_expand<KIND, H><<<blocks, EX_T, 0, s>>>(vid4, d_count, sc->W_rowptr, sc->W_col, sc->W_val, sc->n_node, rec, cap, \
+                                            want_g, grad, h, c->status)
+  if (kind == 0) {
+    if (want_h)
+      EX_CALL(0, true);
+    else
+      EX_CALL(0, false);
+  } else {
+    if (want_h)
+      EX_CALL(1, true);
+    else
+      EX_CALL(1, false);
+  }
+#undef EX_CALL
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
