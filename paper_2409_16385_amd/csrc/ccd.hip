@@ -118,14 +118,14 @@ __global__ __launch_bounds__(256) void k_ccd(int64_t cap, const int64_t *d_n, co
 // minimum comes out the same, bit for bit.
 constexpr int64_t CCD_SHORT = 4;
 
-template <int KIND, int PASS>
-__global__ __launch_bounds__(256) void k_ccd2(int64_t cap, const int64_t *d_n, const int32_t *__restrict__ pairs,
+template <int KIND>
+__global__ __launch_bounds__(256) void k_ccd_short(int64_t cap, const int64_t *d_n, const int32_t *__restrict__ pairs,
                        const int32_t *__restrict__ faces, const int32_t *__restrict__ edges,
                        const double *__restrict__ xs, const double *__restrict__ ps, int n_vert, double sfac,
                        double t_max, int64_t max_iter, unsigned long long *alpha_bits, int32_t *__restrict__ longl,
                        int64_t *n_long, const int32_t *__restrict__ vscene, int n_scene, uint32_t *status,
                        bool dir) {
-  const int64_t n = PASS == 0 ? (d_n ? (*d_n < cap ? *d_n : cap) : cap) : (*n_long < cap ? *n_long : cap);
+  const int64_t n = d_n ? (*d_n < cap ? *d_n : cap) : cap;
   const int lane = threadIdx.x & 63;
   bool capped = false;
   // each workgroup walks a contiguous range of the list: a scene's pairs
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(256) void k_ccd2(int64_t cap, const int64_t *d_n, c
     int scene = 0;
     bool decided = false, deferred = false;
     if (live) {
-      const int64_t k = PASS == 0 ? i : (int64_t)longl[i];
-      const int a = pairs[2 * k], b = pairs[2 * k + 1];
+      const int a = pairs[2 * i], b = pairs[2 * i + 1];
       int vid[4];
       if (KIND == 0) {
         vid[0] = a;
@@ -165,7 +164,7 @@ __global__ __launch_bounds__(256) void k_ccd2(int64_t cap, const int64_t *d_n, c
       AccdState st;
       st.dir = dir;
       const double cut = scene_cut(alpha_bits, scene, n_scene, t_max, max_iter);
-      const int64_t lim = PASS == 0 ? (CCD_SHORT < max_iter ? CCD_SHORT : max_iter) : max_iter;
+      const int64_t lim = CCD_SHORT < max_iter ? CCD_SHORT : max_iter;
       const int r = accd_run_cut<KIND>(x, p, t_max, max_iter, cut, lim, st,
                                        accd_init_cut<KIND>(x, p, sfac, t_max, cut, st, false, 0.0));
       if (r == ACCD_DONE) {
@@ -173,9 +172,9 @@ __global__ __launch_bounds__(256) void k_ccd2(int64_t cap, const int64_t *d_n, c
         capped = st.it >= max_iter;
       }
       decided = r != ACCD_OPEN;  // a dropped pair keeps t = t_max
-      deferred = !decided;       // pass 0 only: more than CCD_SHORT steps
+      deferred = !decided;       // more than CCD_SHORT steps
     }
-    if (PASS == 0) {
+    {
       const uint64_t dm = __ballot(deferred);
       if (dm) {
         int64_t p0 = 0;
@@ -190,20 +189,93 @@ __global__ __launch_bounds__(256) void k_ccd2(int64_t cap, const int64_t *d_n, c
   if (__any(capped) && lane == 0) atomicOr(status, ST_CCD_CAPPED);
 }
 
+// Pass 1.  A pair's steps are one serial chain (a squared distance, a root
+// and a division each), so the pass takes as long as its longest pair that
+// is not dropped.  Hence, of a short list, few pairs or one to a wavefront:
+// 64 pairs of different closest features walk each other's branches at every
+// step.  And a pair's bound is published when it is reached, not at the end
+// of its wavefront, and read again every CCD_CUT steps (issued before them,
+// used after them: the read takes about as long): pairs that would go on past
+// the minimum stop there.  A wavefront's pairs are adjacent in the list.
+// 332 edge pairs of the plate, the least bound after 108 steps and the
+// longest run 250: 414 us with 64 to a wavefront and no second look at the
+// bound, 212 like this.  From n_wave pairs on a wavefront has as many as it
+// takes to hold them all at once, up to its 64 lanes.
+constexpr int CCD_CUT = 4;
+
+template <int KIND>
+__global__ __launch_bounds__(256) void k_ccd_long(int64_t cap, const int32_t *__restrict__ pairs,
+                       const int32_t *__restrict__ faces, const int32_t *__restrict__ edges,
+                       const double *__restrict__ xs, const double *__restrict__ ps, double sfac, double t_max,
+                       int64_t max_iter, unsigned long long *alpha_bits, const int32_t *__restrict__ longl,
+                       const int64_t *n_long, const int32_t *__restrict__ vscene, int n_scene, uint32_t *status,
+                       bool dir) {
+  const int64_t n = *n_long < cap ? *n_long : cap;
+  const int lane = threadIdx.x & 63;
+  const int64_t n_wave = (int64_t)gridDim.x * (blockDim.x >> 6);
+  const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int64_t most = (n + n_wave - 1) / n_wave, per = most < 64 ? most : 64;
+  bool capped = false;
+  for (int64_t base = wave * per; base < n; base += n_wave * per) {
+    const int64_t i = base + lane;
+    if (lane >= per || i >= n) continue;
+    const int64_t k = longl[i];
+    const int a = pairs[2 * k], b = pairs[2 * k + 1];
+    int vid[4];
+    if (KIND == 0) {
+      vid[0] = a;
+      vid[1] = faces[3 * (int64_t)b];
+      vid[2] = faces[3 * (int64_t)b + 1];
+      vid[3] = faces[3 * (int64_t)b + 2];
+    } else {
+      vid[0] = edges[2 * (int64_t)a];
+      vid[1] = edges[2 * (int64_t)a + 1];
+      vid[2] = edges[2 * (int64_t)b];
+      vid[3] = edges[2 * (int64_t)b + 1];
+    }
+    const int scene = vscene ? vscene[vid[0]] : 0;
+    V3 x[4], p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ld_pos(xs, vid[q], x[q].x, x[q].y, x[q].z);
+      ld_pos(ps, vid[q], p[q].x, p[q].y, p[q].z);
+    }
+    const bool known = (unsigned)scene < (unsigned)n_scene;
+    if (!known) atomicOr(status, ST_BAD_SCENE);
+    AccdState st;
+    st.dir = dir;
+    double cut = scene_cut(alpha_bits, scene, n_scene, t_max, max_iter);
+    int r = accd_init_cut<KIND>(x, p, sfac, t_max, cut, st, false, 0.0);
+    while (r == ACCD_OPEN) {
+      const unsigned long long next =
+          __hip_atomic_load(&alpha_bits[known ? scene : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t lim = max_iter - st.it < CCD_CUT ? max_iter : st.it + CCD_CUT;
+      r = accd_run_cut<KIND>(x, p, t_max, max_iter, cut, lim, st, r);
+      if (known && max_iter >= 1) cut = fmin(cut, __longlong_as_double((long long)next));
+    }
+    if (r == ACCD_DONE) {
+      capped = capped || st.it >= max_iter;
+      const unsigned long long tb = (unsigned long long)__double_as_longlong(st.t);
+      if (known && tb < (unsigned long long)__double_as_longlong(cut)) atomicMin(&alpha_bits[scene], tb);
+    }
+  }
+  if (__any(capped) && lane == 0) atomicOr(status, ST_CCD_CAPPED);
+}
+
 // Narrow phase and step-bound pass 0 in one sweep over the swept
 // candidates (the planned step with a step bound): each pair's vertices are
 // loaded once; the candidate predicate at x and, for the pairs passing it,
 // the distance and activity test (active pairs staged per workgroup and
 // appended to act/typ with one atomic per flush) come first, then
-// advancement as in k_ccd2 pass 0,
+// advancement as in k_ccd_short,
 // reusing the distance just computed.  The pass-1 list is the same.
-// The PT form is held to three waves per SIMD (168 VGPRs, no spill); the EE
-// form runs at two, where its 189 VGPRs fit without spilling (at three it
-// spilled 68 bytes per lane and was 8 % slower).
+// Both forms run at three waves per SIMD (168 VGPRs, no spill).  Bound by the
+// reads of positions: 6.1 million edge pairs of the grasp in 198 us, 232
+// bytes each, 7 TB/s out of the caches.
 constexpr int NCCD_BUF = 1024;  // staged active pairs per workgroup
 
 template <int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == 0 ? 3 : 2))) void k_narrow_ccd(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_narrow_ccd(
     int64_t cap, const int64_t *d_n, const int32_t *__restrict__ pairs, const int32_t *__restrict__ faces,
     const int32_t *__restrict__ edges, const double *__restrict__ xs, const double *__restrict__ ps, double dhat2,
     double h, int32_t *__restrict__ act, int32_t *__restrict__ typ, int64_t act_cap, int64_t *count,
@@ -377,11 +449,11 @@ eipc_status launch_ccd_long(eipc_ctx *c, const eipc_scene *sc, int kind, const d
   unsigned long long *ab = (unsigned long long *)d_alpha_bits;
   ProfScope prof(c, kind == 0 ? K_CCD_LONG_PT : K_CCD_LONG_EE, s);
   if (kind == 0)
-    k_ccd2<0, 1><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
-                                        max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
+    k_ccd_long<0><<<blocks, 256, 0, s>>>(n, pairs, sc->faces, sc->edges, xs, ps, sfac, t_max, max_iter, ab, longl,
+                                         n_long, vsc, nsc, c->status, c->ccd_method == 1);
   else
-    k_ccd2<1, 1><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
-                                        max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
+    k_ccd_long<1><<<blocks, 256, 0, s>>>(n, pairs, sc->faces, sc->edges, xs, ps, sfac, t_max, max_iter, ab, longl,
+                                         n_long, vsc, nsc, c->status, c->ccd_method == 1);
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
@@ -400,15 +472,15 @@ eipc_status launch_ccd(eipc_ctx *c, const eipc_scene *sc, int kind, const double
     EIPC_TRY(ensure_t(c, kind == 0 ? B_CCD_LONG_PT : B_CCD_LONG_EE, (size_t)n, &longl));
     unsigned long long *ab = (unsigned long long *)d_alpha_bits;
     if (kind == 0) {
-      k_ccd2<0, 0><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
+      k_ccd_short<0><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
                                           max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
-      k_ccd2<0, 1><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
-                                          max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
+      k_ccd_long<0><<<blocks, 256, 0, s>>>(n, pairs, sc->faces, sc->edges, xs, ps, sfac, t_max, max_iter, ab, longl,
+                                           n_long, vsc, nsc, c->status, c->ccd_method == 1);
     } else {
-      k_ccd2<1, 0><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
+      k_ccd_short<1><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
                                           max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
-      k_ccd2<1, 1><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max,
-                                          max_iter, ab, longl, n_long, vsc, nsc, c->status, c->ccd_method == 1);
+      k_ccd_long<1><<<blocks, 256, 0, s>>>(n, pairs, sc->faces, sc->edges, xs, ps, sfac, t_max, max_iter, ab, longl,
+                                           n_long, vsc, nsc, c->status, c->ccd_method == 1);
     }
   } else if (kind == 0)
     k_ccd<0><<<blocks, 256, 0, s>>>(n, d_n, pairs, sc->faces, sc->edges, xs, ps, sc->n_vert, sfac, t_max, max_iter,
