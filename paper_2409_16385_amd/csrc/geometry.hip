@@ -1052,8 +1052,13 @@ __global__ __launch_bounds__(QT) void k_query(int nq, const double *__restrict__
 // that one huge box does not keep a single thread scanning thousands of
 // cells.  MODE 0 counts each query's candidates into cnt[q]; MODE 1 writes
 // them, unsorted, to tmp at the query's offset (k_seg_rank then puts them
-// in order into out); MODE 2 appends them to out (staged per lane).
+// in order into out); MODE 2 appends them to out (staged per lane), with a
+// short list's queries in up to LQ_PARTS parts, a wavefront each: one
+// wavefront to each of the 10 large edges of a sheet took 62 us, most of it
+// waits for one group of loads after the other; 9 us in 32 parts each.
 // ---------------------------------------------------------------------------
+constexpr int LQ_PARTS = 32;
+
 template <int KIND, int MODE>
 __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qlist, const int64_t *__restrict__ n_qlist,
                                                  const double *__restrict__ xs, const double *__restrict__ x1s,
@@ -1069,8 +1074,10 @@ __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qli
   const int n_large = (int)*qa_.n_large;
   const int64_t nl = *n_qlist;
   const int64_t nw = ((int64_t)gridDim.x * QT) >> 6;
-  for (int64_t w = ((int64_t)blockIdx.x * QT + threadIdx.x) >> 6; w < nl; w += nw) {
-    const int q = qlist[w];
+  int parts = 1;
+  while (MODE == 2 && parts < LQ_PARTS && nl * (2 * parts) <= nw) parts *= 2;
+  for (int64_t w = ((int64_t)blockIdx.x * QT + threadIdx.x) >> 6; w < nl * parts; w += nw) {
+    const int q = qlist[w / parts], part = (int)(w % parts);
     double qlo[3], qhi[3];
     int qa, qb, qsc;
     bool qdof;
@@ -1088,7 +1095,7 @@ __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qli
     // this lane's share: cells lane, lane + 64, ..., then large items alike
     auto each = [&](auto emit) {
       if (all_items) {
-        for (int i0 = 0; i0 < qa_.n_items; i0 += 256) {
+        for (int i0 = 256 * part; i0 < qa_.n_items; i0 += 256 * parts) {
           ItemRec r[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
@@ -1106,7 +1113,7 @@ __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qli
         }
         return;
       }
-      for (int64_t ci = lane; ci < nc; ci += 64) {
+      for (int64_t ci = 64 * part + lane; ci < nc; ci += 64 * parts) {
         const int x = c0[0] + (int)(ci % nx), y = c0[1] + (int)((ci / nx) % ny), z = c0[2] + (int)(ci / (nx * ny));
         const uint64_t key = cell_key(x, y, z, qsc);
         const uint32_t b = cell_hash(x, y, z, qsc) & qa_.bmask;
@@ -1114,7 +1121,7 @@ __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qli
         scan_bucket<KIND>(qa_.ent, items, qa_.bstart[b], e1, key, x, y, z, c0[0], c0[1], c0[2], q, qa, qb, qdof,
                           qlo, qhi, emit);
       }
-      for (int j = lane; j < n_large; j += 64) {
+      for (int j = 64 * part + lane; j < n_large; j += 64 * parts) {
         const int it = qa_.large[j];
         const ItemRec r = items[it];
         if ((r.tag >> 1) == qsc && pair_ok<KIND>(q, qa, qb, qdof, it, r) && overlap(qlo, qhi, r)) emit(it);
@@ -1468,7 +1475,7 @@ __global__ __launch_bounds__(QT) void k_query_sm(int nq, const double *__restric
 // Bucket join (work split 3).  The queries are hashed like the items (PT:
 // vertex records in a second hash over the same grid and buckets; EE: the
 // edge hash itself), so every (query, item) pair that shares a cell lies in
-// one bucket of both hashes.  A workgroup takes JT consecutive query
+// one bucket of both hashes.  A workgroup takes tiles of consecutive query
 // entries (rows, in bucket order); the item entries of the buckets those
 // rows touch form one contiguous window of the item hash, staged in LDS in
 // chunks of JWIN entries together with their records.  Each row then tests
@@ -1479,11 +1486,30 @@ __global__ __launch_bounds__(QT) void k_query_sm(int nq, const double *__restric
 // it, wrapping to the bucket's start), so that every unordered pair of the
 // bucket is tested once, and reports (min, max).  The row that is a query's lower cell also runs the
 // items too large to hash, as in the per-query splits; queries too large
-// to hash run per query (k_query_sm on a list).
+// to hash run per query (k_query_lq).
 // ---------------------------------------------------------------------------
-constexpr int JT = 128;     // rows per workgroup
+constexpr int JT = 128;     // threads of a workgroup
 constexpr int JWIN = 192;   // item entries staged in LDS per chunk (five workgroups per CU)
 constexpr int JOUT = 1024;  // candidates staged per wavefront
+// Lanes to a row (log2; PT, EE): a row's partners are taken in turn by 4 or
+// 2 lanes, and by up to 2^JSPLIT in a list so short that its rows would not
+// fill the chip (below JSWG workgroups per CU).  A wavefront goes on for its
+// longest row, and with few rows to it the rows of one bucket, of one
+// length, are together: grasp (19.0 and 44.9 million tests) PT 148 us with
+// one lane to a row, 104 with two, 92 with four, 131 with eight; EE 244 and
+// 194 with one and two; the sphere's 5,072 PT rows 93 us and, with eight, 18;
+// plate PT 100 and 68, but EE 107 and 121 (21 partners a row on average).
+constexpr int JLANES[2] = {2, 1};
+constexpr int JSPLIT = 3;
+constexpr int JSWG[2] = {10, 5};
+// A workgroup takes every gridDim-th tile, at most JWG workgroups per CU,
+// and adds to the counter once at its end: with a workgroup to a tile and an
+// add for each wavefront, the adds to that one address (7.5 ns each) took
+// half of the batch's 959 us (62,072 wavefronts; now 569).  More workgroups
+// add more often, fewer leave uneven tiles: 10, 20 and 40 to a CU, edges:
+// candidates of the grasp 118, 117 and 165 us, its step 212, 199 and 195,
+// plate 97, 108 and 123, batch 623, 569 and 558.
+constexpr int JWG = 20;
 
 struct JoinArgs {
   const Entry *rows;        // query entries in bucket order
@@ -1529,12 +1555,13 @@ __device__ __forceinline__ bool join_test(const ItemRec &r, int qa, int qb, bool
 }
 
 template <int KIND>
-__global__ __launch_bounds__(JT) void k_join(JoinArgs ja, int32_t *__restrict__ out, int64_t cap,
+__global__ __launch_bounds__(JT) void k_join(JoinArgs ja, int64_t split_rows, int32_t *__restrict__ out, int64_t cap,
                                              unsigned long long *total) {
   __shared__ Entry s_ent[JWIN];
   __shared__ ItemRec s_rec[JWIN];
   __shared__ int2 s_out[JT / 64][JOUT];
   __shared__ int64_t s_win[2];
+  __shared__ int s_left[JT / 64];
   int2 *wout = s_out[threadIdx.x >> 6];
   int wcnt = 0;
   const int64_t nr0 = *ja.n_rows;
@@ -1542,142 +1569,161 @@ __global__ __launch_bounds__(JT) void k_join(JoinArgs ja, int32_t *__restrict__ 
   // wavefront's stores, which kept finished wavefronts resident
   const int nl = (int)*ja.n_large;
   const int64_t n_rows = nr0 < ja.row_cap ? nr0 : ja.row_cap;
-  const int64_t r0 = (int64_t)blockIdx.x * JT;
-  if (r0 >= n_rows) return;  // uniform over the workgroup
-  const int64_t r1 = r0 + JT < n_rows ? r0 + JT : n_rows;
-  const int64_t i = r0 + threadIdx.x;
-  const bool live = i < r1;
-  // the row: its entry, bucket, record and partner range
-  Entry re{0, 0, 0};
-  // partners: the entries [pa0, pa1) and then [pb0, pb1) of the row's
-  // bucket [bs, be).  PT: the whole bucket.  EE: the next h entries after
-  // the row, cyclically (wrapping to the bucket's start), with h = (n - 1)
-  // / 2 for a bucket of n entries, plus one for the first half of an even
-  // bucket (its partner n / 2 ahead): every unordered pair of the bucket
-  // once, and every row about half the bucket, where scanning all later
-  // entries left the first rows of a bucket with all of it.
-  int64_t pa0 = 0, pa1 = 0, pb0 = 0, pb1 = 0, bs = 0, be = 0;
-  double qlo[3] = {0, 0, 0}, qhi[3] = {0, 0, 0};
-  int qa = 0, qb = -1, qsc = 0;
-  bool qdof = false;
-  if (live) {
-    re = ja.rows[i];
-    const uint32_t b = key_bucket(re.cell, ja.bmask);
-    const int64_t e0 = ja.pbstart[b], e1 = ja.pbstart[b + 1];
-    be = e1 < ja.pent_cap ? e1 : ja.pent_cap;
-    bs = e0 < be ? e0 : be;
-    if (KIND == 0) {
-      pa0 = bs;
-      pa1 = be;
-    } else {
-      const int64_t n = be - bs, pos = i - bs;
-      const int64_t h = (n - 1) / 2 + ((n % 2 == 0 && pos < n / 2) ? 1 : 0);
-      pa0 = i + 1;
-      pa1 = i + 1 + h < be ? i + 1 + h : be;
-      pb0 = bs;
-      pb1 = bs + (i + 1 + h - be > 0 ? i + 1 + h - be : 0);
-    }
-    const ItemRec qr = ja.qrec[re.item];
-    qa = qr.v[0];
-    qb = qr.v[1];
-    qdof = qr.tag & 1;
-    qsc = qr.tag >> 1;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      qlo[a] = qr.lo[a];
-      qhi[a] = qr.hi[a];
-    }
-  }
-  // window of item entries for the whole tile: first row's bucket start to
-  // last row's bucket end (rows are in bucket order)
-  const int rmask = nonzero_fields(re.dlo);
-  if (threadIdx.x == 0) s_win[0] = bs;
-  if (i == r1 - 1) s_win[1] = be;
-  __syncthreads();
-  const int64_t w0 = s_win[0], w1 = s_win[1];
-  for (int64_t c0 = w0; c0 < w1; c0 += JWIN) {
-    const int nw = (int)(w1 - c0 < JWIN ? w1 - c0 : JWIN);
-    __syncthreads();  // previous chunk consumed
-    {
-      constexpr int U = (JWIN + JT - 1) / JT;
-      Entry e[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = u * JT + threadIdx.x;
-        if (k < nw) e[u] = ja.pent[c0 + k];
+  int sp = JLANES[KIND];
+  while (sp < JSPLIT && n_rows << (sp + 1) <= split_rows) ++sp;
+  const int rt = JT >> sp, sub = threadIdx.x & ((1 << sp) - 1), step = 1 << sp;
+  for (int64_t r0 = (int64_t)blockIdx.x * rt; r0 < n_rows; r0 += (int64_t)gridDim.x * rt) {  // uniform
+    const int64_t r1 = r0 + rt < n_rows ? r0 + rt : n_rows;
+    const int64_t i = r0 + (threadIdx.x >> sp);
+    const bool live = i < r1;
+    // the row: its entry, bucket, record and partner range
+    Entry re{0, 0, 0};
+    // partners: the entries [pa0, pa1) and then [pb0, pb1) of the row's
+    // bucket [bs, be).  PT: the whole bucket.  EE: the next h entries after
+    // the row, cyclically (wrapping to the bucket's start), with h = (n - 1)
+    // / 2 for a bucket of n entries, plus one for the first half of an even
+    // bucket (its partner n / 2 ahead): every unordered pair of the bucket
+    // once, and every row about half the bucket, where scanning all later
+    // entries left the first rows of a bucket with all of it.
+    int64_t pa0 = 0, pa1 = 0, pb0 = 0, pb1 = 0, bs = 0, be = 0;
+    double qlo[3] = {0, 0, 0}, qhi[3] = {0, 0, 0};
+    int qa = 0, qb = -1, qsc = 0;
+    bool qdof = false;
+    if (live) {
+      re = ja.rows[i];
+      const uint32_t b = key_bucket(re.cell, ja.bmask);
+      const int64_t e0 = ja.pbstart[b], e1 = ja.pbstart[b + 1];
+      be = e1 < ja.pent_cap ? e1 : ja.pent_cap;
+      bs = e0 < be ? e0 : be;
+      if (KIND == 0) {
+        pa0 = bs;
+        pa1 = be;
+      } else {
+        const int64_t n = be - bs, pos = i - bs;
+        const int64_t h = (n - 1) / 2 + ((n % 2 == 0 && pos < n / 2) ? 1 : 0);
+        pa0 = i + 1;
+        pa1 = i + 1 + h < be ? i + 1 + h : be;
+        pb0 = bs;
+        pb1 = bs + (i + 1 + h - be > 0 ? i + 1 + h - be : 0);
       }
+      const ItemRec qr = ja.qrec[re.item];
+      qa = qr.v[0];
+      qb = qr.v[1];
+      qdof = qr.tag & 1;
+      qsc = qr.tag >> 1;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = u * JT + threadIdx.x;
-        if (k < nw) {
-          s_ent[k] = e[u];
-          s_rec[k] = ja.items[e[u].item];
-        }
+      for (int a = 0; a < 3; ++a) {
+        qlo[a] = qr.lo[a];
+        qhi[a] = qr.hi[a];
       }
     }
+    // window of item entries for the whole tile: first row's bucket start to
+    // last row's bucket end (rows are in bucket order)
+    const int rmask = nonzero_fields(re.dlo);
+    __syncthreads();  // the previous tile's window is read
+    if (threadIdx.x == 0) s_win[0] = bs;
+    if (i == r1 - 1) s_win[1] = be;
     __syncthreads();
-    // this chunk's part of the two partner ranges, taken as one list
-    const int64_t cend = c0 + nw;
-    const int64_t a0 = pa0 > c0 ? pa0 : c0, a1 = pa1 < cend ? pa1 : cend;
-    const int64_t b0 = pb0 > c0 ? pb0 : c0, b1 = pb1 < cend ? pb1 : cend;
-    // chunk-relative: the list's entry tu is ra + tu below na, else rb + tu
-    const int na = a1 > a0 ? (int)(a1 - a0) : 0;
-    const int ntot = na + (b1 > b0 ? (int)(b1 - b0) : 0);
-    const int ra = (int)(a0 - c0), rb = (int)(b0 - c0) - na;
-    int t = 0;
-    while (__any(t < ntot)) {
-      // four partners per lane: their entries and records read from LDS
-      // without conditions (a conditional read kept the previous records
-      // live in registers: ~45 copies per step and 200 VGPRs), then the
-      // same-cell and lower-corner rule and the pair test
-      Entry pe[4];
-      bool pass[4];
-      int idx[4];
+    const int64_t w0 = s_win[0], w1 = s_win[1];
+    for (int64_t c0 = w0; c0 < w1; c0 += JWIN) {
+      const int nw = (int)(w1 - c0 < JWIN ? w1 - c0 : JWIN);
+      __syncthreads();  // previous chunk consumed
+      {
+        constexpr int U = (JWIN + JT - 1) / JT;
+        Entry e[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int tu = t + u;
-        idx[u] = tu < ntot ? (tu < na ? ra : rb) + tu : 0;
-        pe[u] = s_ent[idx[u]];
-      }
-      ItemRec r[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) r[u] = s_rec[idx[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        pass[u] = (t + u < ntot) & (pe[u].cell == re.cell) & ((pe[u].dlo & rmask) == 0);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        // & rather than &&: the test is branch-free, a short circuit would branch
-        const bool ok = pass[u] & join_test<KIND>(r[u], qa, qb, qdof, qlo, qhi);
-        const int it = pe[u].item;
-        const int2 pr = (KIND == 0 || re.item < it) ? make_int2(re.item, it) : make_int2(it, re.item);
-        wave_push(ok, pr, wout, wcnt);
-      }
-      t += 4;
-      if (wcnt > JOUT - 4 * 64) wave_out_flush(wout, wcnt, total, out, cap);
-    }
-  }
-  // the query's lower-cell row also runs the items too large to hash
-  if (nl > 0) {
-    const bool lower = live && re.dlo == 0;
-    const int q = re.item;
-    for (int jb = 0; __any(lower && jb < nl); jb += 4) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int jj = jb + u;
-        bool ok = false;
-        int it = 0;
-        if (lower && jj < nl) {
-          it = ja.large[jj];
-          const ItemRec r = ja.items[it];
-          ok = ((r.tag >> 1) == qsc) & pair_ok<KIND>(q, qa, qb, qdof, it, r) & overlap(qlo, qhi, r);
+        for (int u = 0; u < U; ++u) {
+          const int k = u * JT + threadIdx.x;
+          if (k < nw) e[u] = ja.pent[c0 + k];
         }
-        wave_push(ok, make_int2(q, it), wout, wcnt);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = u * JT + threadIdx.x;
+          if (k < nw) {
+            s_ent[k] = e[u];
+            s_rec[k] = ja.items[e[u].item];
+          }
+        }
       }
-      if (wcnt > JOUT - 4 * 64) wave_out_flush(wout, wcnt, total, out, cap);
+      __syncthreads();
+      // this chunk's part of the two partner ranges, taken as one list
+      const int64_t cend = c0 + nw;
+      const int64_t a0 = pa0 > c0 ? pa0 : c0, a1 = pa1 < cend ? pa1 : cend;
+      const int64_t b0 = pb0 > c0 ? pb0 : c0, b1 = pb1 < cend ? pb1 : cend;
+      // chunk-relative: the list's entry tu is ra + tu below na, else rb + tu
+      const int na = a1 > a0 ? (int)(a1 - a0) : 0;
+      const int ntot = na + (b1 > b0 ? (int)(b1 - b0) : 0);
+      const int ra = (int)(a0 - c0), rb = (int)(b0 - c0) - na;
+      int t = sub;
+      while (__any(t < ntot)) {
+        // four partners per lane (the lanes of a row take them in turn): their entries and records read from LDS
+        // without conditions (a conditional read kept the previous records
+        // live in registers: ~45 copies per step and 200 VGPRs), then the
+        // same-cell and lower-corner rule and the pair test
+        Entry pe[4];
+        bool pass[4];
+        int idx[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int tu = t + u * step;
+          idx[u] = tu < ntot ? (tu < na ? ra : rb) + tu : 0;
+          pe[u] = s_ent[idx[u]];
+        }
+        ItemRec r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = s_rec[idx[u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          pass[u] = (t + u * step < ntot) & (pe[u].cell == re.cell) & ((pe[u].dlo & rmask) == 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          // & rather than &&: the test is branch-free, a short circuit would branch
+          const bool ok = pass[u] & join_test<KIND>(r[u], qa, qb, qdof, qlo, qhi);
+          const int it = pe[u].item;
+          const int2 pr = (KIND == 0 || re.item < it) ? make_int2(re.item, it) : make_int2(it, re.item);
+          wave_push(ok, pr, wout, wcnt);
+        }
+        t += 4 * step;
+        if (wcnt > JOUT - 4 * 64) wave_out_flush(wout, wcnt, total, out, cap);
+      }
+    }
+    // the query's lower-cell row also runs the items too large to hash
+    if (nl > 0) {
+      const bool lower = live && re.dlo == 0;
+      const int q = re.item;
+      for (int jb = sub; __any(lower && jb < nl); jb += 4 * step) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int jj = jb + u * step;
+          bool ok = false;
+          int it = 0;
+          if (lower && jj < nl) {
+            it = ja.large[jj];
+            const ItemRec r = ja.items[it];
+            ok = ((r.tag >> 1) == qsc) & pair_ok<KIND>(q, qa, qb, qdof, it, r) & overlap(qlo, qhi, r);
+          }
+          wave_push(ok, make_int2(q, it), wout, wcnt);
+        }
+        if (wcnt > JOUT - 4 * 64) wave_out_flush(wout, wcnt, total, out, cap);
+      }
     }
   }
-  wave_out_flush(wout, wcnt, total, out, cap);
+  // what is left, with one atomic for the workgroup
+  if ((threadIdx.x & 63) == 0) s_left[threadIdx.x >> 6] = wcnt;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < JT / 64; ++w) {
+    before += w < (int)(threadIdx.x >> 6) ? s_left[w] : 0;
+    all += s_left[w];
+  }
+  if (all == 0) return;
+  if (threadIdx.x == 0) s_win[0] = (int64_t)atomicAdd(total, (unsigned long long)all);
+  __syncthreads();
+  const int64_t p0 = s_win[0] + before;
+  int2 *o2 = reinterpret_cast<int2 *>(out);
+  for (int k = threadIdx.x & 63; k < wcnt; k += 64)
+    if (p0 + k < cap) o2[p0 + k] = wout[k];
 }
 
 static BPRun bp_run(const eipc_scene *sc, int kind, const double *xs, const double *x1s, double dhat, bool join) {
@@ -1804,6 +1850,11 @@ static eipc_status bp_large(eipc_ctx *c, const BPRun &r, const int32_t *list, co
   return EIPC_OK;
 }
 
+// workgroups of a join over at most row_cap rows
+static int join_grid(eipc_ctx *c, int64_t row_cap) {
+  return (int)std::min<int64_t>(grid_for(row_cap << JSPLIT, JT), (int64_t)JWG * c->num_cu);
+}
+
 // the bucket join of a built hash, appended to out (*total counts past cap)
 static eipc_status bp_join(eipc_ctx *c, const BPRun &r, int32_t *out, int64_t cap, unsigned long long *total,
                            hipStream_t s) {
@@ -1812,13 +1863,13 @@ static eipc_status bp_join(eipc_ctx *c, const BPRun &r, int32_t *out, int64_t ca
   if (r.kind == 0) {
     const JoinArgs ja{reinterpret_cast<const Entry *>(b.qent), b.vbstart + r.nb, r.qent_cap, b.vrec, b.bstart, b.ent,
                       r.ent_cap, b.items, b.large, b.n_large, r.nb - 1};
-    k_join<0><<<grid_for(r.qent_cap, JT), JT, 0, s>>>(ja, out, cap, total);
+    k_join<0><<<join_grid(c, r.qent_cap), JT, 0, s>>>(ja, (int64_t)JSWG[r.kind] * c->num_cu * JT, out, cap, total);
     EIPC_HIP(c, hipGetLastError());
     return bp_large(c, r, b.qlarge, b.n_qlarge, out, cap, total, s);
   }
   const JoinArgs ja{b.ent, b.bstart + r.nb, r.ent_cap, b.items, b.bstart, b.ent, r.ent_cap, b.items, b.large,
                     b.n_large, r.nb - 1};
-  k_join<1><<<grid_for(r.ent_cap, JT), JT, 0, s>>>(ja, out, cap, total);
+  k_join<1><<<join_grid(c, r.ent_cap), JT, 0, s>>>(ja, (int64_t)JSWG[r.kind] * c->num_cu * JT, out, cap, total);
   EIPC_HIP(c, hipGetLastError());
   return bp_large(c, r, b.large, b.n_large, out, cap, total, s);
 }
