@@ -210,8 +210,10 @@ __device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t *smem, int
 // Up to two scans side by side (grid y).  Arrays of up to SCAN_ONE entries:
 // one launch, one workgroup each.  Larger ones: two launches over at most
 // SCAN_BLOCKS ranges; the second sums the ranges before its own itself (at
-// most four loads a thread), so no launch between them scans the sums.
-constexpr int64_t SCAN_ONE = 32768;
+// most four loads a thread), so no launch between them scans the sums.  One workgroup
+// takes 5 us for one pass of 8,192 entries and 34 for four of them, the two
+// launches 9.5 us for 32,768.
+constexpr int64_t SCAN_ONE = 8192;
 constexpr int SCAN_BLOCKS = 1024;
 struct ScanArgs {
   const int32_t *in[2];
@@ -571,7 +573,33 @@ __device__ __forceinline__ void big_cell(const int *c0, const int *c1, int c, in
 // count (histogram) or reserves the bucket's range (fill).  An entry whose
 // probe finds neither its bucket nor a free slot within LT_PROBE steps goes
 // to the global counters directly; its bucket then never enters the table.
-constexpr int LT_T = 256;       // items per workgroup
+// Threads to an item (Q), which take its cells in turn, and items to a
+// workgroup.  Short lists leave the chip idle with one thread to an item,
+// its cells one chain of table lookups: with four, the fill of the sphere 54
+// and 20 us, of a sheet 76 and 29 (both launches), of the grasp (825
+// workgroups of 256 items) 157 and 104, its candidates 733 and 632 us as a
+// whole.  Where the chip is full they only add divisions: the batch (above
+// 4,000 workgroups) 271 and 409 us.
+constexpr int lt_items(int q) { return q == 1 ? 256 : 128; }
+constexpr int lt_threads(int q) { return q * lt_items(q); }
+constexpr int LT_FEW = 4;       // four threads to an item below this many workgroups of 256 items per CU
+
+// the cells of [c0, c1] that thread sub of Q takes
+template <int Q, class F>
+__device__ __forceinline__ void each_cell(const int *c0, const int *c1, int nc, int sub, F &&f) {
+  if constexpr (Q == 1) {
+    for (int z = c0[2]; z <= c1[2]; ++z)
+      for (int y = c0[1]; y <= c1[1]; ++y)
+        for (int x = c0[0]; x <= c1[0]; ++x) f(x, y, z);
+  } else {
+    for (int c = sub; c < nc; c += Q) {
+      int x, y, z;
+      big_cell(c0, c1, c, x, y, z);
+      f(x, y, z);
+    }
+  }
+}
+
 constexpr int LT_SLOTS = 2048;  // LDS table slots
 constexpr int LT_PROBE = 32;
 
@@ -622,19 +650,20 @@ struct HSides {
 // A first launch counts the cells and lists big and large records (count)
 // and counts the entries per bucket (hist): one pass, or two where the
 // number of buckets has to follow the number of entries.
-__global__ __launch_bounds__(LT_T) void k_cells(HSides hs, const uint64_t *st, int n_items, double cell_scale,
+template <int Q>
+__global__ __launch_bounds__(lt_threads(Q)) void k_cells(HSides hs, const uint64_t *st, int n_items, double cell_scale,
                                                 GridDev *gp, uint32_t bmask, bool count, bool hist, int64_t *n_ent,
                                                 uint32_t *status) {
   __shared__ uint32_t s_key[LT_SLOTS];
   __shared__ int32_t s_cnt[LT_SLOTS];
   __shared__ GridDev s_g;
   __shared__ double s_stat[9];
-  __shared__ int s_big[LT_T];
+  __shared__ int s_big[lt_items(Q)];
   __shared__ int s_nbig, s_ent;
   const bool second = (int)blockIdx.x >= hs.blocks0;
   const HSide &h = hs.s[second ? 1 : 0];
   if (hist)
-    for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T) {
+    for (int k = threadIdx.x; k < LT_SLOTS; k += lt_threads(Q)) {
       s_key[k] = 0u;
       s_cnt[k] = 0;
     }
@@ -653,7 +682,7 @@ __global__ __launch_bounds__(LT_T) void k_cells(HSides hs, const uint64_t *st, i
   }
   __syncthreads();
   const GridDev g = s_g;
-  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * LT_T + threadIdx.x;
+  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * lt_items(Q) + threadIdx.x / Q, sub = threadIdx.x % Q;
   if (i < h.n) {
     int c0[3], c1[3];
     cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
@@ -662,7 +691,7 @@ __global__ __launch_bounds__(LT_T) void k_cells(HSides hs, const uint64_t *st, i
     // non-finite boxes: nothing is hashed (the error is reported)
     const bool small = nc <= MAX_ITEM_CELLS && !g.bad;
     const bool big = !small && sx <= 64 && sy <= 64 && sz <= 64 && nc <= BIG_CELLS && !g.bad;
-    if (count) {
+    if (count && sub == 0) {
       h.cnt[i] = small ? (int32_t)nc : 0;
       if (big) {
         const int slot = (int)atomicAdd((unsigned long long *)&h.n_big[0], 1ull);
@@ -673,30 +702,28 @@ __global__ __launch_bounds__(LT_T) void k_cells(HSides hs, const uint64_t *st, i
       }
       if (n_ent && small) atomicAdd(&s_ent, (int)nc);
     }
-    if (hist && big) s_big[atomicAdd(&s_nbig, 1)] = i;
+    if (hist && big && sub == 0) s_big[atomicAdd(&s_nbig, 1)] = i;
     if (hist && small) {
       const int sc = h.rec[i].tag >> 1;
-      for (int z = c0[2]; z <= c1[2]; ++z)
-        for (int y = c0[1]; y <= c1[1]; ++y)
-          for (int x = c0[0]; x <= c1[0]; ++x) {
-            const uint32_t b = cell_hash(x, y, z, sc) & bmask;
-            const int t = lt_insert(s_key, b);
-            if (t >= 0)
-              atomicAdd(&s_cnt[t], 1);
-            else
-              atomicAdd(&h.bcnt[b], 1);
-          }
+      each_cell<Q>(c0, c1, (int)nc, sub, [&](int x, int y, int z) {
+        const uint32_t b = cell_hash(x, y, z, sc) & bmask;
+        const int t = lt_insert(s_key, b);
+        if (t >= 0)
+          atomicAdd(&s_cnt[t], 1);
+        else
+          atomicAdd(&h.bcnt[b], 1);
+      });
     }
   }
   __syncthreads();
   if (n_ent && threadIdx.x == 0 && s_ent)
     atomicAdd((unsigned long long *)&n_ent[second ? 1 : 0], (unsigned long long)s_ent);
   if (!hist) return;
-  for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T)
+  for (int k = threadIdx.x; k < LT_SLOTS; k += lt_threads(Q))
     if (s_key[k] != 0u) atomicAdd(&h.bcnt[s_key[k] - 1u], s_cnt[k]);
   // the workgroup's big records: a wavefront each, adds that return nothing
   const int lane = threadIdx.x & 63;
-  for (int w = threadIdx.x >> 6; w < s_nbig; w += LT_T / 64) {
+  for (int w = threadIdx.x >> 6; w < s_nbig; w += lt_threads(Q) / 64) {
     const int ib = s_big[w];
     const int sc = h.rec[ib].tag >> 1;
     int c0[3], c1[3];
@@ -720,26 +747,28 @@ struct Entry {
 
 // Places the entries: a bucket's count is taken down from its end, so the
 // counters need no second array and end at zero.
-__global__ __launch_bounds__(LT_T) void k_item_fill(HSides hs, const GridDev *__restrict__ gp, uint32_t bmask,
+template <int Q>
+__global__ __launch_bounds__(lt_threads(Q)) void k_item_fill(HSides hs, const GridDev *__restrict__ gp, uint32_t bmask,
                                                     uint32_t *status) {
   __shared__ uint32_t s_key[LT_SLOTS];
   __shared__ int32_t s_cnt[LT_SLOTS];
   __shared__ int32_t s_base[LT_SLOTS];
   const bool second = (int)blockIdx.x >= hs.blocks0;
   const HSide &h = hs.s[second ? 1 : 0];
-  for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T) {
+  for (int k = threadIdx.x; k < LT_SLOTS; k += lt_threads(Q)) {
     s_key[k] = 0u;
     s_cnt[k] = 0;
   }
   __syncthreads();
-  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * LT_T + threadIdx.x;
+  const int i = (blockIdx.x - (second ? hs.blocks0 : 0)) * lt_items(Q) + threadIdx.x / Q, sub = threadIdx.x % Q;
   const bool live = i < h.n && h.cnt[i] != 0;
   GridDev g;
-  int sc = 0, c0[3] = {0, 0, 0}, c1[3] = {-1, -1, -1};
+  int sc = 0, nc = 0, c0[3] = {0, 0, 0}, c1[3] = {-1, -1, -1};
   if (live) {
     g = *gp;
     sc = h.rec[i].tag >> 1;
     cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
+    nc = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
   }
   auto put = [&](int64_t slot, int x, int y, int z) {
     if (slot < h.ent_cap) {
@@ -754,29 +783,25 @@ __global__ __launch_bounds__(LT_T) void k_item_fill(HSides hs, const GridDev *__
   };
   // count per bucket in LDS (entries that find no slot take their global
   // slot now)
-  for (int z = c0[2]; z <= c1[2]; ++z)
-    for (int y = c0[1]; y <= c1[1]; ++y)
-      for (int x = c0[0]; x <= c1[0]; ++x) {
-        const uint32_t b = cell_hash(x, y, z, sc) & bmask;
-        const int t = lt_insert(s_key, b);
-        if (t >= 0)
-          atomicAdd(&s_cnt[t], 1);
-        else
-          put(h.bstart[b] + atomicSub(&h.bcnt[b], 1) - 1, x, y, z);
-      }
+  each_cell<Q>(c0, c1, nc, sub, [&](int x, int y, int z) {
+    const uint32_t b = cell_hash(x, y, z, sc) & bmask;
+    const int t = lt_insert(s_key, b);
+    if (t >= 0)
+      atomicAdd(&s_cnt[t], 1);
+    else
+      put(h.bstart[b] + atomicSub(&h.bcnt[b], 1) - 1, x, y, z);
+  });
   __syncthreads();
   // reserve each bucket's range once
-  for (int k = threadIdx.x; k < LT_SLOTS; k += LT_T)
+  for (int k = threadIdx.x; k < LT_SLOTS; k += lt_threads(Q))
     if (s_key[k] != 0u) s_base[k] = atomicSub(&h.bcnt[s_key[k] - 1u], s_cnt[k]) - s_cnt[k];
   __syncthreads();
   // place: rank within the workgroup's range from the LDS count
-  for (int z = c0[2]; z <= c1[2]; ++z)
-    for (int y = c0[1]; y <= c1[1]; ++y)
-      for (int x = c0[0]; x <= c1[0]; ++x) {
-        const uint32_t b = cell_hash(x, y, z, sc) & bmask;
-        const int t = lt_find(s_key, b);
-        if (t >= 0) put(h.bstart[b] + s_base[t] + atomicSub(&s_cnt[t], 1) - 1, x, y, z);
-      }
+  each_cell<Q>(c0, c1, nc, sub, [&](int x, int y, int z) {
+    const uint32_t b = cell_hash(x, y, z, sc) & bmask;
+    const int t = lt_find(s_key, b);
+    if (t >= 0) put(h.bstart[b] + s_base[t] + atomicSub(&s_cnt[t], 1) - 1, x, y, z);
+  });
 }
 
 // big records, one wavefront each (grid y: the side)
@@ -1785,17 +1810,22 @@ static void bp_clear(const BPRun &r, FillList &fl, bool small, bool buckets) {
   }
 }
 
-static HSides bp_sides(const BPRun &r) {
+// threads to an item in the launches over items and records
+static int bp_side_threads(const eipc_ctx *c, const BPRun &r) {
+  return grid_for((int64_t)r.ni + (r.vhash ? r.nq : 0), 256) < LT_FEW * c->num_cu ? 4 : 1;
+}
+
+static HSides bp_sides(const BPRun &r, int q) {
   const BPScratch &b = r.b;
   HSides h{};
   h.s[0] = HSide{r.ni, b.items, b.cnt, b.large, b.n_large, b.big, b.n_big, b.bcnt, b.bstart, b.ent, r.ent_cap};
   h.s[1] = HSide{r.vhash ? r.nq : 0, b.vrec,  b.qcnt,    b.qlarge, b.n_qlarge, b.qbig,
                  b.n_qbig,           b.vbcnt, b.vbstart, reinterpret_cast<Entry *>(b.qent), r.qent_cap};
-  h.blocks0 = grid_for(r.ni, LT_T);
+  h.blocks0 = grid_for(r.ni, lt_items(q));
   return h;
 }
-static unsigned bp_side_blocks(const BPRun &r) {
-  return (unsigned)(grid_for(r.ni, LT_T) + (r.vhash ? grid_for(r.nq, LT_T) : 0));
+static unsigned bp_side_blocks(const BPRun &r, int q) {
+  return (unsigned)(grid_for(r.ni, lt_items(q)) + (r.vhash ? grid_for(r.nq, lt_items(q)) : 0));
 }
 
 static eipc_status bp_items(eipc_ctx *c, const BPRun &r, hipStream_t s) {
@@ -1814,8 +1844,14 @@ static eipc_status bp_items(eipc_ctx *c, const BPRun &r, hipStream_t s) {
 
 static eipc_status bp_cells(eipc_ctx *c, const BPRun &r, bool count, bool hist, int64_t *n_ent, uint32_t *status,
                             hipStream_t s) {
-  k_cells<<<bp_side_blocks(r), LT_T, 0, s>>>(bp_sides(r), r.b.st, r.ni, c->cell_scale, r.b.g, r.nb - 1, count, hist,
-                                             n_ent, status);
+  const int q = bp_side_threads(c, r);
+  const HSides h = bp_sides(r, q);
+  if (q == 4)
+    k_cells<4><<<bp_side_blocks(r, 4), lt_threads(4), 0, s>>>(h, r.b.st, r.ni, c->cell_scale, r.b.g, r.nb - 1, count,
+                                                              hist, n_ent, status);
+  else
+    k_cells<1><<<bp_side_blocks(r, 1), lt_threads(1), 0, s>>>(h, r.b.st, r.ni, c->cell_scale, r.b.g, r.nb - 1, count,
+                                                              hist, n_ent, status);
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
@@ -1824,8 +1860,12 @@ static eipc_status bp_cells(eipc_ctx *c, const BPRun &r, bool count, bool hist, 
 static eipc_status bp_entries(eipc_ctx *c, const BPRun &r, uint32_t *status, hipStream_t s) {
   const BPScratch &b = r.b;
   EIPC_TRY(exclusive_scan2(c, b.bcnt, r.nb, b.bstart, r.vhash ? b.vbcnt : nullptr, r.nb, b.vbstart, s));
-  const HSides h = bp_sides(r);
-  k_item_fill<<<bp_side_blocks(r), LT_T, 0, s>>>(h, b.g, r.nb - 1, status);
+  const int q = bp_side_threads(c, r);
+  const HSides h = bp_sides(r, q);
+  if (q == 4)
+    k_item_fill<4><<<bp_side_blocks(r, 4), lt_threads(4), 0, s>>>(h, b.g, r.nb - 1, status);
+  else
+    k_item_fill<1><<<bp_side_blocks(r, 1), lt_threads(1), 0, s>>>(h, b.g, r.nb - 1, status);
   EIPC_HIP(c, hipGetLastError());
   k_big_fill<<<dim3(BIG_BLOCKS, r.vhash ? 2 : 1), 256, 0, s>>>(h, b.g, r.nb - 1, status);
   EIPC_HIP(c, hipGetLastError());
