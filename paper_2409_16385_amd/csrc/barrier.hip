@@ -347,10 +347,13 @@ __device__ __forceinline__ int local_index(const LocalAcc &L, int node, bool val
   return li;
 }
 
+template <bool HESS>
 __device__ __forceinline__ void local_init(const LocalAcc &L) {
   for (int t = threadIdx.x; t < LN; t += blockDim.x) L.nkey[t] = -1;
-  for (int t = threadIdx.x; t < LNB * 9; t += blockDim.x) L.bval[t] = 0.0;
-  for (int t = threadIdx.x; t < LNB; t += blockDim.x) L.touched[t] = 0;
+  if (HESS) {
+    for (int t = threadIdx.x; t < LNB * 9; t += blockDim.x) L.bval[t] = 0.0;
+    for (int t = threadIdx.x; t < LNB; t += blockDim.x) L.touched[t] = 0;
+  }
   for (int t = threadIdx.x; t < LN * 3; t += blockDim.x) L.gval[t] = 0.0;
   if (threadIdx.x == 0) *L.count = 0;
 }
@@ -368,8 +371,8 @@ struct FlushList {
 // all of them), then the adds with consecutive lanes on consecutive entries
 // of a block: the memory takes a wavefront's adds by the line, so that a
 // block's nine adds are two requests and not nine.
-__device__ __forceinline__ void local_flush(const LocalAcc &L, const HessOut &h, int n_node, double *grad,
-                                            uint32_t *status, FlushList &F) {
+__device__ __forceinline__ void flush_blocks(const LocalAcc &L, const HessOut &h, int n_node, uint32_t *status,
+                                             FlushList &F) {
   if (threadIdx.x == 0) F.n = 0;
   __syncthreads();
   for (int idx = threadIdx.x; idx < LNB; idx += blockDim.x) {
@@ -416,6 +419,10 @@ __device__ __forceinline__ void local_flush(const LocalAcc &L, const HessOut &h,
     }
     *v = 0.0;
   }
+}
+
+// the gradient, and the accumulator empty again
+__device__ __forceinline__ void flush_nodes(const LocalAcc &L, double *grad) {
   for (int i = threadIdx.x; i < 3 * LN; i += blockDim.x) {
     const int node = L.nkey[i / 3];
     if (node >= 0 && grad) atomicAdd(&grad[3 * (int64_t)node + i % 3], L.gval[i]);
@@ -544,24 +551,23 @@ __device__ __forceinline__ void expand_alone(const double *R, int nd, double wv,
 }
 
 // Instantiated per pair kind (the code is the same) so that the two launches
-// of a step carry their own names in kernel traces.
+// of a step carry their own names in kernel traces, and without the Hessian:
+// then the workgroup's blocks (112 KiB of LDS, one workgroup per CU) are not
+// there, and four fit (39,379 edge pairs: 56 and 33 us).
 template <int KIND, bool HESS>
-__global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_expand(
+__global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(HESS ? 2 : 4, HESS ? 2 : 5))) void k_expand(
     const int4 *__restrict__ vid4, const int64_t *__restrict__ d_count, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ col, const double *__restrict__ val, int n_node, const double *__restrict__ rec,
     int64_t cap, bool want_g, double *grad, HessOut h, uint32_t *status) {
   __shared__ int s_nkey[LN];
-  __shared__ double s_bval[LNB * 9];
+  __shared__ double s_bval[HESS ? LNB * 9 : 1];
   __shared__ double s_gval[LN * 3];
-  __shared__ unsigned char s_touched[LNB];
+  __shared__ unsigned char s_touched[HESS ? LNB : 1];
   __shared__ int s_count;
   __shared__ union __align__(16) {
     ExStage stage[EX_W];
-    FlushList flush;
+    std::conditional_t<HESS, FlushList, char> flush;
   } s_u;
-  LocalAcc L{s_nkey, s_bval, s_touched, s_gval, &s_count};
-  local_init(L);
-  __syncthreads();
   // consecutive ranges on one XCD (workgroups are dealt to the 8 XCDs in turn)
   int rid = blockIdx.x;
   if ((gridDim.x & 7) == 0) rid = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
@@ -569,6 +575,10 @@ __global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
   const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 63) / 64 * 64;
   const int64_t r0 = (int64_t)rid * per;
   const int64_t r1 = r0 + per < n ? r0 + per : n;
+  if (r0 >= n) return;  // before the accumulator is cleared: most of a short list's time
+  LocalAcc L{s_nkey, s_bval, s_touched, s_gval, &s_count};
+  local_init<HESS>(L);
+  __syncthreads();
   // the wavefront's number as a scalar: its ranges and loops are then uniform
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   ExStage &S = s_u.stage[wave];
@@ -786,7 +796,10 @@ __global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
       }
     }
     __syncthreads();
-    if (base + EX_STEP >= r1 || s_count > LN / 2) local_flush(L, h, n_node, want_g ? grad : nullptr, status, s_u.flush);
+    if (last_step || s_count > LN / 2) {
+      if constexpr (HESS) flush_blocks(L, h, n_node, status, s_u.flush);
+      flush_nodes(L, want_g ? grad : nullptr);
+    }
     __syncthreads();
   }
 }
