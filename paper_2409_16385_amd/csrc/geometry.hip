@@ -573,6 +573,9 @@ __device__ __forceinline__ void big_cell(const int *c0, const int *c1, int c, in
 // count (histogram) or reserves the bucket's range (fill).  An entry whose
 // probe finds neither its bucket nor a free slot within LT_PROBE steps goes
 // to the global counters directly; its bucket then never enters the table.
+// parts, at most, of a large box in a short list: its cells in turn
+constexpr int LQ_PARTS = 32;
+
 // Threads to an item (Q), which take its cells in turn, and items to a
 // workgroup.  Short lists leave the chip idle with one thread to an item,
 // its cells one chain of table lookups: with four, the fill of the sphere 54
@@ -804,20 +807,24 @@ __global__ __launch_bounds__(lt_threads(Q)) void k_item_fill(HSides hs, const Gr
   });
 }
 
-// big records, one wavefront each (grid y: the side)
+// big records, cut into up to LQ_PARTS parts, a wavefront each (grid y: the
+// side): the two ground triangles of the sphere took a wavefront each 14 us,
+// one group of 64 returning adds after the other, and 4 like this.
 __global__ void k_big_fill(HSides hs, const GridDev *__restrict__ gp, uint32_t bmask, uint32_t *status) {
   const HSide &h = hs.s[blockIdx.y];
   const int lane = threadIdx.x & 63;
   const int64_t nbig = h.n_big[0];
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nbig; w += nw) {
-    const int i = h.big[w];
+  int parts = 1;
+  while (parts < LQ_PARTS && nbig * (2 * parts) <= nw) parts *= 2;
+  for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nbig * parts; w += nw) {
+    const int i = h.big[w / parts], part = (int)(w % parts);
     const GridDev g = *gp;
     const int sc = h.rec[i].tag >> 1;
     int c0[3], c1[3];
     cell_range(g, h.rec[i].lo, h.rec[i].hi, c0, c1);
     const int nc = (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
-    for (int c = lane; c < nc; c += 64) {
+    for (int c = 64 * part + lane; c < nc; c += 64 * parts) {
       int x, y, z;
       big_cell(c0, c1, c, x, y, z);
       const uint32_t b = cell_hash(x, y, z, sc) & bmask;
@@ -1082,8 +1089,6 @@ __global__ __launch_bounds__(QT) void k_query(int nq, const double *__restrict__
 // wavefront to each of the 10 large edges of a sheet took 62 us, most of it
 // waits for one group of loads after the other; 9 us in 32 parts each.
 // ---------------------------------------------------------------------------
-constexpr int LQ_PARTS = 32;
-
 template <int KIND, int MODE>
 __global__ __launch_bounds__(QT) void k_query_lq(const int32_t *__restrict__ qlist, const int64_t *__restrict__ n_qlist,
                                                  const double *__restrict__ xs, const double *__restrict__ x1s,
