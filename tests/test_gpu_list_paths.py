@@ -96,7 +96,7 @@ def test_batch_step_bound_per_scene():
     assert np.array_equal(alpha, [o[0] for o in one]) and n == sum(o[1] for o in one)
 
 
-@pytest.mark.parametrize("n_node", [1, 2047, 2048, 2049, 32768, 32769, 70001])
+@pytest.mark.parametrize("n_node", [1, 2047, 2048, 2049, 8192, 8193, 32768, 32769, 70001])
 def test_scan_sizes(n_node):
     """Reduction over node counts around the scans' one-workgroup limit and
     tile size: unused nodes only lengthen the scans, so blocks and columns are
