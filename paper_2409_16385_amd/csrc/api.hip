@@ -1009,22 +1009,35 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
     EIPC_HIP(c, hipEventRecord(c->fork_ev, s));
     EIPC_HIP(c, hipStreamWaitEvent(c->side, c->fork_ev, 0));
+    auto stage = [&](int kind, int k) -> eipc_status {
+      hipStream_t st = kind == 0 && !c->prof_serial ? c->side : s;
+      int32_t *cand = kind == 0 ? cpt : cee;
+      int32_t *act = kind == 0 ? act_pt : act_ee, *typ = kind == 0 ? typ_pt : typ_ee;
+      const int64_t swept_cap = kind == 0 ? plan->swept_pt : plan->swept_ee;
+      const int64_t act_cap = kind == 0 ? plan->act_pt : plan->act_ee;
+      if (k == 0) return bp_planned_run(c, run[kind], cand, swept_cap, cn + 7 + kind, st);
+      if (k == 1)
+        return launch_narrow_ccd(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, dhat, act, typ, act_cap,
+                                 cn + 2 + kind, cn + 5 + kind, sfac, t_max, max_iter, (uint64_t *)alpha, st);
+      if (k == 2)
+        return launch_ccd_long(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, sfac, t_max, max_iter,
+                               (uint64_t *)alpha, st);
+      return barrier ? launch_barrier(c, sc, kind, xs, cand, act, typ, cn + 2 + kind, act_cap, dhat, kappa, f, energy,
+                                      g, h, st)
+                     : EIPC_OK;
+    };
+    // EE, the longer chain, first, and the two stage by stage: issued one
+    // chain after the other, the second began when the host had issued all
+    // of the first (22 launches of 4 us): sphere 315 and 293 us, plate 690
+    // and 663.
     auto chains = [&]() -> eipc_status {
-      for (int kind = 0; kind < 2; ++kind) {
-        hipStream_t st = kind == 0 && !c->prof_serial ? c->side : s;
-        int32_t *cand = kind == 0 ? cpt : cee;
-        int32_t *act = kind == 0 ? act_pt : act_ee, *typ = kind == 0 ? typ_pt : typ_ee;
-        const int64_t swept_cap = kind == 0 ? plan->swept_pt : plan->swept_ee;
-        const int64_t act_cap = kind == 0 ? plan->act_pt : plan->act_ee;
-        EIPC_TRY(bp_planned_run(c, run[kind], cand, swept_cap, cn + 7 + kind, st));
-        EIPC_TRY(launch_narrow_ccd(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, dhat, act, typ, act_cap,
-                                   cn + 2 + kind, cn + 5 + kind, sfac, t_max, max_iter, (uint64_t *)alpha, st));
-        EIPC_TRY(launch_ccd_long(c, sc, kind, xs, ps, cand, swept_cap, cn + 7 + kind, sfac, t_max, max_iter,
-                                 (uint64_t *)alpha, st));
-        if (barrier)
-          EIPC_TRY(launch_barrier(c, sc, kind, xs, cand, act, typ, cn + 2 + kind, act_cap, dhat, kappa, f, energy,
-                                  g, h, st));
+      if (c->prof_serial) {
+        for (int kind = 0; kind < 2; ++kind)
+          for (int k = 0; k < 4; ++k) EIPC_TRY(stage(kind, k));
+        return EIPC_OK;
       }
+      for (int k = 0; k < 4; ++k)
+        for (int kind = 1; kind >= 0; --kind) EIPC_TRY(stage(kind, k));
       return EIPC_OK;
     };
     c->step_pairs[0] = cpt;
