@@ -1254,7 +1254,9 @@ __global__ void k_hash_rowfill(int64_t cap, const int64_t *hkey, int n_node, con
 // column.  Rows of up to 64 entries rank by shuffles; longer rows are
 // taken 64 entries at a time, each ranked against the whole row by
 // wavefront-uniform reads (any length; time grows as len^2 / 64).
-// Rows that end beyond the capacity are left alone (overflow is raised).
+// A capacity that is too small raises the overflow and cuts the list: rows
+// past it are empty, and what lies within it of the row that crosses it is
+// marked as having no source (column 0, a zero block).
 __global__ void k_row_sort(int n_node, const int64_t *rowptr, const int32_t *bcol, const int64_t *bsrc,
                            int32_t *bcol2, int64_t *bsrc2, int32_t *rowptr32, int64_t nnzb_cap, uint32_t *status) {
   const int lane = threadIdx.x & 63;
@@ -1270,7 +1272,13 @@ __global__ void k_row_sort(int n_node, const int64_t *rowptr, const int32_t *bco
   }
   const int64_t b = rowptr[r], e = rowptr[r + 1];
   if (lane == 0) rowptr32[r] = (int32_t)(b < nnzb_cap ? b : nnzb_cap);
-  if (e > nnzb_cap) return;
+  if (e > nnzb_cap) {
+    for (int64_t p = b + lane; p < nnzb_cap; p += 64) {
+      bcol2[p] = 0;
+      bsrc2[p] = -1;
+    }
+    return;
+  }
   const int64_t len = e - b;
   if (len <= 64) {
     const bool v = lane < len;
@@ -1303,6 +1311,11 @@ __global__ void k_bsr_gather(int64_t cap, const int32_t *rowptr32, int n_node, c
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnzb && p < cap;
        p += (int64_t)gridDim.x * blockDim.x) {
     const int64_t src = bsrc[p];
+    if (src < 0) {  // in the row that the capacity cuts
+#pragma unroll
+      for (int t = 0; t < 9; ++t) blocks[9 * p + t] = 0.0;
+      continue;
+    }
     const double *v = hval + 9 * (src >> 1);
     if ((src & 1) == 0) {
 #pragma unroll

@@ -1,0 +1,67 @@
+"""Lists and tables at the limits of their sizes: what does not fit is
+reported or run again, and nothing past it is read."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2409_16385_amd as E  # noqa: E402
+from paper_2409_16385_amd import binding as B  # noqa: E402
+from scenes import scene as S  # noqa: E402
+
+FLAGS = E.ENERGY | E.GRAD | E.HESS | E.PROJECT
+
+
+def _dev(a):
+    return None if a is None else torch.as_tensor(np.ascontiguousarray(a), device="cuda:0")
+
+
+def _same(a, b):
+    """Sums of the same terms in another order."""
+    return float((a - b).norm()) <= 1e-12 * float(b.norm())
+
+
+def test_more_blocks_than_the_first_size():
+    """A per-call reduction sizes its BSR view from the node count (16 blocks
+    a row and 1,024) on a context's first call and is compacted again when
+    they are more."""
+    sc = S.grasp_scene(0, 50, 400, 28, frac=0.8)
+    ctx = E.Context(0)
+    dsc = E.Scene.from_host(ctx, sc)
+    q = _dev(sc.q)
+    pt, ee = E.build_candidates(ctx, dsc, q, sc.dhat)
+    dense = E.barrier_reduce(ctx, dsc, q, pt, ee, sc.dhat, sc.kappa, FLAGS, hess="dense")["hess"]
+    for _ in range(2):
+        rp, col, blk = E.barrier_reduce(ctx, dsc, q, pt, ee, sc.dhat, sc.kappa, FLAGS, hess="bsr")["hess"]
+        assert blk.shape[0] > 16 * sc.n_node + 1024
+        row = torch.repeat_interleave(torch.arange(sc.n_node, device="cuda:0"), (rp[1:] - rp[:-1]).long())
+        at = dense.view(sc.n_node, 3, sc.n_node, 3).permute(0, 2, 1, 3)[row, col.long()]
+        assert _same(blk, at) and _same(blk.norm(), dense.norm())
+
+
+@pytest.mark.parametrize("reserve", [0, 1 << 29])
+def test_blocks_past_the_plan(reserve):
+    """A plan with fewer BSR blocks than the step has: the overflow is
+    reported, rows within the capacity are whole, the row that crosses it
+    holds zero blocks."""
+    sc = S.config1(0)
+    ctx = E.Context(0, reserve_bytes=reserve)
+    dsc = E.Scene.from_host(ctx, sc)
+    q = _dev(sc.q)
+    plan = E.plan_step(ctx, dsc, q, sc.dhat)
+    out = E.StepOut(ctx, dsc, plan, FLAGS, with_alpha=False)
+    E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, flags=FLAGS)
+    assert ctx.sync_status() == B.OK
+    rp, col, blk = out.hess(ctx)
+    n = (rp[1:] - rp[:-1]).cpu().numpy()
+    for r in (int(np.flatnonzero(n > 1)[0]), int(np.flatnonzero(n > 1)[-1])):
+        b = int(rp[r])
+        plan.nnzb = b + 1
+        E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, flags=FLAGS)
+        assert ctx.sync_status() == B.ERR_CAPACITY
+        rp1, col1, blk1 = out.hess(ctx)
+        assert torch.equal(rp1, rp.clamp(max=b + 1)) and torch.equal(col1[:b], col[:b])
+        assert b == 0 or _same(blk1[:b], blk[:b])
+        assert int(col1[b]) == 0 and not bool(blk1[b].any())
