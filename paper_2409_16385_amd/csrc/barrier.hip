@@ -886,7 +886,7 @@ __global__ void k_pair_scatter(const int32_t *__restrict__ act, const int32_t *_
 // the counters of sort_active, to be cleared before it runs
 eipc_status sort_clear(eipc_ctx *c, const eipc_scene *sc, int kind, FillList &fl) {
   const int nn = std::max(sc->n_node, 1);
-  const size_t bytes = (sizeof(int32_t) * (nn + 1) + 7) & ~(size_t)7;
+  const size_t bytes = fill_bytes(sizeof(int32_t) * ((size_t)nn + 1));
   int32_t *hist, *fill;
   EIPC_TRY(ensure_t(c, kind ? B_SHIST_EE : B_SHIST, (size_t)nn + 1, &hist));
   EIPC_TRY(ensure_t(c, kind ? B_SFILL_EE : B_SFILL, (size_t)nn + 1, &fill));
@@ -1331,7 +1331,7 @@ __global__ void k_bsr_gather(int64_t cap, const int32_t *rowptr32, int n_node, c
 
 // the row counters of bsr_compact, to be cleared before it runs
 eipc_status bsr_clear(eipc_ctx *c, int n_node, FillList &fl) {
-  const size_t bytes = (sizeof(int32_t) * ((size_t)n_node + 1) + 7) & ~(size_t)7;
+  const size_t bytes = fill_bytes(sizeof(int32_t) * ((size_t)n_node + 1));
   int32_t *rowcnt, *rowfill;
   EIPC_TRY(ensure_t(c, B_ROWCNT, (size_t)n_node + 1, &rowcnt));
   EIPC_TRY(ensure_t(c, B_ROWFILL, (size_t)n_node + 1, &rowfill));

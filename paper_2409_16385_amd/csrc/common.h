@@ -280,19 +280,29 @@ eipc_status launch_embed_swept(eipc_ctx *c, const eipc_scene *sc, const double *
 eipc_status exclusive_scan2(eipc_ctx *c, const int32_t *in0, int64_t n0, int64_t *out0, const int32_t *in1,
                             int64_t n1, int64_t *out1, hipStream_t s);
 
-// Buffers to set to a 64-bit value, all in one launch (bytes a multiple of
-// 8; scratch buffers have room past their end for rounding up).
+// Buffers to set to a 64-bit value, all in one launch.  Sizes are whole
+// 8-byte words: a caller of 4-byte counters rounds up (fill_bytes; scratch
+// buffers have room past their end).  A size that is not, or more segments
+// than there is room for, fails the launch: nothing is left out silently.
 struct FillSeg {
   uint64_t *p;
   int64_t n;
   uint64_t v;
   int blocks;
 };
+constexpr int FILL_SEGS = 24;  // a planned step with every output takes 17
+inline size_t fill_bytes(size_t bytes) { return (bytes + 7) & ~(size_t)7; }
 struct FillList {
-  FillSeg seg[24];
+  FillSeg seg[FILL_SEGS];
   int n = 0;
+  bool bad = false;
   void add(void *p, size_t bytes, uint64_t v) {
-    if (p && bytes) seg[n++] = FillSeg{(uint64_t *)p, (int64_t)(bytes / 8), v, 0};
+    if (!p || !bytes) return;
+    if ((bytes & 7) || n == FILL_SEGS) {
+      bad = true;
+      return;
+    }
+    seg[n++] = FillSeg{(uint64_t *)p, (int64_t)(bytes / 8), v, 0};
   }
 };
 eipc_status launch_fill(eipc_ctx *c, FillList &l, hipStream_t s);

@@ -162,6 +162,7 @@ __global__ __launch_bounds__(256) void k_fill_list(FillList l) {
 }
 
 eipc_status launch_fill(eipc_ctx *c, FillList &l, hipStream_t s) {
+  if (l.bad) return set_err(c, EIPC_ERR_ARG, "a buffer to clear is not whole words");
   if (l.n == 0) return EIPC_OK;
   int64_t blocks = 0;
   for (int k = 0; k < l.n; ++k) {
@@ -1810,8 +1811,8 @@ static eipc_status bp_scratch(eipc_ctx *c, BPRun &r) {
 static void bp_clear(const BPRun &r, FillList &fl, bool small, bool buckets) {
   if (small) fl.add(r.b.g, 512, 0);
   if (buckets) {
-    fl.add(r.b.bcnt, sizeof(int32_t) * (size_t)r.nb, 0);
-    if (r.vhash) fl.add(r.b.vbcnt, sizeof(int32_t) * (size_t)r.nb, 0);
+    fl.add(r.b.bcnt, fill_bytes(sizeof(int32_t) * (size_t)r.nb), 0);
+    if (r.vhash) fl.add(r.b.vbcnt, fill_bytes(sizeof(int32_t) * (size_t)r.nb), 0);
   }
 }
 
@@ -2218,7 +2219,7 @@ eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, const double *xs, con
         EIPC_TRY(ensure_t(c, B_SORT_SLOT, (size_t)cap[kind], &slot[kind]));
         EIPC_TRY(ensure_t(c, B_LQTMP, (size_t)cap[kind], &tmp[kind]));
         EIPC_TRY(ensure_t(c, kind == 0 ? B_SORT_CNT_PT : B_SORT_CNT_EE, (size_t)r.nq, &cnt[kind]));
-        fl.add(cnt[kind], (sizeof(int32_t) * (size_t)r.nq + 7) & ~(size_t)7, 0);
+        fl.add(cnt[kind], fill_bytes(sizeof(int32_t) * (size_t)r.nq), 0);
       } else {
         EIPC_TRY(ensure_t(c, (BufId)q.grow_id, (size_t)2 * cap[kind], &list[kind]));
       }

@@ -65,3 +65,33 @@ def test_blocks_past_the_plan(reserve):
         assert torch.equal(rp1, rp.clamp(max=b + 1)) and torch.equal(col1[:b], col[:b])
         assert b == 0 or _same(blk1[:b], blk[:b])
         assert int(col1[b]) == 0 and not bool(blk1[b].any())
+
+
+@pytest.mark.parametrize("reserve", [0, 1 << 29])
+@pytest.mark.parametrize("buckets", [1, 2, 64])
+def test_few_hash_buckets(reserve, buckets):
+    """Any power of two of buckets gives the same step, on scratch that an
+    earlier call left full of set bits (the empty keys of a block table)."""
+    sc = S.tiny_scene(3)
+    ctx = E.Context(0, reserve_bytes=reserve)
+    dsc = E.Scene.from_host(ctx, sc)
+    q, dq, off = _dev(sc.q), _dev(sc.dq), _dev(sc.dx_off)
+    plan = E.plan_step(ctx, dsc, q, sc.dhat, dq, off)
+    out = E.StepOut(ctx, dsc, plan, FLAGS)
+
+    def step():
+        E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, dq, off, flags=FLAGS)
+        assert ctx.sync_status() == B.OK
+        return [t.clone() for t in (out.counts, out.alpha, out.energy, out.grad)], out.hess(ctx)
+
+    ref, href = step()
+    assert int(ref[0][2]) > 0
+    none = torch.zeros((0, 2), dtype=torch.int32, device="cuda:0")
+    E.barrier_reduce(ctx, dsc, q, none, none, sc.dhat, sc.kappa, FLAGS, hess="bsr")
+    for k in range(4):
+        plan.buckets[k] = buckets
+    for _ in range(2):
+        got, hgot = step()
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+        assert _same(got[2], ref[2]) and _same(got[3], ref[3])
+        assert torch.equal(hgot[0], href[0]) and torch.equal(hgot[1], href[1]) and _same(hgot[2], href[2])
