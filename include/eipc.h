@@ -206,9 +206,9 @@ eipc_status eipc_ccd_max_step(eipc_ctx *ctx, const eipc_scene *sc, const double 
  *   out = sum_k W_k^T H_k (W_k v + v_off_k)
  * with H_k the true pair Hessian, or its PSD projection with EIPC_PROJECT.
  * v: device double[3*n_node]; v_off: device double[3*n_vert] or NULL.
- * out: device double[3*n_node] (overwritten).  out_off: device
- * double[3*n_vert] or NULL, receives the unreduced per-vertex sums
- * sum_k H_k z_k (the rows of kinematic vertices). */
+ * out: device double[3*n_node] (overwritten; may be v).  out_off: device
+ * double[3*n_vert] or NULL (may be v_off), receives the unreduced per-vertex
+ * sums sum_k H_k z_k (the rows of kinematic vertices). */
 eipc_status eipc_barrier_hvp(eipc_ctx *ctx, const eipc_scene *sc, const double *q, const int32_t *pt,
                              int64_t n_pt, const int32_t *ee, int64_t n_ee, double dhat, double kappa,
                              uint32_t flags, const double *v, const double *v_off, double *out, double *out_off,

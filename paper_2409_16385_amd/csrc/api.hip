@@ -500,11 +500,11 @@ eipc_status eipc_barrier_reduce(eipc_ctx *c, const eipc_scene *sc, const double 
     }
     if (g || want_h)
       for (int kind = 0; kind < 2; ++kind) EIPC_TRY(sort_clear(c, sc, kind, fl));
+    // q is read before anything is cleared: grad_q may be q
+    if (attempt == 0) EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
     EIPC_TRY(launch_fill(c, fl, s));
-    if (attempt == 0) {
-      EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
+    if (attempt == 0)
       EIPC_TRY(narrow_both(c, sc, xs, pt, n_pt, ee, n_ee, dhat, &act_pt, &typ_pt, &act_ee, &typ_ee, s));
-    }
     // with enough pairs of both kinds, the PT chain runs on the side stream
     // beside the EE chain, as in the planned step (their outputs meet in
     // atomics; their scratch is per kind); small calls stay on one stream,
@@ -630,8 +630,9 @@ eipc_status eipc_barrier_hvp(eipc_ctx *c, const eipc_scene *sc, const double *q,
   fl.add(out, sizeof(double) * 3 * (size_t)sc->n_node, 0);
   fl.add(out_off, sizeof(double) * 3 * (size_t)sc->n_vert, 0);
   for (int kind = 0; kind < 2; ++kind) EIPC_TRY(sort_clear(c, sc, kind, fl));
-  EIPC_TRY(launch_fill(c, fl, s));
+  // v and v_off are read before anything is cleared: out may be v
   EIPC_TRY(launch_embed_swept(c, sc, q, v, v_off, xs, xvs, nullptr, s));
+  EIPC_TRY(launch_fill(c, fl, s));
   int32_t *act_pt, *typ_pt, *act_ee, *typ_ee;
   EIPC_TRY(narrow_both(c, sc, xs, pt, n_pt, ee, n_ee, dhat, &act_pt, &typ_pt, &act_ee, &typ_ee, s));
   EIPC_TRY(launch_hvp(c, sc, 0, xs, xvs, pt, act_pt, typ_pt, c->counters + 2, n_pt, dhat, kappa, flags, out, out_off,
@@ -676,8 +677,8 @@ eipc_status eipc_barrier_hvp_noalloc(eipc_ctx *c, const eipc_scene *sc, const do
   fl.add(cnt, 2 * sizeof(int64_t), 0);  // the array keeps the last call's counts
   fl.add(out, sizeof(double) * 3 * (size_t)sc->n_node, 0);
   fl.add(out_off, sizeof(double) * 3 * (size_t)sc->n_vert, 0);
-  EIPC_TRY(launch_fill(c, fl, s));
   EIPC_TRY(launch_embed_swept(c, sc, q, v, v_off, xs, xvs, nullptr, s));
+  EIPC_TRY(launch_fill(c, fl, s));
   EIPC_TRY(launch_narrow(c, sc, 0, xs, pt, n_pt, dhat, act_pt, typ_pt, cnt, s));
   EIPC_TRY(launch_narrow(c, sc, 1, xs, ee, n_ee, dhat, act_ee, typ_ee, cnt + 1, s));
   EIPC_TRY(launch_hvp(c, sc, 0, xs, xvs, pt, act_pt, typ_pt, cnt, n_pt, dhat, kappa, flags, out, out_off, s, false));
@@ -1005,8 +1006,9 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     fl.add(alpha, 8 * (size_t)n_scene_of(sc), tb);
     for (int kind = 0; kind < 2; ++kind)
       EIPC_TRY(bp_planned_begin(c, sc, kind, xs, x1s, dhat, bp[2 + kind], run[kind], fl));
-    EIPC_TRY(launch_fill(c, fl, s));
+    // q and dq are read before anything is cleared: grad_q may be q
     EIPC_TRY(launch_embed_swept(c, sc, q, dq, dx_off, xs, ps, x1s, s));
+    EIPC_TRY(launch_fill(c, fl, s));
     EIPC_HIP(c, hipEventRecord(c->fork_ev, s));
     EIPC_HIP(c, hipStreamWaitEvent(c->side, c->fork_ev, 0));
     auto stage = [&](int kind, int k) -> eipc_status {
@@ -1064,8 +1066,8 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     c->step_pair_cap[1] = plan->cand_ee;
     for (int kind = 0; kind < 2; ++kind)
       EIPC_TRY(bp_planned_begin(c, sc, kind, xs, nullptr, dhat, bp[kind], run[kind], fl));
-    EIPC_TRY(launch_fill(c, fl, s));
     EIPC_TRY(launch_embed(c, sc, q, sc->x_off, xs, nullptr, s));
+    EIPC_TRY(launch_fill(c, fl, s));
     EIPC_TRY(bp_planned_run(c, run[0], ppt, plan->cand_pt, cn + 5, s));
     EIPC_TRY(bp_planned_run(c, run[1], pee, plan->cand_ee, cn + 6, s));
     EIPC_TRY(launch_narrow(c, sc, 0, xs, ppt, plan->cand_pt, dhat, act_pt, typ_pt, cn + 2, s, cn + 5, plan->act_pt));
