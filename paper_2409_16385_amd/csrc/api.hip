@@ -900,13 +900,19 @@ eipc_status eipc_set_ccd_method(eipc_ctx *c, int32_t method) {
 
 namespace eipc {
 
-__global__ void k_step_counts(const int64_t *cn, int64_t *out) {
+// ctr: the counters of the two broad-phase lists (5 or 7), whose counts go on
+// past the lists' capacities; reported is what the lists hold
+__global__ void k_step_counts(const int64_t *cn, int ctr, int64_t cap_pt, int64_t cap_ee, int64_t *out) {
   if (threadIdx.x == 0) {
-    out[0] = cn[5];
-    out[1] = cn[6];
+    auto held = [&](int k) {
+      const int64_t v = cn[k], cap = k == ctr ? cap_pt : (k == ctr + 1 ? cap_ee : v);
+      return v < cap ? v : cap;
+    };
+    out[0] = held(5);
+    out[1] = held(6);
     out[2] = cn[2] + cn[3];
-    out[3] = cn[7];
-    out[4] = cn[8];
+    out[3] = held(7);
+    out[4] = held(8);
   }
 }
 
@@ -1085,7 +1091,7 @@ eipc_status eipc_contact_step(eipc_ctx *c, const eipc_scene *sc, const eipc_plan
     c->step_act_cap[kind] = kind == 0 ? plan->act_pt : plan->act_ee;
   }
   if (counts) {
-    k_step_counts<<<1, 64, 0, s>>>(cn, counts);
+    k_step_counts<<<1, 64, 0, s>>>(cn, c->step_pair_ctr[0], c->step_pair_cap[0], c->step_pair_cap[1], counts);
     EIPC_HIP(c, hipGetLastError());
   }
   return EIPC_OK;

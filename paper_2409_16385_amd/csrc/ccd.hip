@@ -412,13 +412,13 @@ eipc_status launch_narrow_ccd(eipc_ctx *c, const eipc_scene *sc, int kind, const
                               const int32_t *pairs, int64_t n, const int64_t *d_n, double dhat, int32_t *act,
                               int32_t *typ, int64_t act_cap, int64_t *d_count, int64_t *cand_count, double sfac,
                               double t_max, int64_t max_iter, uint64_t *d_alpha_bits, hipStream_t s) {
-  if (n == 0) return EIPC_OK;
+  // also of a list without room: its count may have passed it
   const int blocks = (int)std::min<int64_t>(grid_for(n, 256), (int64_t)c->wg_per_cu[3] * c->num_cu);
   const int32_t *vsc = vscene_of(sc);
   const int nsc = n_scene_of(sc);
   int64_t *n_long = c->counters + 9 + kind;
   int32_t *longl;
-  EIPC_TRY(ensure_t(c, kind == 0 ? B_CCD_LONG_PT : B_CCD_LONG_EE, (size_t)n, &longl));
+  EIPC_TRY(ensure_t(c, kind == 0 ? B_CCD_LONG_PT : B_CCD_LONG_EE, (size_t)std::max<int64_t>(n, 1), &longl));
   unsigned long long *ab = (unsigned long long *)d_alpha_bits;
   const double d2 = dhat * dhat, h = 0.5 * dhat;
   {

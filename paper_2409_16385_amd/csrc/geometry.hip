@@ -2408,7 +2408,8 @@ __global__ void k_narrow(int64_t cap, const int64_t *d_n, const int32_t *__restr
 eipc_status launch_narrow(eipc_ctx *c, const eipc_scene *sc, int kind, const double *xs, const int32_t *pairs,
                           int64_t n, double dhat, int32_t *act, int32_t *typ, int64_t *d_count, hipStream_t s,
                           const int64_t *d_n, int64_t act_cap, int64_t *cand_count) {
-  if (n == 0) return EIPC_OK;
+  // a planned list without room is looked at too: its count may have passed it
+  if (n == 0 && !d_n) return EIPC_OK;
   const double d2 = dhat * dhat;
   const double h = 0.5 * dhat;
   if (act_cap < 0) act_cap = n;

@@ -95,3 +95,24 @@ def test_few_hash_buckets(reserve, buckets):
         assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
         assert _same(got[2], ref[2]) and _same(got[3], ref[3])
         assert torch.equal(hgot[0], href[0]) and torch.equal(hgot[1], href[1]) and _same(hgot[2], href[2])
+
+
+@pytest.mark.parametrize("cap", [0, 5])
+@pytest.mark.parametrize("field", ["cand_pt", "cand_ee", "swept_pt", "swept_ee"])
+def test_candidates_past_the_plan(field, cap):
+    """A list with less room than candidates, or with none, is reported, and
+    its count is what it holds."""
+    sc = S.tiny_scene(3)
+    ctx = E.Context(0)
+    dsc = E.Scene.from_host(ctx, sc)
+    q, dq, off = _dev(sc.q), _dev(sc.dq), _dev(sc.dx_off)
+    plan = E.plan_step(ctx, dsc, q, sc.dhat, dq, off)
+    swept = field.startswith("swept")
+    out = E.StepOut(ctx, dsc, plan, FLAGS, with_alpha=swept)
+    at = ["cand_pt", "cand_ee", "", "swept_pt", "swept_ee"].index(field)
+    E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, dq, off, flags=FLAGS)
+    assert ctx.sync_status() == B.OK and int(out.counts[at]) > 5
+    setattr(plan, field, cap)
+    E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, dq, off, flags=FLAGS)
+    assert ctx.sync_status() == B.ERR_CAPACITY
+    assert int(out.counts[at]) == cap
