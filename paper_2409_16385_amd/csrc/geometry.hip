@@ -2025,13 +2025,14 @@ __global__ __launch_bounds__(256) void k_sort_gather(const int2 *__restrict__ li
     tmp[off[p.x] + slot[i]] = p.y;
   }
 }
-// nothing is written when the output is too small
+// nothing is written when the output is too small, nor from a pass that ran
+// out of hash entries (cut): its list is a part, and run again
 __global__ __launch_bounds__(256) void k_sort_rank(const int2 *__restrict__ list, const unsigned long long *total,
                                                    int64_t cap, const int64_t *__restrict__ off,
-                                                   const int32_t *__restrict__ tmp, int2 *__restrict__ out,
-                                                   int64_t out_cap) {
+                                                   const int32_t *__restrict__ tmp, const uint32_t *cut,
+                                                   int2 *__restrict__ out, int64_t out_cap) {
   const int64_t n = (int64_t)*total;
-  if (n > cap || n > out_cap) return;
+  if (n > cap || n > out_cap || *cut) return;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     const int2 p = list[i];
     const int64_t o0 = off[p.x], o1 = off[p.x + 1];
@@ -2244,7 +2245,8 @@ eipc_status broad_phase(eipc_ctx *c, const eipc_scene *sc, const double *xs, con
         EIPC_TRY(exclusive_scan(c, cnt[kind], r.nq, b.qoff, s));
         k_sort_gather<<<g, 256, 0, s>>>(l2, b.total, cap[kind], b.qoff, slot[kind], tmp[kind]);
         EIPC_HIP(c, hipGetLastError());
-        k_sort_rank<<<g, 256, 0, s>>>(l2, b.total, cap[kind], b.qoff, tmp[kind], (int2 *)q.out, q.out ? q.cap : 0);
+        k_sort_rank<<<g, 256, 0, s>>>(l2, b.total, cap[kind], b.qoff, tmp[kind], b.flag, (int2 *)q.out,
+                                      q.out ? q.cap : 0);
         EIPC_HIP(c, hipGetLastError());
       }
       col.add(&b.g->bad, 4);

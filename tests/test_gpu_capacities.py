@@ -116,3 +116,34 @@ def test_candidates_past_the_plan(field, cap):
     E.contact_step(ctx, dsc, plan, q, sc.dhat, sc.kappa, out, dq, off, flags=FLAGS)
     assert ctx.sync_status() == B.ERR_CAPACITY
     assert int(out.counts[at]) == cap
+
+
+@pytest.mark.parametrize("swept", [False, True])
+def test_nothing_written_when_a_list_does_not_fit(swept):
+    """Also on a context's first call, whose first pass over so small a cell
+    runs out of hash entries and finds only some of the pairs."""
+    import ctypes as C
+    sc = S.config1(0)
+    ctx = E.Context(0)
+    dsc = E.Scene.from_host(ctx, sc)
+    q, dq, off = _dev(sc.q), _dev(sc.dq), _dev(sc.dx_off)
+    if swept:
+        pt, ee = E.ccd_candidates(ctx, dsc, q, dq, sc.dhat, off)
+    else:
+        pt, ee = E.build_candidates(ctx, dsc, q, sc.dhat)
+    ctx = E.Context(0)
+    dsc = E.Scene.from_host(ctx, sc)
+    E.set_tuning(ctx, 0.4)
+    bpt = torch.full((len(pt) - 1, 2), -7, dtype=torch.int32, device="cuda:0")
+    bee = torch.full((len(ee) - 1, 2), -7, dtype=torch.int32, device="cuda:0")
+    n_pt, n_ee = C.c_int64(), C.c_int64()
+    L = B._load()
+    lists = (bpt.data_ptr(), len(bpt), bee.data_ptr(), len(bee), C.byref(n_pt), C.byref(n_ee), ctx.stream())
+    if swept:
+        st = L.eipc_ccd_candidates(ctx.handle, dsc.ref, q.data_ptr(), dq.data_ptr(),
+                                   None if off is None else off.data_ptr(), sc.dhat, *lists)
+    else:
+        st = L.eipc_build_candidates(ctx.handle, dsc.ref, q.data_ptr(), sc.dhat, *lists)
+    torch.cuda.synchronize()
+    assert st == B.ERR_CAPACITY and (n_pt.value, n_ee.value) == (len(pt), len(ee))
+    assert bool((bpt == -7).all()) and bool((bee == -7).all())
