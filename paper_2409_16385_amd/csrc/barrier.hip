@@ -670,6 +670,7 @@ __global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(HESS ? 2 :
       if (pending == 0 && i0 < p1) {
         const int np = p1 - i0 < EX_PB ? p1 - i0 : EX_PB;
         uint32_t bad = 0;  // pairs whose records are not finite
+        gr = want_g ? gr : 0.0;  // not written by the terms otherwise
         {
           uint32_t nf = fabs(gr) < INFINITY ? 0u : 1u << gpr;
           if (HESS) {
