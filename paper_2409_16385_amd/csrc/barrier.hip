@@ -308,6 +308,11 @@ constexpr int EX_NS = 16;                // nodes of a wavefront's table
 constexpr int LN = 56;                   // local node slots
 constexpr int LNB = LN * (LN + 1) / 2;   // their upper 3x3 blocks (112 KiB)
 constexpr int LN_PROBE = 16;
+// Records and weights below these go into the products: x w w and its sums
+// over a product's 16 x 12 terms then stay in range.  A pair with a larger
+// one, or one that is not finite, is taken alone: in a product its infinite
+// or undefined sums would reach nodes that it does not have (0 x Inf).
+constexpr double EX_MAX_REC = 1e150, EX_MAX_W = 1e75;
 
 struct LocalAcc {
   int *nkey;               // LN: node of the slot, -1 = empty
@@ -504,9 +509,8 @@ __device__ __forceinline__ void expand_out(const LocalAcc &L, const HessOut &h, 
   }
 }
 
-// A pair whose record is not finite, straight to the outputs and entry by
-// entry: in a product it would reach every node of the table (0 x Inf).  The
-// pair's 16 entries of W are nd and wv of 16 lanes from l0.
+// A pair that does not go into a product, straight to the outputs and entry
+// by entry.  The pair's 16 entries of W are nd and wv of 16 lanes from l0.
 template <bool HESS>
 __device__ __forceinline__ void expand_alone(const double *R, int nd, double wv, int l0, const HessOut &h, int n_node,
                                              double *grad, uint32_t *status, bool want_g) {
@@ -669,13 +673,14 @@ __global__ __launch_bounds__(EX_T) __attribute__((amdgpu_waves_per_eu(HESS ? 2 :
     for (;;) {
       if (pending == 0 && i0 < p1) {
         const int np = p1 - i0 < EX_PB ? p1 - i0 : EX_PB;
-        uint32_t bad = 0;  // pairs whose records are not finite
+        uint32_t bad = 0;  // pairs to be taken alone
         gr = want_g ? gr : 0.0;  // not written by the terms otherwise
         {
-          uint32_t nf = fabs(gr) < INFINITY ? 0u : 1u << gpr;
+          uint32_t nf = fabs(gr) < EX_MAX_REC ? 0u : 1u << gpr;
+          nf |= !has || fabs(wt) < EX_MAX_W ? 0u : 1u << lk;
           if (HESS) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) nf |= fabs(xr[k]) < INFINITY ? 0u : 1u << xpr[k];
+            for (int k = 0; k < 4; ++k) nf |= fabs(xr[k]) < EX_MAX_REC ? 0u : 1u << xpr[k];
           }
           if (__any(nf != 0)) {
 #pragma unroll 1

@@ -52,3 +52,38 @@ def test_hessian_alone_reads_no_stale_gradient():
     assert torch.equal(h0[0], h1[0]) and torch.equal(h0[1], h1[1]) and _same(h1[2], h0[2])
     print(f"expansion {t0:.4f} ms, on records with a gradient that is not finite {t1:.4f} ms")
     assert t1 <= 3 * t0
+
+
+def _two_pairs(w):
+    """Two vertices over one triangle, gaps 1e-10 and 5e-3, row v of W being w
+    at node v.  Listed 18 and 14 times, so that a wavefront's run of four
+    holds both."""
+    x = np.array([[0.2, 0.2, 1e-10], [0, 0, 0], [1, 0, 0], [0, 1, 0], [0.5, 0.3, 5e-3]])
+    x = x @ np.array([[2, -1, 2], [2, 2, -1], [-1, 2, 2]]) / 3.0  # no axis along the normal
+    faces = np.array([[1, 2, 3]], np.int32)
+    edges = np.array([[1, 2], [2, 3], [1, 3]], np.int32)
+    ctx = E.Context(0)
+    sc = E.Scene(ctx, faces, edges, np.arange(6, dtype=np.int32), np.arange(5, dtype=np.int32), np.full(5, w), 5)
+    return ctx, sc, _dev((x / w).reshape(-1)), _dev(np.array([[0, 0]] * 18 + [[4, 0]] * 14, np.int32))
+
+
+@pytest.mark.parametrize("w,kappa", [(1.0, 1.0), (1e8, 1e287), (1e120, 1e58)])
+@pytest.mark.parametrize("hess", ["dense", "bsr"])
+def test_an_overflow_stays_with_its_pair(w, kappa, hess):
+    """Terms of one pair that pass the range in the sums over its rows of W do
+    not reach the blocks of another pair's own node."""
+    ctx, sc, q, pt = _two_pairs(w)
+    none = torch.zeros((0, 2), dtype=torch.int32, device="cuda:0")
+
+    def reduction(pairs):
+        r = E.barrier_reduce(ctx, sc, q, pairs, none, 1e-2, kappa, E.GRAD | E.HESS, hess=hess, count=False)
+        H = r["hess"].cpu().numpy() if hess == "dense" else E.bsr_to_dense(*r["hess"], 5)
+        return r["grad"].cpu().numpy(), H
+
+    (g, H), (g1, H1) = reduction(pt), reduction(pt[18:])
+    assert np.isfinite(H[:12, :12]).all() == (w == 1.0)
+    big = np.abs(H1[12:]).max()
+    assert 0 < big < 1e307
+    for a, b in ((H[12:], H1[12:]), (H[:, 12:], H1[:, 12:])):
+        assert np.abs(a - b).max() <= 1e-12 * big
+    assert np.abs(g[12:] - g1[12:]).max() <= 1e-12 * np.abs(g1[12:]).max()
