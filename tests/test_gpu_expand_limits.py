@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2409_16385_amd as E  # noqa: E402
-from scenes import scene as S  # noqa: E402
+from scenes import config2, scene as S  # noqa: E402
 
 
 def _dev(a):
@@ -87,3 +87,53 @@ def test_an_overflow_stays_with_its_pair(w, kappa, hess):
     for a, b in ((H[12:], H1[12:]), (H[:, 12:], H1[:, 12:])):
         assert np.abs(a - b).max() <= 1e-12 * big
     assert np.abs(g[12:] - g1[12:]).max() <= 1e-12 * np.abs(g1[12:]).max()
+
+
+def test_list_of_several_steps():
+    """A wavefront's table, the workgroup's accumulator and their flushes over
+    a range of several steps of 1,024 pairs: with one workgroup per CU config
+    2's edge pairs are 1,378 to a workgroup.  Against the default launch, one
+    step, which the sampled-oracle tests check."""
+    sc = config2()
+    ctx, ref = E.Context(0), E.Context(0)
+    q = _dev(sc.q)
+    pt, ee = E.build_candidates(ref, E.Scene.from_host(ref, sc), q, sc.dhat)
+    E.set_tuning(ctx, 2.0, [0, 1, 0, 0])
+    dsc = E.Scene.from_host(ctx, sc)
+    for n in (len(ee), len(ee) - 7777):
+        args = (q, pt, ee[:n], sc.dhat, sc.kappa)
+        a = E.barrier_reduce(ctx, dsc, *args)
+        b = E.barrier_reduce(ref, E.Scene.from_host(ref, sc), *args)
+        assert a["n_active"] == b["n_active"] > 350000
+        assert torch.equal(a["hess"][0], b["hess"][0]) and torch.equal(a["hess"][1], b["hess"][1])
+        assert _same(a["hess"][2], b["hess"][2]) and _same(a["grad"], b["grad"])
+        g = E.barrier_reduce(ctx, dsc, *args, flags=E.GRAD, hess=None)["grad"]
+        assert _same(g, b["grad"])
+
+
+@pytest.mark.parametrize("n_node,spread,most", [(16, 16, 4), (57, 57, 4), (400, 300, 4), (3000, 2500, 4)])
+@pytest.mark.parametrize("n", [1024 * 256 + 1, 1024 * 256 + 515, 1024 * 768 + 64 * 256])
+def test_repeated_list_of_several_steps(n_node, spread, most, n):
+    """The same over lists of few and of many nodes (the accumulator of 56 is
+    flushed at the end, between steps, or overflows): config 1's pairs listed
+    again and again against the sum of their one reduction."""
+    from test_gpu_expand import _rewired
+    import oracle as O
+    sc, x = _rewired(n_node, spread, most)
+    pt, _ = O.candidates_grid(sc, x, sc.dhat)
+    pt = pt[O.narrow(sc, x, 0, pt, sc.dhat)[2]]
+    m, rest = divmod(n, len(pt))
+    ctx = E.Context(0)
+    E.set_tuning(ctx, 2.0, [0, 1, 0, 0])
+    dsc = E.Scene.from_host(ctx, sc)
+    q, none = _dev(sc.q), _dev(np.zeros((0, 2), np.int32))
+    one, head = _dev(pt), _dev(pt[:rest])
+    args = (none, sc.dhat, sc.kappa, E.GRAD | E.HESS | E.PROJECT)
+    a = E.barrier_reduce(ctx, dsc, q, torch.cat([one.repeat(m, 1), head]), *args, hess="dense")
+    b = E.barrier_reduce(ctx, dsc, q, one, *args, hess="dense")
+    c = E.barrier_reduce(ctx, dsc, q, head, *args, hess="dense")
+    assert a["n_active"] == n
+    for k in ("grad", "hess"):
+        assert _same(a[k], m * b[k] + c[k])
+    g = E.barrier_reduce(ctx, dsc, q, torch.cat([one.repeat(m, 1), head]), none, sc.dhat, sc.kappa, E.GRAD, hess=None)
+    assert _same(g["grad"], m * b["grad"] + c["grad"])
