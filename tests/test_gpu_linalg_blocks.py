@@ -56,3 +56,26 @@ def test_first_bad_minor(ctx, n, bad):
     if bad + 70 < n:
         A[bad + 70, bad + 70] = float("nan")
     assert E.cholesky(ctx, A) == bad + 1
+
+
+@pytest.mark.parametrize("n,cond", [(64, 1e13), (200, 1e13), (500, 1e13), (500, 1e6)])
+def test_stiff_blocks(ctx, n, cond):
+    """Independent 12 x 12 blocks with eigenvalues over 13 decades (stiff
+    contacts; the blocks cross the factorization's tiles of 16): entry by
+    entry |A - L L^T|_ij <= c u sqrt(A_ii A_jj), the bound of substitution.
+    An entry has at most 12 products, c = 2 (12 + 4) with four more roundings
+    for the pivots and the solve, doubled; an error that grows with the
+    condition of the diagonal tiles is beyond it."""
+    rng = np.random.default_rng(0)
+    A = np.zeros((n, n))
+    for b in range(0, n, 12):
+        m = min(12, n - b)
+        Q, _ = np.linalg.qr(rng.normal(size=(m, m)))
+        A[b:b + m, b:b + m] = (Q * np.geomspace(1, 1 / cond, m)) @ Q.T
+    A = 0.5 * (A + A.T)
+    F = torch.as_tensor(A, device="cuda")
+    assert E.cholesky(ctx, F) == 0
+    L = np.tril(F.cpu().numpy()).astype(np.longdouble)
+    D = np.sqrt(np.diag(A))
+    R = np.abs((L @ L.T - A) / np.outer(D, D)).astype(float)
+    assert R.max() <= 2 * (12 + 4) * 1.1e-16
