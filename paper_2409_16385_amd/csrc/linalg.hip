@@ -33,17 +33,19 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   return __longlong_as_double(((uint64_t)hi << 32) | lo);
 }
 
-// Factors the 64x64 tile s (lower triangle; LDS) in place, by a workgroup of
-// four wavefronts.  Wavefront w holds columns 16 w .. 16 w + 15, lane = row:
+// Factors the 64x64 tile s (lower triangle; LDS) in place, by the first four
+// wavefronts of a workgroup.  Wavefront w holds columns 16 w .. 16 w + 15, lane = row:
 // in step p wavefront p factors its 16 columns for all rows, passing column
 // entries between lanes by readlane, and the later wavefronts apply them.
 // Bound by the serial chain of 64 pivots.  k0 + 64 may pass n: the caller
 // pads with the unit matrix.
 __device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k0, int64_t *info) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double a[16];
+  double a[16] = {};
+  if (w < 4) {
 #pragma unroll
-  for (int j = 0; j < 16; ++j) a[j] = s[lane][16 * w + j];
+    for (int j = 0; j < 16; ++j) a[j] = s[lane][16 * w + j];
+  }
   for (int p = 0; p < 4; ++p) {
     if (w == p) {
       int bad = NB;
@@ -71,7 +73,7 @@ __device__ __forceinline__ void chol_tile(double (*s)[NBP], int64_t n, int64_t k
       for (int j = 0; j < 16; ++j) s[lane][16 * p + j] = a[j];
     }
     __syncthreads();
-    if (w > p) {
+    if (w > p && w < 4) {
       double x[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) x[j] = s[lane][16 * p + j];
@@ -195,21 +197,30 @@ __global__ __launch_bounds__(256) void k_chol_panel(double *A, int64_t n, int64_
 }
 
 // Update A_ij -= P_i P_j^T of the lower tiles with columns in [r0, c_end),
-// P the K finished columns from kc (K a multiple of 16, kc + K <= r0).  Tile
-// TM x TM, four wavefronts each a quarter of it as (TM / 32)^2 products of
-// v_mfma_f64_16x16x4; the operands go through LDS 16 columns at a time, the
-// next 16 loaded into registers meanwhile.  TM = 128 halves the operand
-// traffic of 64 and serves the trailing matrix; TM = 64 serves the outer
-// block's few columns and short remainders, where 128 leaves most of the 256
-// CUs without a tile.  The first workgroup's tile holds the next diagonal
-// tile, which it factors at once.  tri: the grid is the packed lower
-// triangle of tiles, else (row tile, column tile).
+// P the K finished columns from kc (K a multiple of NB, kc + K <= r0).  Tile
+// TM x TM over 2 x 2 wavefronts (TM = 64) or 2 x 4 (TM = 128), each its part
+// of it as products of v_mfma_f64_16x16x4; the operands go through LDS 16
+// columns at a time, the next 16 loaded into registers meanwhile.  TM = 128
+// halves the operand traffic of 64 and serves the trailing matrix; TM = 64
+// serves the outer block's few columns and short remainders, where 128 leaves
+// most of the 256 CUs without a tile.
+// A run of products sums 64 columns and is then added to the tile's sum: one
+// run over all 256 doubled the factor's error (dense matrix of condition
+// 1e6, n = 1100: |A - L L^T| / |A| 4.2e-16; 2.2e-16 like this, as with 64
+// columns at a time).  The second set of sums takes the registers of four
+// wavefronts at TM = 128, hence eight (7,644 unknowns 9.95 and 9.60 ms).
+// The first workgroup's tile holds the next diagonal tile, which it factors
+// at once.  tri: the grid is the packed lower triangle of tiles, else (row
+// tile, column tile).
+constexpr int upd_threads(int tm) { return tm == 128 ? 512 : 256; }
+
 template <int TM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chol_update(double *A, int64_t n, int64_t lda, int64_t kc, int K, int64_t r0,
-                                                     int64_t c_end, int tri, int64_t *info) {
+__global__ __launch_bounds__(upd_threads(TM)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chol_update(
+    double *A, int64_t n, int64_t lda, int64_t kc, int K, int64_t r0, int64_t c_end, int tri, int64_t *info) {
   constexpr int KB = 16, KP = KB + 2;        // stride of 36 banks: 16 rows x 2 columns without conflict
-  constexpr int NLD = TM * KB / 256;         // loads per thread and operand
-  constexpr int MT = TM / 32;                // 16x16 products per wavefront and axis
+  constexpr int TH = upd_threads(TM), WC = TH / 128;  // wavefronts: 2 x WC
+  constexpr int NLD = TM * KB / TH;          // loads per thread and operand
+  constexpr int MT = TM / 32, MC = TM / WC / 16;  // 16x16 products per wavefront: rows, columns
   __shared__ union {
     struct {
       double a[TM][KP], b[TM][KP];
@@ -230,53 +241,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   const int64_t ri = r0 + TM * i, rj = r0 + TM * j;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int wr = (w >> 1) * (TM / 2), wc = (w & 1) * (TM / 2);
+  const int wr = (w / WC) * (TM / 2), wc = (w % WC) * (TM / WC);
   const int lr = lane & 15, lk = lane >> 4;
-  v4d acc[MT][MT];
+  v4d sum[MT][MC];
 #pragma unroll
   for (int u = 0; u < MT; ++u)
 #pragma unroll
-    for (int v = 0; v < MT; ++v) acc[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int v = 0; v < MC; ++v) sum[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
   double pa[NLD], pb[NLD];
   auto load = [&](int64_t k) {
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
-      const int e = u * 256 + t, r = e / KB, c = e % KB;
+      const int e = u * TH + t, r = e / KB, c = e % KB;
       // rows past n clamped: their products are not stored
       pa[u] = A[(ri + r < n ? ri + r : n - 1) * lda + k + c];
       pb[u] = A[(rj + r < n ? rj + r : n - 1) * lda + k + c];
     }
   };
   load(kc);
-  for (int k = 0; k < K; k += KB) {
-    __syncthreads();  // the previous chunk is consumed
+  for (int k0 = 0; k0 < K; k0 += NB) {
+    v4d acc[MT][MC];
 #pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int e = u * 256 + t, r = e / KB, c = e % KB;
-      sh.op.a[r][c] = pa[u];
-      sh.op.b[r][c] = pb[u];
-    }
-    __syncthreads();
-    load(kc + (k + KB < K ? k + KB : k));  // unconditional: a branch here moves the sums between register files
+    for (int u = 0; u < MT; ++u)
 #pragma unroll
-    for (int kk = 0; kk < KB; kk += 4) {
-      double fa[MT], fb[MT];
+      for (int v = 0; v < MC; ++v) acc[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int k = k0; k < k0 + NB; k += KB) {
+      __syncthreads();  // the previous chunk is consumed
 #pragma unroll
-      for (int u = 0; u < MT; ++u) {
-        fa[u] = sh.op.a[wr + 16 * u + lr][kk + lk];
-        fb[u] = sh.op.b[wc + 16 * u + lr][kk + lk];
+      for (int u = 0; u < NLD; ++u) {
+        const int e = u * TH + t, r = e / KB, c = e % KB;
+        sh.op.a[r][c] = pa[u];
+        sh.op.b[r][c] = pb[u];
       }
+      __syncthreads();
+      load(kc + (k + KB < K ? k + KB : k));  // unconditional: a branch here moves the sums between register files
 #pragma unroll
-      for (int u = 0; u < MT; ++u)
+      for (int kk = 0; kk < KB; kk += 4) {
+        double fa[MT], fb[MC];
 #pragma unroll
-        for (int v = 0; v < MT; ++v)
-          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[v], acc[u][v], 0, 0, 0);
+        for (int u = 0; u < MT; ++u) fa[u] = sh.op.a[wr + 16 * u + lr][kk + lk];
+#pragma unroll
+        for (int v = 0; v < MC; ++v) fb[v] = sh.op.b[wc + 16 * v + lr][kk + lk];
+#pragma unroll
+        for (int u = 0; u < MT; ++u)
+#pragma unroll
+          for (int v = 0; v < MC; ++v)
+            acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[v], acc[u][v], 0, 0, 0);
+      }
     }
+#pragma unroll
+    for (int u = 0; u < MT; ++u)
+#pragma unroll
+      for (int v = 0; v < MC; ++v) sum[u][v] += acc[u][v];
   }
   const bool first = i == 0 && j == 0;
   if (first) {
     __syncthreads();  // operands consumed: their space takes the diagonal tile
-    for (int e = t; e < NB * NB; e += 256) {
+    for (int e = t; e < NB * NB; e += TH) {
       const int r = e / NB, c = e % NB;
       sh.s[r][c] = r == c ? 1.0 : 0.0;
     }
@@ -286,9 +308,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // then its stores
 #pragma unroll
   for (int u = 0; u < MT; ++u) {
-    double x[MT][4];
+    double x[MC][4];
 #pragma unroll
-    for (int v = 0; v < MT; ++v)
+    for (int v = 0; v < MC; ++v)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         int64_t r = ri + wr + 16 * u + 4 * e + lk;
@@ -297,13 +319,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         x[v][e] = A[r * lda + (c <= r ? c : r)];
       }
 #pragma unroll
-    for (int v = 0; v < MT; ++v)
+    for (int v = 0; v < MC; ++v)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int tr = wr + 16 * u + 4 * e + lk, tc = wc + 16 * v + lr;
         const int64_t r = ri + tr, c = rj + tc;
         if (r < n && c <= r && c < c_end) {
-          const double y = x[v][e] - acc[u][v][e];
+          const double y = x[v][e] - sum[u][v][e];
           if (first && tr < NB && tc < NB)
             sh.s[tr][tc] = y;
           else
@@ -504,7 +526,7 @@ eipc_status eipc_cholesky(eipc_ctx *c, double *A, int64_t n, int64_t lda, int64_
       // while 128-tiles would be fewer than two per CU
       const int64_t nt = (n - r0 + 127) / 128, nblk = nt * (nt + 1) / 2;
       if (nblk >= 2 * (int64_t)c->num_cu)
-        k_chol_update<128><<<(unsigned)nblk, 256, 0, s>>>(A, n, lda, o0, OB, r0, n, 1, d_info);
+        k_chol_update<128><<<(unsigned)nblk, upd_threads(128), 0, s>>>(A, n, lda, o0, OB, r0, n, 1, d_info);
       else
         k_chol_update<64><<<(unsigned)(rem * (rem + 1) / 2), 256, 0, s>>>(A, n, lda, o0, OB, r0, n, 1, d_info);
     }

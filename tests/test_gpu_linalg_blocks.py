@@ -79,3 +79,52 @@ def test_stiff_blocks(ctx, n, cond):
     D = np.sqrt(np.diag(A))
     R = np.abs((L @ L.T - A) / np.outer(D, D)).astype(float)
     assert R.max() <= 2 * (12 + 4) * 1.1e-16
+
+
+def _spread(n, cond):
+    """Dense, eigenvalues over `cond` evenly in the logarithm."""
+    G = torch.as_tensor(np.random.default_rng(n).normal(size=(n, n)), device="cuda")
+    Q, _ = torch.linalg.qr(G)
+    A = (Q * torch.logspace(0, -np.log10(cond), n, dtype=torch.float64, device="cuda")) @ Q.T.contiguous()
+    return (0.5 * (A + A.T)).cpu().numpy()
+
+
+def _backward(L, A):
+    """|A - L L^T| / |A| in the Frobenius norm, from four products with
+    vectors of signs in extended precision."""
+    rng, LD, e = np.random.default_rng(1), np.longdouble, 0.0
+    for _ in range(4):
+        v = rng.choice([-1.0, 1.0], size=len(A)).astype(LD)
+        t, r = np.zeros_like(v), np.zeros_like(v)
+        for i in range(0, len(A), 256):
+            t += L[i:i + 256].T.astype(LD) @ v[i:i + 256]
+        for i in range(0, len(A), 256):
+            r[i:i + 256] = L[i:i + 256].astype(LD) @ t - A[i:i + 256].astype(LD) @ v
+        e += float((r * r).sum()) / 4
+    return np.sqrt(e) / np.linalg.norm(A)
+
+
+def _by_64(A):
+    """The same factorization in numpy, 64 columns at a time: each is
+    subtracted before the next 64 are summed."""
+    A, L = A.copy(), np.zeros_like(A)
+    for k in range(0, len(A), 64):
+        e = min(k + 64, len(A))
+        L[k:e, k:e] = np.linalg.cholesky(A[k:e, k:e])
+        for j in range(k, e):
+            L[e:, j] = (A[e:, j] - L[e:, k:j] @ L[j, k:j]) / L[j, j]
+        A[e:, e:] -= L[e:, k:e] @ L[e:, k:e].T
+    return L
+
+
+@pytest.mark.parametrize("n,cond", [(500, 1e6), (500, 1e13), (4700, 1e6)])
+def test_sums_of_64_columns(ctx, n, cond):
+    """The trailing update reads 256 columns at a time but sums no more than
+    64 in one go: its error is that of 64-column steps (measured at n = 500;
+    it does not depend on n), half again allowed for the other order."""
+    small = _spread(500, cond)
+    most = 1.5 * _backward(_by_64(small), small)
+    A = small if n == 500 else _spread(n, cond)
+    F = torch.as_tensor(A, device="cuda")
+    assert E.cholesky(ctx, F) == 0
+    assert _backward(np.tril(F.cpu().numpy()), A) <= most
