@@ -15,7 +15,6 @@
 namespace eipc {
 
 constexpr int EL_T = 256;
-constexpr int EL_L = 16;  // lanes to a tet (12 columns)
 
 // 3x3 row-major inverse by cofactors; returns the determinant
 __device__ __forceinline__ double inv3(const double *m, double *r) {
@@ -64,11 +63,14 @@ __device__ __forceinline__ void polar_rotation(const double *F, double *R) {
   for (int k = 0; k < 9; ++k) R[k] = X[k];
 }
 
-// 16 lanes to a tet: all compute its rotation, and 12 take a column of its
-// 12 x 12 matrix each, so that a wavefront's add covers four runs of three
-// consecutive entries per tet.  Bound by those adds (156 a tet).  One thread
-// to a tet left the mesh to few wavefronts, each add 64 lines: 15,288 tets 90
-// and 25 us.
+// EL lanes to a tet: all compute its rotation, then share out the 12 columns
+// of its matrix.  With the Hessian 16 (12 of them a column each), so that a
+// wavefront's add covers four runs of three consecutive entries per tet:
+// bound by those adds, 156 a tet (13,182 tets, one thread to a tet 117 us, 46
+// like this).  Without it the rotation is what counts: four lanes with three
+// entries of the gradient each (13,182 and 511,104 tets, one lane 17.5 and
+// 281 us, four 8.7 and 116, sixteen 10.8 and 205), and one for the energy
+// alone (511,104 tets: one 31, four 105, sixteen 396 us).
 // MODEL 0: small-strain linear elasticity,
 // psi = mu eps:eps + lam/2 tr(eps)^2 with eps = sym(F) - I, P = 2 mu eps +
 // lam tr(eps) I, Hessian the constant stiffness K0.  MODEL 1: linear
@@ -76,15 +78,15 @@ __device__ __forceinline__ void polar_rotation(const double *F, double *R) {
 // rotation of F, P = 2 mu (F - R) + lam tr(R^T F - I) R, Newton matrix the
 // warped stiffness R K0 R^T.  K0's (a, b) block is V (mu (g_b g_a^T +
 // (g_a.g_b) I) + lam g_a g_b^T) for the rest shape-function gradients g_a.
-template <int MODEL>
+template <int MODEL, int EL>
 __global__ __launch_bounds__(EL_T) void k_elastic(int n_tet, const int32_t *__restrict__ tets,
                                                   const double *__restrict__ rest, const double *__restrict__ vol,
                                                   double mu, double lam, const double *__restrict__ q, double scale,
                                                   double *energy, double *grad, double *hess, int64_t lda,
                                                   uint32_t *status) {
   __shared__ double s_e[EL_T / 64];
-  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / EL_L;
-  const int sub = threadIdx.x % EL_L;
+  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / EL;
+  const int sub = threadIdx.x % EL;
   double e = 0.0;
   if (t < n_tet && vol[t] > 0.0) {
     const double V = vol[t];
@@ -154,41 +156,46 @@ __global__ __launch_bounds__(EL_T) void k_elastic(int n_tet, const int32_t *__re
     }
     if (!ok) {
       atomicOr(status, ST_DEGENERATE);
-    } else if (sub < 12) {
+    } else {
       if (sub == 0) e = scale * V * psi;
-      // this lane's node b and coordinate j: a column of the element matrix
-      const int b = sub / 3, j = sub % 3;
-      int nb = nd[0];
-      double gb[3] = {g[0][0], g[0][1], g[0][2]};
 #pragma unroll
-      for (int a = 1; a < 4; ++a) {
-        nb = b == a ? nd[a] : nb;
+      for (int u = 0; u < (EL < 12 ? 12 / EL : 1); ++u) {
+        // this lane's node b and coordinate j: a column of the element matrix
+        const int col = sub + EL * u;
+        if (col >= 12 || (!grad && !hess)) break;
+        const int b = col / 3, j = col % 3;
+        int nb = nd[0];
+        double gb[3] = {g[0][0], g[0][1], g[0][2]};
 #pragma unroll
-        for (int c = 0; c < 3; ++c) gb[c] = b == a ? g[a][c] : gb[c];
-      }
-      double Rj[3], Pj[3];
+        for (int a = 1; a < 4; ++a) {
+          nb = b == a ? nd[a] : nb;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        Rj[c] = j == 0 ? R[c] : (j == 1 ? R[3 + c] : R[6 + c]);
-        Pj[c] = j == 0 ? P[c] : (j == 1 ? P[3 + c] : P[6 + c]);
-      }
-      if (grad)
-        atomicAdd(&grad[3 * (int64_t)nb + j], scale * V * (Pj[0] * gb[0] + Pj[1] * gb[1] + Pj[2] * gb[2]));
-      if (hess) {
-        // block(a, b) = V (mu (g_b g_a^T + (g_a . g_b) I) + lam g_a g_b^T),
-        // and with the model R block R^T: column j of it is R w
-        const double bR = gb[0] * Rj[0] + gb[1] * Rj[1] + gb[2] * Rj[2];
+          for (int c = 0; c < 3; ++c) gb[c] = b == a ? g[a][c] : gb[c];
+        }
+        double Rj[3], Pj[3];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const double gab = g[a][0] * gb[0] + g[a][1] * gb[1] + g[a][2] * gb[2];
-          const double aR = g[a][0] * Rj[0] + g[a][1] * Rj[1] + g[a][2] * Rj[2];
-          double w[3];
+        for (int c = 0; c < 3; ++c) {
+          Rj[c] = j == 0 ? R[c] : (j == 1 ? R[3 + c] : R[6 + c]);
+          Pj[c] = j == 0 ? P[c] : (j == 1 ? P[3 + c] : P[6 + c]);
+        }
+        if (grad)
+          atomicAdd(&grad[3 * (int64_t)nb + j], scale * V * (Pj[0] * gb[0] + Pj[1] * gb[1] + Pj[2] * gb[2]));
+        if (EL == 16 && hess) {
+          // block(a, b) = V (mu (g_b g_a^T + (g_a . g_b) I) + lam g_a g_b^T),
+          // and with the model R block R^T: column j of it is R w
+          const double bR = gb[0] * Rj[0] + gb[1] * Rj[1] + gb[2] * Rj[2];
 #pragma unroll
-          for (int k = 0; k < 3; ++k) w[k] = V * (mu * (gb[k] * aR + gab * Rj[k]) + lam * g[a][k] * bR);
+          for (int a = 0; a < 4; ++a) {
+            const double gab = g[a][0] * gb[0] + g[a][1] * gb[1] + g[a][2] * gb[2];
+            const double aR = g[a][0] * Rj[0] + g[a][1] * Rj[1] + g[a][2] * Rj[2];
+            double w[3];
 #pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            const double v = MODEL == 1 ? R[3 * i] * w[0] + R[3 * i + 1] * w[1] + R[3 * i + 2] * w[2] : w[i];
-            atomicAdd(&hess[(3 * (int64_t)nd[a] + i) * lda + 3 * (int64_t)nb + j], scale * v);
+            for (int k = 0; k < 3; ++k) w[k] = V * (mu * (gb[k] * aR + gab * Rj[k]) + lam * g[a][k] * bR);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              const double v = MODEL == 1 ? R[3 * i] * w[0] + R[3 * i + 1] * w[1] + R[3 * i + 2] * w[2] : w[i];
+              atomicAdd(&hess[(3 * (int64_t)nd[a] + i) * lda + 3 * (int64_t)nb + j], scale * v);
+            }
           }
         }
       }
@@ -312,13 +319,27 @@ eipc_status eipc_elastic(eipc_ctx *c, int32_t n_node, int32_t n_tet, const int32
   const double lam = young * poisson / ((1.0 + poisson) * (1.0 - 2.0 * poisson));
   const double mu = young / (2.0 * (1.0 + poisson));
   hipStream_t s = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)(((int64_t)n_tet * EL_L + EL_T - 1) / EL_T);
-  if (model == EIPC_ELASTIC_LINEAR)
-    k_elastic<0><<<blocks, EL_T, 0, s>>>(n_tet, tets, rest, vol, mu, lam, q, scale, energy, grad, hess, lda,
-                                         c->status);
-  else
-    k_elastic<1><<<blocks, EL_T, 0, s>>>(n_tet, tets, rest, vol, mu, lam, q, scale, energy, grad, hess, lda,
-                                         c->status);
+  // lanes to a tet, by what is asked for: see k_elastic
+  const int lanes = hess ? 16 : (grad ? 4 : 1);
+  const unsigned blocks = (unsigned)(((int64_t)n_tet * lanes + EL_T - 1) / EL_T);
+#define EL_CALL(M, L) \
+  k_elastic<M, L><<<blocks, EL_T, 0, s>>>(n_tet, tets, rest, vol, mu, lam, q, scale, energy, grad, hess, lda, c->status)
+  if (model == EIPC_ELASTIC_LINEAR) {
+    if (lanes == 16)
+      EL_CALL(0, 16);
+    else if (lanes == 4)
+      EL_CALL(0, 4);
+    else
+      EL_CALL(0, 1);
+  } else {
+    if (lanes == 16)
+      EL_CALL(1, 16);
+    else if (lanes == 4)
+      EL_CALL(1, 4);
+    else
+      EL_CALL(1, 1);
+  }
+#undef EL_CALL
   EIPC_HIP(c, hipGetLastError());
   return EIPC_OK;
 }
