@@ -361,23 +361,123 @@ struct TrsvTile {
 __device__ __forceinline__ void load_tri(TrsvTile &s, const double *L, int64_t n, int64_t lda, int64_t r0) {
   // all loads in flight together; rows past n and columns past the diagonal
   // are clamped and replaced
+  const bool two = r0 + TBH < n;  // a second half
   double v[3][16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
-    const int64_t a = r0 + r < n ? r0 + r : n - 1, b = r0 + TBH + r < n ? r0 + TBH + r : n - 1;
+    const int64_t a = r0 + r < n ? r0 + r : n - 1;
     v[0][u] = L[a * lda + (r0 + c <= a ? r0 + c : a)];
-    v[1][u] = L[b * lda + (r0 + c <= b ? r0 + c : b)];
-    v[2][u] = L[b * lda + (r0 + TBH + c <= b ? r0 + TBH + c : b)];
+  }
+  if (two) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
+      const int64_t b = r0 + TBH + r < n ? r0 + TBH + r : n - 1;
+      v[1][u] = L[b * lda + (r0 + c <= b ? r0 + c : b)];
+      v[2][u] = L[b * lda + (r0 + TBH + c <= b ? r0 + TBH + c : b)];
+    }
   }
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
-    const bool a = r0 + r < n, b = r0 + TBH + r < n;
-    s.d00[r][c] = a && c <= r ? v[0][u] : (r == c ? 1.0 : 0.0);
-    s.d10[r][c] = b ? v[1][u] : 0.0;
-    s.d11[r][c] = b && c <= r ? v[2][u] : (r == c ? 1.0 : 0.0);
+    s.d00[r][c] = r0 + r < n && c <= r ? v[0][u] : (r == c ? 1.0 : 0.0);
   }
+  if (two) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int r = u * 4 + (int)(threadIdx.x >> 6), c = threadIdx.x & 63;
+      const bool b = r0 + TBH + r < n;
+      s.d10[r][c] = b ? v[1][u] : 0.0;
+      s.d11[r][c] = b && c <= r ? v[2][u] : (r == c ? 1.0 : 0.0);
+    }
+  }
+}
+
+// The solves of one block's unknowns by one wavefront, rows lane and 64 +
+// lane, the solved unknown passed by readlane: na unknowns of the first half
+// and, with TWO, 64 of the second.  A last block of 64 rows or fewer takes na
+// steps and no second half.
+template <bool TWO, class N>
+__device__ __forceinline__ void solve_lower(const TrsvTile &s, int lane, N na, double &ta, double &tb) {
+  const double ia = 1.0 / s.d00[lane][lane];
+#pragma unroll 8
+  for (int j = 0; j < na; ++j) {
+    const double y = lane_value(ta * ia, j);
+    ta = lane == j ? ta : ta - s.d00[lane][j] * y;  // zero above the diagonal
+    if (TWO) tb -= s.d10[lane][j] * y;
+  }
+  ta *= ia;
+  if (TWO) {
+    const double ib = 1.0 / s.d11[lane][lane];
+#pragma unroll 8
+    for (int j = 0; j < TBH; ++j) {
+      const double y = lane_value(tb * ib, j);
+      tb = lane == j ? tb : tb - s.d11[lane][j] * y;
+    }
+    tb *= ib;
+  }
+}
+template <bool TWO, class N>
+__device__ __forceinline__ void solve_upper(const TrsvTile &s, int lane, N na, double &ta, double &tb) {
+  if (TWO) {
+    const double ib = 1.0 / s.d11[lane][lane];
+#pragma unroll 8
+    for (int j = TBH - 1; j >= 0; --j) {
+      const double x = lane_value(tb * ib, j);
+      tb = lane == j ? tb : tb - s.d11[j][lane] * x;  // zero above the diagonal
+      ta -= s.d10[j][lane] * x;
+    }
+    tb *= ib;
+  }
+  const double ia = 1.0 / s.d00[lane][lane];
+#pragma unroll 8
+  for (int j = na - 1; j >= 0; --j) {
+    const double x = lane_value(ta * ia, j);
+    ta = lane == j ? ta : ta - s.d00[j][lane] * x;
+  }
+  ta *= ia;
+}
+
+// Systems of up to 64 unknowns: one launch for both directions, four
+// right-hand sides to a workgroup, a wavefront each.  (In the blocked form
+// each right-hand side is a workgroup that fills 100 KiB of LDS, one to a CU:
+// 3 and 30 unknowns with 8,192 right-hand sides 127 and 248 us, 9 and 20 like
+// this; with one 12 and 10, and 8.)
+constexpr int TS_RHS = 4;
+
+__global__ __launch_bounds__(64 * TS_RHS) void k_trsv_small(const double *__restrict__ L, int n, int64_t lda, double *B,
+                                                            int64_t nrhs) {
+  __shared__ double d[TBH][TBH + 1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double v[TBH / TS_RHS];
+#pragma unroll
+  for (int u = 0; u < TBH / TS_RHS; ++u) {
+    const int r = u * TS_RHS + w < n ? u * TS_RHS + w : n - 1;
+    v[u] = L[r * lda + (lane <= r ? lane : r)];
+  }
+#pragma unroll
+  for (int u = 0; u < TBH / TS_RHS; ++u) {
+    const int r = u * TS_RHS + w;
+    d[r][lane] = r < n && lane <= r ? v[u] : (r == lane ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  const int64_t rhs = (int64_t)blockIdx.x * TS_RHS + w;
+  if (rhs >= nrhs) return;
+  const double inv = 1.0 / d[lane][lane];
+  double t = lane < n ? B[lane * nrhs + rhs] : 0.0;
+#pragma unroll 8
+  for (int j = 0; j < n; ++j) {
+    const double y = lane_value(t * inv, j);
+    t = lane == j ? t : t - d[lane][j] * y;  // zero above the diagonal
+  }
+  t *= inv;
+#pragma unroll 8
+  for (int j = n - 1; j >= 0; --j) {
+    const double x = lane_value(t * inv, j);
+    t = lane == j ? t : t - d[j][lane] * x;
+  }
+  if (lane < n) B[lane * nrhs + rhs] = t * inv;
 }
 
 // forward: block kb is solved (kb < 0: none yet); workgroup x updates block
@@ -426,20 +526,12 @@ __global__ __launch_bounds__(256) void k_trsv_lower(const double *__restrict__ L
     ta -= s.part[0][lane];
     tb -= s.part[0][TBH + lane];
   }
-  const double ia = 1.0 / s.d00[lane][lane], ib = 1.0 / s.d11[lane][lane];
-#pragma unroll 8
-  for (int j = 0; j < TBH; ++j) {
-    const double y = lane_value(ta * ia, j);
-    ta = lane == j ? ta : ta - s.d00[lane][j] * y;  // zero above the diagonal
-    tb -= s.d10[lane][j] * y;
-  }
-#pragma unroll 8
-  for (int j = 0; j < TBH; ++j) {
-    const double y = lane_value(tb * ib, j);
-    tb = lane == j ? tb : tb - s.d11[lane][j] * y;
-  }
-  if (ra < n) B[ra * nrhs + rhs] = ta * ia;
-  if (rb < n) B[rb * nrhs + rhs] = tb * ib;
+  if (r0 + TBH < n)
+    solve_lower<true>(s, lane, std::integral_constant<int, TBH>{}, ta, tb);
+  else
+    solve_lower<false>(s, lane, (int)(n - r0), ta, tb);
+  if (ra < n) B[ra * nrhs + rhs] = ta;
+  if (rb < n) B[rb * nrhs + rhs] = tb;
 }
 
 // backward, L^T x = y: block kb is solved (kb = number of blocks: none yet);
@@ -479,20 +571,12 @@ __global__ __launch_bounds__(256) void k_trsv_upper(const double *__restrict__ L
   const int64_t ra = r0 + lane, rb = r0 + TBH + lane;
   double ta = ra < n ? B[ra * nrhs + rhs] - part(lane) : 0.0;
   double tb = rb < n ? B[rb * nrhs + rhs] - part(TBH + lane) : 0.0;
-  const double ia = 1.0 / s.d00[lane][lane], ib = 1.0 / s.d11[lane][lane];
-#pragma unroll 8
-  for (int j = TBH - 1; j >= 0; --j) {
-    const double x = lane_value(tb * ib, j);
-    tb = lane == j ? tb : tb - s.d11[j][lane] * x;  // zero above the diagonal
-    ta -= s.d10[j][lane] * x;
-  }
-#pragma unroll 8
-  for (int j = TBH - 1; j >= 0; --j) {
-    const double x = lane_value(ta * ia, j);
-    ta = lane == j ? ta : ta - s.d00[j][lane] * x;
-  }
-  if (ra < n) B[ra * nrhs + rhs] = ta * ia;
-  if (rb < n) B[rb * nrhs + rhs] = tb * ib;
+  if (r0 + TBH < n)
+    solve_upper<true>(s, lane, std::integral_constant<int, TBH>{}, ta, tb);
+  else
+    solve_upper<false>(s, lane, (int)(n - r0), ta, tb);
+  if (ra < n) B[ra * nrhs + rhs] = ta;
+  if (rb < n) B[rb * nrhs + rhs] = tb;
 }
 
 }  // namespace eipc
@@ -543,6 +627,11 @@ eipc_status eipc_cholesky_solve(eipc_ctx *c, const double *L, int64_t n, int64_t
     return c ? set_err(c, EIPC_ERR_ARG, "bad solve arguments") : EIPC_ERR_ARG;
   EIPC_HIP(c, hipSetDevice(c->device));
   hipStream_t s = (hipStream_t)stream;
+  if (n > 0 && n <= TBH) {
+    k_trsv_small<<<(unsigned)((nrhs + TS_RHS - 1) / TS_RHS), 64 * TS_RHS, 0, s>>>(L, (int)n, lda, B, nrhs);
+    EIPC_HIP(c, hipGetLastError());
+    return EIPC_OK;
+  }
   const int64_t nt = (n + TB - 1) / TB;
   // right-hand sides go to the grid's second axis, in runs it can hold
   for (int64_t j0 = 0; j0 < nrhs; j0 += 65535) {

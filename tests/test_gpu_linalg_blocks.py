@@ -128,3 +128,41 @@ def test_sums_of_64_columns(ctx, n, cond):
     F = torch.as_tensor(A, device="cuda")
     assert E.cholesky(ctx, F) == 0
     assert _backward(np.tril(F.cpu().numpy()), A) <= most
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 31, 63, 64, 65, 100, 129, 190, 193])
+@pytest.mark.parametrize("nrhs", [1, 3, 4, 5, 1030])
+def test_solve_sizes(ctx, n, nrhs):
+    """Solves of one launch (64 unknowns) and in blocks of 128, the last of
+    one half or two, against the backward error of the factor test."""
+    rng = np.random.default_rng(1000 * n + nrhs)
+    F = np.tril(rng.normal(size=(n, n))) / np.sqrt(n) + 2 * np.eye(n)
+    rhs = rng.normal(size=(n, nrhs))
+    pad = np.full((n, n + 3), np.nan)  # only the lower triangle is read
+    pad[np.tril_indices(n)] = F[np.tril_indices(n)]
+    pad = torch.as_tensor(pad, device="cuda")
+    x = torch.as_tensor(rhs, device="cuda").clone()
+    ctx.check(B._load().eipc_cholesky_solve(ctx.handle, pad.data_ptr(), n, n + 3, x.data_ptr(), nrhs, ctx.stream()))
+    x = x.cpu().numpy()
+    A = np.abs(F) @ np.abs(F.T) @ np.abs(x) + np.abs(rhs)
+    assert (np.abs(F @ (F.T @ x) - rhs) <= 3 * 8 * max(n, 8) * 1.1e-16 * A).all()
+
+
+def test_small_systems_with_many_right_hand_sides(ctx):
+    """The work follows the size: 3 unknowns take less than half of 64."""
+    def ms(n):
+        F, x = torch.eye(n, dtype=torch.float64, device="cuda"), torch.ones((n, 65536), dtype=torch.float64, device="cuda")
+        best = np.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                E.cholesky_solve(ctx, F, x)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 5)
+        return best
+
+    t3, t64 = ms(3), ms(64)
+    print(f"3 unknowns {t3:.4f} ms, 64 {t64:.4f}")
+    assert t3 <= 0.5 * t64
