@@ -404,7 +404,7 @@ __device__ __forceinline__ void solve_lower(const TrsvTile &s, int lane, N na, d
 #pragma unroll 8
   for (int j = 0; j < na; ++j) {
     const double y = lane_value(ta * ia, j);
-    ta = lane == j ? ta : ta - s.d00[lane][j] * y;  // zero above the diagonal
+    ta = lane > j ? ta - s.d00[lane][j] * y : ta;  // not the zeros above the diagonal: y may be infinite
     if (TWO) tb -= s.d10[lane][j] * y;
   }
   ta *= ia;
@@ -413,7 +413,7 @@ __device__ __forceinline__ void solve_lower(const TrsvTile &s, int lane, N na, d
 #pragma unroll 8
     for (int j = 0; j < TBH; ++j) {
       const double y = lane_value(tb * ib, j);
-      tb = lane == j ? tb : tb - s.d11[lane][j] * y;
+      tb = lane > j ? tb - s.d11[lane][j] * y : tb;
     }
     tb *= ib;
   }
@@ -425,7 +425,7 @@ __device__ __forceinline__ void solve_upper(const TrsvTile &s, int lane, N na, d
 #pragma unroll 8
     for (int j = TBH - 1; j >= 0; --j) {
       const double x = lane_value(tb * ib, j);
-      tb = lane == j ? tb : tb - s.d11[j][lane] * x;  // zero above the diagonal
+      tb = lane < j ? tb - s.d11[j][lane] * x : tb;
       ta -= s.d10[j][lane] * x;
     }
     tb *= ib;
@@ -434,7 +434,7 @@ __device__ __forceinline__ void solve_upper(const TrsvTile &s, int lane, N na, d
 #pragma unroll 8
   for (int j = na - 1; j >= 0; --j) {
     const double x = lane_value(ta * ia, j);
-    ta = lane == j ? ta : ta - s.d00[j][lane] * x;
+    ta = lane < j ? ta - s.d00[j][lane] * x : ta;
   }
   ta *= ia;
 }
@@ -469,13 +469,13 @@ __global__ __launch_bounds__(64 * TS_RHS) void k_trsv_small(const double *__rest
 #pragma unroll 8
   for (int j = 0; j < n; ++j) {
     const double y = lane_value(t * inv, j);
-    t = lane == j ? t : t - d[lane][j] * y;  // zero above the diagonal
+    t = lane > j ? t - d[lane][j] * y : t;
   }
   t *= inv;
 #pragma unroll 8
   for (int j = n - 1; j >= 0; --j) {
     const double x = lane_value(t * inv, j);
-    t = lane == j ? t : t - d[j][lane] * x;
+    t = lane < j ? t - d[j][lane] * x : t;
   }
   if (lane < n) B[lane * nrhs + rhs] = t * inv;
 }

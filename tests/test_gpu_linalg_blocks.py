@@ -166,3 +166,16 @@ def test_small_systems_with_many_right_hand_sides(ctx):
     t3, t64 = ms(3), ms(64)
     print(f"3 unknowns {t3:.4f} ms, 64 {t64:.4f}")
     assert t3 <= 0.5 * t64
+
+
+@pytest.mark.parametrize("n,at", [(40, 20), (64, 63), (65, 30), (65, 64), (129, 20), (129, 100), (300, 150)])
+def test_an_infinite_unknown_stays_in_its_rows(ctx, n, at):
+    """An unknown that passes the range in the backward pass reaches the rows
+    before it (their products with it, 0 x Inf among them) and none after."""
+    L = np.eye(n)
+    L[at, at] = 1e-200
+    b = np.arange(1.0, n + 1)
+    x = torch.as_tensor(b[:, None], device="cuda").clone()
+    E.cholesky_solve(ctx, torch.as_tensor(L, device="cuda"), x)
+    x = x.cpu().numpy()[:, 0]
+    assert np.isinf(x[at]) and np.array_equal(x[at + 1:], b[at + 1:])
