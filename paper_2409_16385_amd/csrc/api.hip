@@ -308,7 +308,6 @@ eipc_status eipc_create(eipc_ctx **out, int32_t device, size_t reserve_bytes) {
   if (!c) return EIPC_ERR_HIP;
   c->device = device;
   if (hipSetDevice(device) != hipSuccess || hipMalloc(&c->status, 256) != hipSuccess ||
-      hipMalloc(&c->stats, 32 * sizeof(double)) != hipSuccess ||
       hipMalloc(&c->counters, 16 * sizeof(int64_t)) != hipSuccess ||
       hipHostMalloc((void **)&c->host_res, 64 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
       hipMemset(c->status, 0, 256) != hipSuccess || hipMemset(c->counters, 0, 16 * sizeof(int64_t)) != hipSuccess) {
@@ -356,7 +355,6 @@ void eipc_destroy(eipc_ctx *c) {
   }
   free_retired(c);
   if (c->status) hipFree(c->status);
-  if (c->stats) hipFree(c->stats);
   if (c->host_res) hipHostFree(c->host_res);
   if (c->counters) hipFree(c->counters);
   if (c->fork_ev) hipEventDestroy(c->fork_ev);

@@ -104,26 +104,6 @@ __device__ __forceinline__ V3 load3(const double *xs, int n, int v) {
   return r;
 }
 
-// global destination of a 3x3 block (I <= J)
-__device__ __forceinline__ void global_block_add(const HessOut &h, int n_node, int64_t I, int64_t J,
-                                                 const double *B, uint32_t *status) {
-  if (h.kind == 1) {
-    const int64_t n3 = 3 * (int64_t)n_node;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) atomicAdd(&h.dense[(3 * (int64_t)I + i) * n3 + 3 * J + j], B[3 * i + j]);
-  } else if (h.kind == 2) {
-    const int64_t slot = table_slot64((long long *)h.hkey, h.hmask, (long long)(I * n_node + J), GLOBAL_PROBE);
-    if (slot < 0) {
-      atomicOr(status, ST_HASH_OVERFLOW);
-      return;
-    }
-#pragma unroll
-    for (int t = 0; t < 9; ++t) atomicAdd(&h.hval[9 * (int64_t)slot + t], B[t]);
-  }
-}
-
 // A workgroup's LDS table of node 3-vectors keyed by node.
 struct LdsTables {
   uint32_t *gkey;
@@ -275,7 +255,8 @@ __device__ __forceinline__ void agg_scene_add(double *out, bool valid, int scene
 // w Q[a] (3 numbers per node and pair) a pair adds
 //   B(I, J)[r][c] += sum_{alpha, beta} z_I[alpha] X[3 alpha + r][3 beta + c] z_J[beta]
 // to the 3x3 block of its nodes I and J.  Pairs come in locality order: a run
-// of tens of them touches 16 nodes or fewer (47 to 94 pairs on the grasp).
+// of tens of them touches 16 nodes or fewer (on the grasp 19 point-triangle
+// or 35 edge pairs, on average, before a table is put out).
 // A wavefront keeps a table of up to 16 nodes and, for each of the six (r, c)
 // with r <= c, the 16 x 16 matrix over (I, J) in four registers per lane;
 // four pairs are one product with K = (pair, alpha) = 12:
@@ -1132,7 +1113,8 @@ eipc_status launch_barrier(eipc_ctx *c, const eipc_scene *sc, int kind, const do
                            double dhat, double kappa, uint32_t flags, double *energy, double *grad,
                            const HessOut &h, hipStream_t s) {
   if (max_count == 0) return EIPC_OK;
-  // node ids are packed with 4 bits of slot in the expansion's sort
+  // the interface's limit (a reduction that packed node ids with four bits
+  // set it); larger systems stay refused
   if (sc->n_node >= (1 << 27)) return set_err(c, EIPC_ERR_ARG, "n_node must be below 2^27");
   const bool want_g = (flags & EIPC_GRAD) && grad;
   const bool want_h = (flags & EIPC_HESS) && h.kind != 0;

@@ -37,7 +37,7 @@ enum BufId {
   B_CAND_PT, B_CAND_EE,  // swept candidates (CCD)
   B_HKEY, B_HVAL,        // global block hash
   B_ROWCNT, B_ROWFILL, B_ROWPTR, B_BCOL, B_BSRC, B_BBLK, B_BCOL2, B_BSRC2,
-  B_PG_PT, B_PG_EE, B_PX_PT, B_PX_EE,  // per-pair gradient / Hessian in the Q basis
+  B_PX_PT, B_PX_EE,                    // per-pair term records (gradient and Hessian in the Q basis)
   B_STEP_PT, B_STEP_EE,                // candidates of a planned step
   B_ALPHA,                             // per-scene step bound bits
   B_PLAN_OUT,                          // outputs of the reserving step of a plan
@@ -95,7 +95,6 @@ struct eipc_ctx {
   char err[512] = {0};
   eipc::DevBuf buf[eipc::B_NUM];
   uint32_t *status = nullptr;   // device status word
-  double *stats = nullptr;      // device [32] reduction scratch
   int64_t *counters = nullptr;  // device [16] counters
   // Scratch.  Grow mode (no reservation): each buffer is allocated on
   // first need and replaced by a larger one when a call needs more; the

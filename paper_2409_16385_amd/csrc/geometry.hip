@@ -1218,12 +1218,6 @@ __global__ __launch_bounds__(RANK_T) void k_seg_rank(const int32_t *__restrict__
   }
 }
 
-static uint32_t next_pow2(uint64_t v) {
-  uint64_t p = 1;
-  while (p < v) p <<= 1;
-  return (uint32_t)p;
-}
-
 template <int KIND, int MODE>
 static void launch_query(int nq, const double *xs, const double *x1s, int n_vert, double h, const QueryArgs &qa,
                          int32_t *cnt, const int64_t *off, int32_t *out, int64_t cap, unsigned long long *total,

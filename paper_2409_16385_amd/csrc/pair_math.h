@@ -704,8 +704,6 @@ __device__ __forceinline__ void project_psd(double *a) {
     }
 }
 
-__device__ __forceinline__ void project_psd9(double *a) { project_psd<9>(a); }
-
 // Symmetric eigendecomposition of a packed N x N matrix by the same cyclic
 // Jacobi sweeps: on return the diagonal of a holds the eigenvalues and the
 // columns of v (row-major N x N) the eigenvectors.
@@ -747,21 +745,6 @@ __device__ __forceinline__ void x_block(const double *X, int a, int b, double *B
           acc += (kS[a][al] * kS[b][be] > 0) ? x : -x;
         }
       B[i * 3 + j] = 0.25 * acc;
-    }
-}
-
-// gradient over the 4 slots from the Y basis: g_x[a] = sum_J T[J][a] gY[J]
-template <int KIND>
-__device__ __forceinline__ void slot_grad(const double *gY, double *gx) {
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      double acc = 0.0;
-#pragma unroll
-      for (int J = 0; J < 3; ++J)
-        if (kT[KIND][J][a] != 0) acc += kT[KIND][J][a] * gY[3 * J + i];
-      gx[3 * a + i] = acc;
     }
 }
 
