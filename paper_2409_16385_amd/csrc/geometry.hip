@@ -574,6 +574,7 @@ __device__ __forceinline__ void big_cell(const int *c0, const int *c1, int c, in
 // count (histogram) or reserves the bucket's range (fill).  An entry whose
 // probe finds neither its bucket nor a free slot within LT_PROBE steps goes
 // to the global counters directly; its bucket then never enters the table.
+
 // parts, at most, of a large box in a short list: its cells in turn
 constexpr int LQ_PARTS = 32;
 
@@ -583,7 +584,10 @@ constexpr int LQ_PARTS = 32;
 // and 20 us, of a sheet 76 and 29 (both launches), of the grasp (825
 // workgroups of 256 items) 157 and 104, its candidates 733 and 632 us as a
 // whole.  Where the chip is full they only add divisions: the batch (above
-// 4,000 workgroups) 271 and 409 us.
+// 4,000 workgroups) 271 and 409 us.  The line, 1,024 workgroups, lies well
+// below that: single grasps gain little from there on (candidates with one
+// thread and with four: 725 workgroups 485 and 447 us, 1,084 791 and 720,
+// 2,115 1,889 and 1,782, 4,822 8,880 and 8,743), the batch loses much.
 constexpr int lt_items(int q) { return q == 1 ? 256 : 128; }
 constexpr int lt_threads(int q) { return q * lt_items(q); }
 constexpr int LT_FEW = 4;       // four threads to an item below this many workgroups of 256 items per CU
@@ -1524,6 +1528,14 @@ constexpr int JOUT = 1024;  // candidates staged per wavefront
 // one lane to a row, 104 with two, 92 with four, 131 with eight; EE 244 and
 // 194 with one and two; the sphere's 5,072 PT rows 93 us and, with eight, 18;
 // plate PT 100 and 68, but EE 107 and 121 (21 partners a row on average).
+// The lines (a list takes 8 lanes up to 40,960 PT or 20,480 EE rows, an EE
+// list 4 up to 40,960), with both sides in us:
+//   PT, 4 and 8 lanes: 747 rows 11.5 and 9.6, 5,105 17.3 and 13.9, 15,411
+//   21.1 and 21.4, 27,989 24.8 and 34.2, 52,868 44.6 and 54.7;
+//   EE, 2, 4 and 8 lanes: the sphere's 23,493 rows, whose ground edges share
+//   buckets with everything, 22.0, 18.6 and 26.3; grasps of 5,338 rows 11.3,
+//   9.9 and 11.2, 18,945 14.6, 15.3 and 21.1, 34,254 16.0, 21.7 and 31.7.
+// So short lists of long buckets set them; they cost even lists up to 10 us.
 constexpr int JLANES[2] = {2, 1};
 constexpr int JSPLIT = 3;
 constexpr int JSWG[2] = {10, 5};
