@@ -272,11 +272,12 @@ __device__ __forceinline__ void agg_scene_add(double *out, bool valid, int scene
 // full) goes straight to the outputs.  Between steps the accumulator is
 // flushed into the outputs once it holds more than LN / 2 nodes (each
 // touched block once).
-// What bounds it, 352,809 edge pairs of the grasp (310 us, 92,789 products,
-// 10,101 tables put out; 2,048 wavefronts at a time): 35% of a wavefront's
-// time in the products (21 instructions of 64 cycles each, shared by two
-// wavefronts), 20% in waits for records and rows of W, 15% at the barriers
-// of unequal runs, 8% in finding slots, 6% in putting tables out.  The
+// What bounds it, 352,809 edge pairs of the grasp (276 us; the shares were
+// counted in a build that took 310: 92,789 products, 10,101 tables put out;
+// 2,048 wavefronts at a time): 35% of a wavefront's time in the products (21
+// instructions of 64 cycles each, shared by two wavefronts), 20% in waits for
+// records and rows of W, 15% at the barriers of unequal runs, 8% in finding
+// slots, 6% in putting tables out.  The
 // earlier form, one block per lane and 9 LDS atomics per block and pair (41
 // blocks a pair), was bound by those atomics at 37 cycles per wavefront
 // instruction: 405 us.

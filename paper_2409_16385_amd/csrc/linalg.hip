@@ -346,9 +346,9 @@ __global__ __launch_bounds__(upd_threads(TM)) __attribute__((amdgpu_waves_per_eu
 // TB unknowns.  Launch k subtracts the solved block k from every remaining
 // block (one workgroup each), and the workgroup of the next block then
 // solves it, so a launch needs only what earlier launches finished.  Bound
-// by the chain of n / TB launches.  The TB x TB diagonal block waits in LDS
-// meanwhile; one wavefront solves it with two rows per lane, the solved
-// unknown passed by readlane.
+// by the chain of n / TB launches, 15 us each.  The TB x TB diagonal block
+// waits in LDS meanwhile; one wavefront solves it with two rows per lane, the
+// solved unknown passed by readlane.
 // ---------------------------------------------------------------------------
 constexpr int TB = 128;
 constexpr int TBH = TB / 2;
